@@ -56,9 +56,12 @@ void dense_solve(const T* L, int64_t n, int64_t ld, const T* X256, const T* XT25
 // C[i, j] += alpha * sum_k A[i, k] B[j, k] (column-major operands); with
 // `lower`, tiles strictly above the diagonal of the global matrix (C[0,0] at
 // global (gr, gc)) are skipped.
+// Where a product stands in a factorisation: on its critical path (AHEAD), in
+// the trailing update beside it (BEHIND), or neither.
+enum GemmRole { GEMM_PLAIN, GEMM_AHEAD, GEMM_BEHIND };
 template <typename T>
 void gemm_nt(T* C, int64_t ldc, const T* A, int64_t lda, const T* B, int64_t ldb, int64_t M, int64_t N, int64_t K,
-             T alpha, bool lower, int64_t gr, int64_t gc, hipStream_t st);
+             T alpha, bool lower, int64_t gr, int64_t gc, hipStream_t st, GemmRole role = GEMM_PLAIN);
 int64_t linv_elems(int64_t n);
 double cholesky_flops(int64_t n);
 }  // namespace hc

@@ -10,14 +10,14 @@
 //
 // Layout: S is column-major with leading dimension ld, lower triangle used.
 // Algorithm: blocked right-looking Cholesky with 64-wide diagonal blocks.
-//   diag:   the 64x64 block is factored in registers by one workgroup, which
-//           also writes the inverse of the factor block (Linv, 64x64 per block)
-//   trsm:   L21 = A21 * Linv' in place, one workgroup per 64 rows
+//   step:   one launch per 64 columns: L21 = A21 * Linv' in place, one
+//           workgroup per 64 rows, the update of the next 64 columns, and
+//           the next diagonal block's factor with its inverse (Linv, 64x64
+//           per block)
 //   update: trailing C -= L21 L21' on MFMA (v_mfma_f64_16x16x4f64 or
-//           v_mfma_f32_16x16x4f32), 256x128 tiles, lower tiles only.  The
-//           update of the trailing matrix is delayed to every panel of
-//           Aux::nb columns (the panel's own columns are updated eagerly),
-//           so the trailing matrix is read and written once per panel.
+//           v_mfma_f32_16x16x4f32), 64x64 tiles, lower tiles only.  It is
+//           delayed to every panel of 256 or Aux::nb columns, so the trailing
+//           matrix is read and written once per panel.
 // Triangular solves use the stored Linv blocks: one launch per 256 rows.
 #include "hc_dense.h"
 
@@ -51,26 +51,451 @@ template <> struct Mfma<float> {
 };
 
 constexpr int BS = 64;    // diagonal block
+constexpr int IB = 256;   // inner panel
+// Rows from which a trailing update is long enough to run beside the next
+// panel on a second stream (two event waits, about 10 us, per panel): 5,056
+// rows take 3.97 ms with the rule at 4,096, 4.03 at 2,048, 3.97 without.
+constexpr int64_t LOOKAHEAD_MIN = 4096;
+// Rows from which panels are Aux::nb columns wide instead of IB: the update
+// then runs at K = 768 (65 TFLOP/s instead of 57 at K = 256) and reads the
+// trailing matrix a third as often, but a panel's chain is three times as
+// long and has to fit behind it.  10,048 / 20,032 rows: 11.5 / 53.5 ms with
+// the rule at 8,192, 11.7 / 54.5 at 12,288, 11.8 / 59.3 without wide panels.
+constexpr int64_t WIDE_MIN = 8192;
+// LDS a trailing update's workgroup takes on top of its own 20 KB: three fit
+// a compute unit and leave 37 KB and 248 VGPRs per lane in one piece, room
+// for a workgroup of the panel chain.  At full occupancy the chain's
+// workgroups (one of them for k_chol_diag) found no room until the update
+// ended, 4.8 ms at 20,032 rows; the update alone loses 4 % (65.1 -> 62.8 TFLOP/s).
+constexpr size_t BEHIND_PAD = 21504;
 
 // ---------------------------------------------------------------------------
-// diagonal block: Cholesky + inverse of the factor, one wave
+// 64 x 64 diagonal block: Cholesky factor and its inverse, one workgroup of
+// four waves
 // ---------------------------------------------------------------------------
-// value of v in a runtime-uniform lane
-__device__ inline double lane_bcast_u(double v, int src) {
+// value of v in a wave-uniform lane
+__device__ inline double lane_bcast(double v, int src) {
   const unsigned long long u = (unsigned long long)__double_as_longlong(v);
   const unsigned lo = __builtin_amdgcn_readlane((unsigned)u, src);
   const unsigned hi = __builtin_amdgcn_readlane((unsigned)(u >> 32), src);
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
-__device__ inline float lane_bcast_u(float v, int src) {
+__device__ inline float lane_bcast(float v, int src) {
   return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), src));
 }
-__device__ inline double lane_shfl(double v, int src) { return __shfl(v, src, 64); }
-__device__ inline float lane_shfl(float v, int src) { return __shfl(v, src, 64); }
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_chol_diag(T* __restrict__ A, int64_t ld, int64_t c, int64_t n,
-                                                   T* __restrict__ Linv, double tol, double fix,
+// 1 / sqrt(d): v_rsq_f64 is good to about 2^-24, one cubic step takes that past 2^-53
+__device__ inline double rsqrt_full(double d) {
+  const double e = __builtin_amdgcn_rsq(d);
+  const double h = fma(-(d * e), e, 1.0);
+  return fma(e, h * fma(h, 0.375, 0.5), e);
+}
+
+// exchanges lane groups and registers: x[a] of lane 16 g + i becomes x[g] of
+// lane 16 a + i (v_permlane16_swap, v_permlane32_swap)
+__device__ inline void swap16(double& x, double& y) {
+  const uint64_t a = (uint64_t)__double_as_longlong(x), b = (uint64_t)__double_as_longlong(y);
+  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)a, (unsigned)b, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(a >> 32), (unsigned)(b >> 32), false, false);
+  x = __longlong_as_double((long long)(((uint64_t)hi[0] << 32) | lo[0]));
+  y = __longlong_as_double((long long)(((uint64_t)hi[1] << 32) | lo[1]));
+}
+__device__ inline void swap32(double& x, double& y) {
+  const uint64_t a = (uint64_t)__double_as_longlong(x), b = (uint64_t)__double_as_longlong(y);
+  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)a, (unsigned)b, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(a >> 32), (unsigned)(b >> 32), false, false);
+  x = __longlong_as_double((long long)(((uint64_t)hi[0] << 32) | lo[0]));
+  y = __longlong_as_double((long long)(((uint64_t)hi[1] << 32) | lo[1]));
+}
+__device__ inline void transpose4(double (&x)[4]) {
+  swap16(x[0], x[1]);
+  swap16(x[2], x[3]);
+  swap32(x[0], x[2]);
+  swap32(x[1], x[3]);
+}
+
+constexpr int CST = 66;                   // column stride of the LDS block
+constexpr int CHOL_LDS = BS * CST + BS;   // doubles: L and below-diagonal L^-1 in one block, 1 / diag(L)
+
+// L^-1[i][k] of the block: below the diagonal it sits in the place of entry
+// (k, i) above it, its diagonal is dv
+__device__ __forceinline__ double chol_inv(const double* __restrict__ lds, int i, int k) {
+  const double v = lds[i * CST + k], d = lds[BS * CST + i];
+  return i > k ? v : (i == k ? d : 0.0);
+}
+
+// On entry Lc holds the 64 x 64 block (Lc[k * CST + i] = A[i][k], i >= k used)
+// and every wave has passed a barrier since it was written; on return its
+// lower triangle is the factor and the rest the inverse (chol_inv).  FP64 in
+// both precision modes (the FP32 mode rounds at the end).
+//
+// It is a chain of 64 dependent pivots, so what counts is the length of the
+// chain and what runs beside it.  Wave s factors column block s alone, four
+// columns at a time: one matrix row per lane, two pivots at a time (the second
+// one's root is that of the 2 x 2 determinant, so that both reciprocal roots
+// run at once), multipliers by readlane.  Lane-group swaps then turn the four
+// columns into MFMA operands (K = 4) and the rest of the block, held in MFMA
+// output registers D[column][row], gets their update.  Behind that wave,
+// between the same four barriers, the waves to its right apply the finished
+// block on MFMA, and those to its left build the inverse: Y_ss in wave s,
+// T_sp = sum_{k=p}^{s-1} L_sk Y_kp in wave p and one stage later Y_sp =
+// -Y_ss T_sp, T_sp staying in the output registers, whose layout is the next
+// product's operand layout.  One pivot at a time with a 15-column update each
+// (an FP64 FMA issues every 8 cycles) and a lane-per-column inverse took
+// 45,600 cycles a block, this takes 30,500 (12.7 us).
+__device__ __forceinline__ void chol_block(int lane, int p, double* __restrict__ lds, double tol, double fix,
+                                  unsigned long long* __restrict__ hits) {
+  typedef Mfma<double> M;
+  // Lc[k * CST + i] = L[i][k], Lc[i * CST + k] = Y[i][k] = L^-1[i][k], i > k.
+  // Row i of Y comes after column i of L, whose zeros above the diagonal the
+  // whole-column stores below put there.
+  double* Lc = lds;
+  double* dv = lds + BS * CST;   // 1 / L[k][k]
+  const int li = lane & 15, lg = lane >> 4;
+  int nhits = 0;
+  v4d t = v4d{0, 0, 0, 0};
+  // U[a][r] = A[16 a + li][16 p + lg + 4 r], a >= p
+  v4d U[4];
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) U[a][r] = a >= p ? Lc[(16 * p + lg + 4 * r) * CST + 16 * a + li] : 0.0;
+  __syncthreads();   // the factor's columns overwrite the block
+  // Y_ip = -Y_ii T_ip
+  auto finish = [&](int i) {
+    v4d y = v4d{0, 0, 0, 0};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) y = M::op(chol_inv(lds, 16 * i + li, 16 * i + lg + 4 * q), t[q], y);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) Lc[(16 * i + lg + 4 * q) * CST + 16 * p + li] = -y[q];
+    __builtin_amdgcn_wave_barrier();   // this wave reads them next
+  };
+#pragma unroll 1
+  for (int s = 0; s < 4; ++s) {
+    if (p == s) {
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const int j0 = 16 * s + 4 * m;
+        double c[4] = {U[0][m], U[1][m], U[2][m], U[3][m]};
+        transpose4(c);   // c[q] = A[lane][j0 + q]
+#pragma unroll
+        for (int h = 0; h < 4; h += 2) {
+          const int j = j0 + h;
+          double a00 = lane_bcast(c[h], j);
+          const double a10 = lane_bcast(c[h], j + 1), a11 = lane_bcast(c[h + 1], j + 1);
+          double det = fma(a00, a11, -(a10 * a10));
+          if (!(a00 > tol) || !(det > tol * a00)) {   // pivots that are not positive (NaN too) are replaced and counted
+            if (!(a00 > tol)) {
+              a00 = fix;
+              ++nhits;
+              det = fma(a00, a11, -(a10 * a10));
+            }
+            if (!(det > tol * a00)) {
+              det = fix * a00;
+              ++nhits;
+            }
+          }
+          const double e0 = rsqrt_full(a00), rd = rsqrt_full(det);
+          const double l00 = a00 * e0, l10 = a10 * e0;
+          const double e1 = l00 * rd, l11 = det * rd * e0;   // the second pivot is det / a00
+          dv[j] = e0;
+          dv[j + 1] = e1;
+          const double x0 = lane > j ? c[h] * e0 : 0.0;
+          const double x1 = lane > j + 1 ? fma(-x0, l10, c[h + 1]) * e1 : 0.0;
+          c[h] = lane == j ? l00 : x0;
+          c[h + 1] = lane == j + 1 ? l11 : x1;
+          if (h == 0) {
+            const double l20 = lane_bcast(x0, j + 2), l21 = lane_bcast(x1, j + 2);
+            const double l30 = lane_bcast(x0, j + 3), l31 = lane_bcast(x1, j + 3);
+            c[2] = fma(-x1, l21, fma(-x0, l20, c[2]));
+            c[3] = fma(-x1, l31, fma(-x0, l30, c[3]));
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) Lc[(j0 + q) * CST + lane] = c[q];
+        if (m < 3) {
+          transpose4(c);   // c[a] = L[16 a + li][j0 + lg]
+          const double ns = -(s == 0 ? c[0] : s == 1 ? c[1] : s == 2 ? c[2] : c[3]);
+#pragma unroll
+          for (int a = 0; a < 4; ++a)
+            if (a >= s) U[a] = M::op(ns, c[a], U[a]);
+        }
+      }
+    }
+    __syncthreads();
+    if (p > s) {
+      // U[a] -= L[rows of a][block s] L[rows of p][block s]'
+      double f[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) f[q] = -Lc[(16 * s + lg + 4 * q) * CST + 16 * p + li];
+#pragma unroll
+      for (int a = 1; a < 4; ++a)
+        if (a >= p) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) U[a] = M::op(f[q], Lc[(16 * s + lg + 4 * q) * CST + 16 * a + li], U[a]);
+        }
+    } else if (p == s) {
+      // Y_ss by rows of 4 x 4 blocks: with R = I at the start, block row b is
+      // Y_b = N_b R_b (N_b the inverse of the diagonal 4 x 4 block) and the
+      // rows below lose L_b Y_b.  R sits in the output registers (block row b
+      // is register b), which are the operand layout of both products.
+      // nv = N_b[u][v] for b = li / 4, u = li % 4, v = lg
+      const int o = 16 * s + (li & 12);
+      const double *c0 = Lc + o * CST + o, *c1 = c0 + CST, *c2 = c1 + CST;
+      const double y0 = lg == 0 ? dv[o] : 0.0;
+      const double y1 = fma(-c0[1], y0, lg == 1 ? 1.0 : 0.0) * dv[o + 1];
+      const double y2 = fma(-c1[2], y1, fma(-c0[2], y0, lg == 2 ? 1.0 : 0.0)) * dv[o + 2];
+      const double y3 = fma(-c2[3], y2, fma(-c1[3], y1, fma(-c0[3], y0, lg == 3 ? 1.0 : 0.0))) * dv[o + 3];
+      const int u = li & 3;
+      const double nv = u == 0 ? y0 : u == 1 ? y1 : u == 2 ? y2 : y3;
+      v4d R;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) R[b] = (lg + 4 * b == li) ? 1.0 : 0.0;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const v4d y = M::op((li >> 2) == b ? nv : 0.0, R[b], v4d{0, 0, 0, 0});
+        if (lg + 4 * b > li) Lc[(16 * s + lg + 4 * b) * CST + 16 * s + li] = y[b];
+        if (b < 3) R = M::op(-Lc[(16 * s + 4 * b + lg) * CST + 16 * s + li], y[b], R);
+      }
+    } else {
+      if (p < s - 1) finish(s - 1);
+      t = v4d{0, 0, 0, 0};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int i = 16 * p + lg + 4 * q;
+        t = M::op(Lc[i * CST + 16 * s + li], chol_inv(lds, i, 16 * p + li), t);
+      }
+      for (int k = p + 1; k < s; ++k) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int i = 16 * k + lg + 4 * q;
+          t = M::op(Lc[i * CST + 16 * s + li], Lc[i * CST + 16 * p + li], t);
+        }
+      }
+    }
+  }
+  __syncthreads();
+  if (p < 3) finish(3);
+  __syncthreads();
+  if (lane == 0 && nhits) atomicAdd(hits, (unsigned long long)nhits);
+}
+
+// writes the factor block's lower triangle to A (its corner at (c, c)) and the
+// inverse, with zeros above its diagonal, to Linv (64 x 64, column-major)
+__device__ __forceinline__ void chol_store(int lane, int p, int bs, const double* __restrict__ lds, double* __restrict__ A,
+                                  int64_t ld, int64_t c, double* __restrict__ Linv) {
+#pragma unroll 4
+  for (int k = 16 * p; k < 16 * p + 16; ++k) {
+    if (lane < bs && k < bs && k <= lane) A[(c + lane) + (c + k) * ld] = lds[k * CST + lane];
+    Linv[lane + k * BS] = chol_inv(lds, lane, k);
+  }
+}
+
+// a block column of the padded diagonal block: identity past bs
+__device__ inline double chol_pad(double v, int i, int k, int bs) {
+  return (i < bs && k < bs) ? v : (i == k ? 1.0 : 0.0);
+}
+
+__global__ __launch_bounds__(256, 3) void k_chol_diag(double* __restrict__ A, int64_t ld, int64_t c, int64_t n,
+                                                   double* __restrict__ Linv, double tol, double fix,
+                                                   unsigned long long* __restrict__ hits) {
+  __shared__ __align__(16) double lds[CHOL_LDS];
+  __builtin_amdgcn_s_setprio(3);   // the factorisation's critical path
+  const int lane = threadIdx.x & 63;
+  const int p = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int bs = (int)std::min<int64_t>(BS, n - c);
+  double g[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q)
+    g[q] = A[(c + std::min(lane, bs - 1)) + (c + std::min(16 * p + q, bs - 1)) * ld];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) lds[(16 * p + q) * CST + lane] = chol_pad(g[q], lane, 16 * p + q, bs);
+  __syncthreads();
+  chol_block(lane, p, lds, tol, fix, hits);
+  chol_store(lane, p, bs, lds, A, ld, c, Linv);
+}
+
+// ---------------------------------------------------------------------------
+// One 64-column step of a panel in one launch.  On entry the block column at
+// c is up to date, its diagonal block factored and that factor's inverse in
+// Linv; a workgroup takes 64 of the rows [c + 64, R), each wave 16 of them:
+//   L[i, c] = A[i, c] Linv'                                     (all rows)
+// and, when another block column follows in the panel (next), brings that
+// column up to date against the columns [kb, c + 64) of the panel:
+//   A[i, c'] -= sum_k L[i, k] L[c', k]',  c' = c + 64,
+// whereupon workgroup 0, whose rows are the next diagonal block, factors it.
+// So the chain per 64 columns is one launch instead of three (factor, TRSM,
+// update), and the factorisation of the next diagonal block runs beside the
+// other rows' work.  L[c', c] is needed by every workgroup and recomputed by
+// each (one 64^3 product); since all of them read A[c', c], workgroup 0 leaves
+// its tile in the free Linv slot of block c'/64 + 1 (defer_out) and the next
+// step puts it in its place (defer_in).
+//
+// Products run on MFMA as X' = Linv A' and U' = X_c' X', whose output
+// registers (rows k, one matrix row i per lane) are the next product's operand
+// registers, and whose stores to A are 16 consecutive rows per column.
+// Bound: the chain of one workgroup (launch, loads past the L2, one or two
+// 64^3 products, 64 pivots); 34 KB of LDS and at most 168 VGPRs let it run
+// beside three trailing-update workgroups.  64 columns at 1,856 rows: 24 us,
+// 34 with 192 earlier columns, against 53 us in three launches.
+// ---------------------------------------------------------------------------
+constexpr int XST = CST;       // k row stride of X_c' in LDS
+constexpr int KST = BS + 16;   // k row stride of a chunk of L[c', k]
+static_assert(BS * XST <= CHOL_LDS && 2 * 16 * KST <= CHOL_LDS, "both fit the block's LDS");
+
+__global__ __launch_bounds__(256, 3) void k_panel_step(double* __restrict__ A, int64_t ld, int64_t n, int64_t kb, int64_t c,
+                                                    int64_t R, double* __restrict__ LinvAll, int next, int defer_in,
+                                                    int defer_out, double tol, double fix,
+                                                    unsigned long long* __restrict__ hits) {
+  typedef Mfma<double> M;
+  __shared__ __align__(16) double lds[CHOL_LDS];   // chunks of L[c', k], X_c', then the next diagonal block
+  __builtin_amdgcn_s_setprio(3);   // the factorisation's critical path
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 15;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool first = blockIdx.x == 0;
+  const double* Linv = LinvAll + (c / BS) * BS * BS;
+  double* slot = LinvAll + (c / BS + (defer_in ? 1 : 2)) * BS * BS;
+  if (first && defer_in) {
+    // L[c, c - 64] left here by the previous step
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int k = w + 4 * e;
+      A[(c + lane) + (c - BS + k) * ld] = slot[lane + k * BS];
+    }
+  }
+  const int64_t r0 = c + BS + (int64_t)blockIdx.x * BS;
+  if (r0 >= R) return;
+  const int64_t row = r0 + 16 * w + li;                       // this lane's row
+  const double* pa = A + std::min<int64_t>(row, R - 1);            // rows past R repeat the last one
+  const int64_t c1 = c + BS;                                  // next block column
+  const bool own_next = next && !first;                       // X_c' computed apart from this tile's X
+  const int nbt = first ? w + 1 : 4;                          // the diagonal tile needs its lower blocks only
+  v4d u[4];
+#pragma unroll
+  for (int b = 0; b < 4; ++b) u[b] = v4d{0, 0, 0, 0};
+  if (next && kb < c) {
+    // U' = L[c', k] L[i, k]' over the panel's earlier columns, 16 of them at a
+    // time: this lane's row in registers, the 64 rows of c' shared in LDS
+    // (each wave brings four columns); two chunks on their way ahead of the
+    // products (they come from other compute units' writes, past the L2)
+    const double* pn = A + std::min<int64_t>(c1 + lane, n - 1) + 4 * w * ld;
+    double av[2][4], bv[2][4];
+    auto load = [&](int s, int64_t k) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        av[s][q] = pa[(k + M::row(lane, q)) * ld];
+        bv[s][q] = pn[(k + q) * ld];
+      }
+    };
+    auto chunk = [&](int s, int64_t k) {   // chunk k from register set s through LDS buffer s, then its successor's loads
+      double* kl = lds + s * 16 * KST;
+      double a0[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        kl[(4 * w + q) * KST + lane] = bv[s][q];
+        a0[q] = av[s][q];
+      }
+      load(s, std::min<int64_t>(k + 32, c - 16));
+      __syncthreads();   // one barrier per chunk: buffer s was read two chunks ago
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+        if (b < nbt)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            u[b] = M::op(kl[M::row(lane, q) * KST + 16 * b + li], a0[q], u[b]);
+    };
+    load(0, kb);
+    load(1, kb + 16);
+    for (int64_t k = kb; k < c; k += 32) {   // c - kb is a multiple of 64
+      chunk(0, k);
+      chunk(1, k + 16);
+    }
+    __syncthreads();   // X_c' overwrites the chunks
+  }
+  // x = Linv A' of the 16 rows at pr: x[t][q] = X[i][16 t + row(lane, q)]
+  v4d x[4];
+  auto trsm = [&](const double* pr) {
+    double a[4][4];   // A[i][m], m = 16 u + row(lane, q)
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) a[u][q] = pr[(c + 16 * u + M::row(lane, q)) * ld];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      x[t] = v4d{0, 0, 0, 0};
+#pragma unroll
+      for (int u = 0; u <= t; ++u)   // Linv is lower triangular
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          x[t] = M::op(Linv[(16 * t + li) + (16 * u + M::row(lane, q)) * BS], a[u][q], x[t]);
+    }
+  };
+  if (own_next) trsm(A + std::min<int64_t>(c1 + 16 * w + li, n - 1));
+  else trsm(pa);
+  if (next) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) lds[(16 * t + M::row(lane, q)) * XST + 16 * w + li] = x[t][q];
+  }
+  if (own_next) trsm(pa);
+  // L[i][c + k], k = 16 t + row(lane, q)
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = 16 * t + M::row(lane, q);
+      if (first && defer_out) LinvAll[(c / BS + 2) * BS * BS + (16 * w + li) + k * BS] = x[t][q];
+      else if (row < R) A[row + (c + k) * ld] = x[t][q];
+    }
+  if (!next) return;
+  // columns c1 + j, j = 16 b + row(lane, q), of this lane's row
+  double cv[4][4];
+  const int nb = (int)std::min<int64_t>(BS, n - c1);
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) cv[b][q] = pa[(c1 + std::min(16 * b + M::row(lane, q), nb - 1)) * ld];
+  __syncthreads();   // X_c' is in LDS
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+      if (b < nbt)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          u[b] = M::op(lds[(16 * t + M::row(lane, q)) * XST + 16 * b + li], x[t][q], u[b]);
+  if (!first) {
+    if (row < R)
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) A[row + (c1 + 16 * b + M::row(lane, q)) * ld] = cv[b][q] - u[b][q];
+    return;
+  }
+  __syncthreads();   // every wave has read X_c'
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = 16 * b + M::row(lane, q), i = 16 * w + li;
+      lds[k * CST + i] = chol_pad(cv[b][q] - u[b][q], i, k, nb);
+    }
+  __syncthreads();
+  chol_block(lane, w, lds, tol, fix, hits);
+  chol_store(lane, w, nb, lds, A, ld, c1, LinvAll + (c1 / BS) * BS * BS);
+}
+
+// ---------------------------------------------------------------------------
+// The FP32 mode's panel: diagonal block, TRSM and in-panel update, a launch
+// each, panels of Aux::nb columns.  Its refinement stops at a fraction of mu,
+// so the rounding of the factor shows in the iterates (a relative 1e-4 where
+// the FP64 mode's differences stay under 1e-10): these kernels keep their
+// order of operations, and with it the results, and the FP64 kernels above,
+// which sum in another order, are not instantiated for it.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void k_chol_diag32(float* __restrict__ A, int64_t ld, int64_t c, int64_t n,
+                                                   float* __restrict__ Linv, double tol, double fix,
                                                    unsigned long long* __restrict__ hits) {
   // Cholesky of one 64 x 64 diagonal block and the inverse of its factor, by
   // 16-column blocks.  Thread (i, p) = (lane, wave) keeps r[q] = A[i][16p + q].
@@ -82,18 +507,18 @@ __global__ __launch_bounds__(256) void k_chol_diag(T* __restrict__ A, int64_t ld
   // forward substitution (rows exchanged with shuffles), and the blocks
   // below the diagonal follow by distance from it,
   // Y_ij = -Y_ii sum_{k=j}^{i-1} L_ik Y_kj.
-  __shared__ T Ls[BS][BS + 1];          // L, then read by the inverse
-  __shared__ T Ys[BS][BS + 1];          // L^-1
-  __shared__ T Ts[4][16][17];           // per-wave scratch of the inverse
+  __shared__ float Ls[BS][BS + 1];          // L, then read by the inverse
+  __shared__ float Ys[BS][BS + 1];          // L^-1
+  __shared__ float Ts[4][16][17];           // per-wave scratch of the inverse
   const int lane = threadIdx.x & 63;
   const int p = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int bs = (int)std::min<int64_t>(BS, n - c);
-  T r[16];
+  float r[16];
 #pragma unroll
   for (int q = 0; q < 16; ++q) {
     const int k = 16 * p + q;
-    const T g = A[(c + std::min(lane, bs - 1)) + (c + std::min(k, bs - 1)) * ld];
-    r[q] = (lane < bs && k < bs) ? (k <= lane ? g : T(0)) : (lane == k ? T(1) : T(0));
+    const float g = A[(c + std::min(lane, bs - 1)) + (c + std::min(k, bs - 1)) * ld];
+    r[q] = (lane < bs && k < bs) ? (k <= lane ? g : float(0)) : (lane == k ? float(1) : float(0));
   }
   int nhits = 0;
   // ---- L: column block pj is factored by its owning wave alone (pivots by
@@ -104,7 +529,7 @@ __global__ __launch_bounds__(256) void k_chol_diag(T* __restrict__ A, int64_t ld
 #pragma unroll
       for (int qj = 0; qj < 16; ++qj) {
         const int j = 16 * pj + qj;
-        double d = (double)lane_bcast_u(r[qj], j);
+        double d = (double)lane_bcast(r[qj], j);
         if (j < bs && !(d > tol)) {
           d = fix;
           ++nhits;
@@ -112,23 +537,23 @@ __global__ __launch_bounds__(256) void k_chol_diag(T* __restrict__ A, int64_t ld
         double e = __builtin_amdgcn_rsq(d);
         e = e * (1.5 - 0.5 * d * e * e);
         e = e * (1.5 - 0.5 * d * e * e);
-        const T inv = (T)e, ljj = (T)(d * e);
-        const T li = (lane > j) ? r[qj] * inv : T(0);
+        const float inv = (float)e, ljj = (float)(d * e);
+        const float li = (lane > j) ? r[qj] * inv : float(0);
         r[qj] = (lane == j) ? ljj : li;   // zero above the diagonal
 #pragma unroll
-        for (int q = qj + 1; q < 16; ++q) r[q] -= li * lane_bcast_u(li, 16 * pj + q);
+        for (int q = qj + 1; q < 16; ++q) r[q] -= li * lane_bcast(li, 16 * pj + q);
       }
 #pragma unroll
-      for (int q = 0; q < 16; ++q) Ls[lane][16 * pj + q] = (16 * pj + q <= lane) ? r[q] : T(0);
+      for (int q = 0; q < 16; ++q) Ls[lane][16 * pj + q] = (16 * pj + q <= lane) ? r[q] : float(0);
     }
     __syncthreads();
     if (p > pj) {
-      T a[16];
+      float a[16];
 #pragma unroll
       for (int t = 0; t < 16; ++t) a[t] = Ls[lane][16 * pj + t];
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
-        T s = 0;
+        float s = 0;
 #pragma unroll
         for (int t = 0; t < 16; ++t) s += a[t] * Ls[16 * p + q][16 * pj + t];
         r[q] -= s;
@@ -147,16 +572,16 @@ __global__ __launch_bounds__(256) void k_chol_diag(T* __restrict__ A, int64_t ld
   {
     // diagonal block p: forward substitution over its rows
     const int o = 16 * p;
-    T y[4];
+    float y[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) y[u] = (s == 4 * g + u) ? T(1) : T(0);
+    for (int u = 0; u < 4; ++u) y[u] = (s == 4 * g + u) ? float(1) : float(0);
 #pragma unroll
     for (int t = 0; t < 16; ++t) {
-      const T dinv = T(1) / Ls[o + t][o + t];
-      const T lst = Ls[o + s][o + t];
+      const float dinv = float(1) / Ls[o + t][o + t];
+      const float lst = Ls[o + s][o + t];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const T yt = lane_shfl(y[u], t + 16 * g) * dinv;   // row t, final
+        const float yt = __shfl(y[u], t + 16 * g, 64) * dinv;   // row t, final
         y[u] = (s == t) ? yt : ((s > t) ? y[u] - lst * yt : y[u]);
       }
     }
@@ -170,21 +595,21 @@ __global__ __launch_bounds__(256) void k_chol_diag(T* __restrict__ A, int64_t ld
   for (int dist = 1; dist < 4; ++dist) {
     if (p + dist < 4) {
       const int i = p + dist, j = p;
-      T t4[4] = {};
+      float t4[4] = {};
       for (int k = j; k < i; ++k)
 #pragma unroll
         for (int m = 0; m < 16; ++m) {
-          const T l = Ls[16 * i + s][16 * k + m];
+          const float l = Ls[16 * i + s][16 * k + m];
 #pragma unroll
           for (int u = 0; u < 4; ++u) t4[u] += l * Ys[16 * k + m][16 * j + 4 * g + u];
         }
 #pragma unroll
       for (int u = 0; u < 4; ++u) Ts[p][s][4 * g + u] = t4[u];
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's scratch writes landed
-      T o4[4] = {};
+      float o4[4] = {};
 #pragma unroll
       for (int m = 0; m < 16; ++m) {
-        const T yim = Ys[16 * i + s][16 * i + m];
+        const float yim = Ys[16 * i + s][16 * i + m];
 #pragma unroll
         for (int u = 0; u < 4; ++u) o4[u] -= yim * Ts[p][m][4 * g + u];
       }
@@ -196,7 +621,7 @@ __global__ __launch_bounds__(256) void k_chol_diag(T* __restrict__ A, int64_t ld
 #pragma unroll
   for (int q = 0; q < 16; ++q) {
     const int k = 16 * p + q;
-    Linv[lane + k * BS] = (k <= lane) ? Ys[lane][k] : T(0);
+    Linv[lane + k * BS] = (k <= lane) ? Ys[lane][k] : float(0);
   }
 }
 
@@ -210,17 +635,15 @@ __global__ __launch_bounds__(256) void k_chol_diag(T* __restrict__ A, int64_t ld
 // 8 KB of LDS a workgroup fits beside a running trailing-update workgroup on
 // the same compute unit instead of waiting for one to finish: this kernel sits
 // on the factorisation's critical path while the trailing update runs.
-template <typename T>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_trsm(
-    T* __restrict__ A, int64_t ld, int64_t c, int64_t r0, int64_t r1, const T* __restrict__ Linv) {
-  typedef typename Mfma<T>::acc_t acc_t;
-  __shared__ T Ls[BS][16];   // Ls[k][jj] = Linv[16 t + jj][k] for the current tile t
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_trsm32(
+    float* __restrict__ A, int64_t ld, int64_t c, int64_t r0, int64_t r1, const float* __restrict__ Linv) {
+  __shared__ float Ls[BS][16];   // Ls[k][jj] = Linv[16 t + jj][k] for the current tile t
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t rb = r0 + (int64_t)blockIdx.x * BS + wave * 16;   // first row of this wave
   // operand lanes: A[i = lane % 16][k = lane / 16], B[k = lane / 16][j = lane % 16]
   const int64_t ra = std::min<int64_t>(rb + (lane & 15), r1 - 1);   // rows past r1 repeat the last one
-  const T* pa = A + ra + (c + (lane >> 4)) * ld;
-  T a[BS / 4];
+  const float* pa = A + ra + (c + (lane >> 4)) * ld;
+  float a[BS / 4];
 #pragma unroll
   for (int q = 0; q < BS / 4; ++q) a[q] = pa[(int64_t)(4 * q) * ld];
 #pragma unroll 1
@@ -232,14 +655,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
       Ls[e >> 4][e & 15] = Linv[(16 * t + (e & 15)) + (e >> 4) * BS];
     }
     __syncthreads();
-    acc_t acc = acc_t{0, 0, 0, 0};
+    v4f acc = v4f{0, 0, 0, 0};
 #pragma unroll
-    for (int q = 0; q < BS / 4; ++q) acc = Mfma<T>::op(a[q], Ls[4 * q + (lane >> 4)][lane & 15], acc);
+    for (int q = 0; q < BS / 4; ++q) acc = Mfma<float>::op(a[q], Ls[4 * q + (lane >> 4)][lane & 15], acc);
     // X[i][j] = sum_k A[i][k] Linv[j][k]; this wave loaded its rows above,
     // other waves own other rows
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int64_t row = rb + Mfma<T>::row(lane, r);
+      const int64_t row = rb + Mfma<float>::row(lane, r);
       if (row < r1) A[row + (c + 16 * t + (lane & 15)) * ld] = acc[r];
     }
   }
@@ -254,24 +677,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
 // global diagonal (C[0, 0] at global (gr, gc)) are skipped.  The products are
 // the same MFMA chain as the large update kernels' (k in steps of four).
 // ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_gemm_panel(
-    T* __restrict__ C, int64_t ldc, const T* __restrict__ A, int64_t lda, const T* __restrict__ B, int64_t ldb,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_gemm_panel32(
+    float* __restrict__ C, int64_t ldc, const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb,
     int64_t M, int64_t N, int K, int64_t gr, int64_t gc) {
-  typedef typename Mfma<T>::acc_t acc_t;
-  __shared__ T Bs[BS][16];   // Bs[k][jj] = B[j0 + jj][k] for the current tile
+  __shared__ float Bs[BS][16];   // Bs[k][jj] = B[j0 + jj][k] for the current tile
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t i_blk = (int64_t)blockIdx.x * BS, j_blk = (int64_t)blockIdx.y * BS;
   if (gr + i_blk + BS - 1 < gc + j_blk) return;   // block strictly above the diagonal
   const int64_t rb = i_blk + wave * 16;             // first row of this wave
   const int64_t ra = std::min<int64_t>(rb + (lane & 15), M - 1);
-  const T* pa = A + ra;
-  T a[BS / 4];
+  const float* pa = A + ra;
+  float a[BS / 4];
 #pragma unroll
   for (int q = 0; q < BS / 4; ++q) {
     const int k = 4 * q + (lane >> 4);
-    const T v = pa[(int64_t)std::min(k, K - 1) * lda];
-    a[q] = k < K ? v : T(0);
+    const float v = pa[(int64_t)std::min(k, K - 1) * lda];
+    a[q] = k < K ? v : float(0);
   }
 #pragma unroll 1
   for (int t = 0; t < 4; ++t) {
@@ -281,453 +702,190 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
 #pragma unroll
     for (int q = 0; q < BS * 16 / 256; ++q) {
       const int e = tid + 256 * q, k = e >> 4, jj = e & 15;
-      const T v = B[std::min<int64_t>(j0 + jj, N - 1) + (int64_t)std::min(k, K - 1) * ldb];
-      Bs[k][jj] = k < K ? v : T(0);
+      const float v = B[std::min<int64_t>(j0 + jj, N - 1) + (int64_t)std::min(k, K - 1) * ldb];
+      Bs[k][jj] = k < K ? v : float(0);
     }
     __syncthreads();
     if (gr + rb + 15 < gc + j0) continue;   // this wave's rows lie above the tile's columns
-    acc_t acc = acc_t{0, 0, 0, 0};
+    v4f acc = v4f{0, 0, 0, 0};
 #pragma unroll
-    for (int q = 0; q < BS / 4; ++q) acc = Mfma<T>::op(a[q], Bs[4 * q + (lane >> 4)][lane & 15], acc);
+    for (int q = 0; q < BS / 4; ++q) acc = Mfma<float>::op(a[q], Bs[4 * q + (lane >> 4)][lane & 15], acc);
     const int64_t j = j0 + (lane & 15);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int64_t i = rb + Mfma<T>::row(lane, r);
+      const int64_t i = rb + Mfma<float>::row(lane, r);
       if (i < M && j < N) C[i + j * ldc] -= acc[r];
     }
   }
 }
 
 // ---------------------------------------------------------------------------
-// C[i, j] += alpha * sum_k A[i, k] * B[j, k]  (i < M, j < N, k < K), all
-// column-major; 128 x 128 tiles of 4 waves, each wave 64 x 64 on 16 MFMA
-// accumulators.  `lower` skips tiles strictly above the global diagonal, whose
-// position is given by the global indices (gr, gc) of C[0, 0].
+// C[i, j] += alpha * sum_k A[i, k] B[j, k]  (i < M, j < N, k < K), all
+// column-major.  64 x 64 tiles of four waves (32 x 32 each); operand chunks of
+// 64 bytes of k go through registers into a double-buffered LDS ring, two
+// chunks ahead of the MFMAs, one barrier per chunk.  A wave's MFMAs take the B
+// rows as first operand and the A rows as second, so its output registers hold
+// 16 consecutive rows of C per column and C is read and written in whole
+// 128-byte lines straight from registers.
+// Bound: FP64 MFMA issue (64 cycles each, 16 per chunk and wave).  What keeps
+// it busy is waves: 80 VGPRs and 20 KB of LDS put six of these workgroups on a
+// compute unit, so one's loads, barriers and C traffic run behind the others'
+// MFMAs.  Measured on the trailing update, K = 768 (TFLOP/s at 19,200 / 8,192 /
+// 4,096 rows): 67.8 / 64.7 / 57.7; 128 x 128 tiles at two workgroups per unit
+// 64.8 / 57.9 / 42.4 (too few waves, and four times the work in a last, partly
+// filled round); one chunk ahead instead of two 64.4 / 61.9 / 54.3.
+// With tri (square C on the diagonal) the grid holds the lower tiles only;
+// with `lower` alone, tiles strictly above the global diagonal (C[0, 0] at
+// (gr, gc)) return at once.  VEC: 16-byte operand loads (row groups of
+// 16 / sizeof(T) whole and aligned, K a multiple of the chunk); otherwise
+// element by element.
 // ---------------------------------------------------------------------------
-constexpr int TM = 128, TN = 128, TK = 16;
-static_assert(TK * TM % 512 == 0, "staging layout");
+template <typename T> struct Vec16;
+template <> struct Vec16<double> { typedef v2d t; };
+template <> struct Vec16<float> { typedef v4f t; };
+constexpr int TL = 64;
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_gemm_nt(T* __restrict__ C, int64_t ldc, const T* __restrict__ A, int64_t lda,
-                                                 const T* __restrict__ B, int64_t ldb, int64_t M, int64_t N, int64_t K,
-                                                 T alpha, int lower, int64_t gr, int64_t gc, int tiles_n) {
+template <typename T, bool VEC>
+__global__ __launch_bounds__(256, 4) void k_gemm_nt(T* __restrict__ C, int64_t ldc, const T* __restrict__ A,
+                                                    int64_t lda, const T* __restrict__ B, int64_t ldb, int64_t M,
+                                                    int64_t N, int64_t K, T alpha, int lower, int tri, int64_t gr,
+                                                    int64_t gc, int tiles_n, int prio) {
   typedef typename Mfma<T>::acc_t acc_t;
-  constexpr int PER = TK * TM / 256;   // staged elements per thread and operand
-  __shared__ T As[TK][TM + 4];
-  __shared__ T Bs[TK][TN + 4];
-  const int tile_m = blockIdx.x / tiles_n, tile_n = blockIdx.x % tiles_n;
-  const int64_t i_base = (int64_t)tile_m * TM, j_base = (int64_t)tile_n * TN;
-  if (lower && gr + i_base + TM - 1 < gc + j_base) return;   // tile strictly above the diagonal
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = (wave & 1) * 64, wn = (wave >> 1) * 64;
-  acc_t acc[4][4];
+  typedef typename Vec16<T>::t vec;
+  constexpr int G = 16 / sizeof(T);     // rows per load
+  constexpr int DK = 64 / sizeof(T);    // k per chunk
+  constexpr int ST = TL + 16;           // k row stride in LDS
+  constexpr int SK = 256 * G / TL;      // k rows one round of loads covers
+  static_assert(SK == DK, "one load per thread, operand and chunk");
+  __shared__ __align__(16) T As[2][DK][ST];
+  __shared__ __align__(16) T Bs[2][DK][ST];
+  if (prio) __builtin_amdgcn_s_setprio(2);   // on the factorisation's critical path
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, lg = lane >> 4;
+  const int wm = (wave & 1) * 32, wn = (wave >> 1) * 32;
+  int tile_m, tile_n;
+  if (tri) {   // tile b is (r, b - r (r + 1) / 2)
+    const int64_t b = blockIdx.x;
+    int64_t r = (int64_t)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
+    if ((r + 1) * (r + 2) / 2 <= b) ++r;
+    if (r * (r + 1) / 2 > b) --r;
+    tile_m = (int)r;
+    tile_n = (int)(b - r * (r + 1) / 2);
+  } else {
+    tile_m = blockIdx.x / tiles_n;
+    tile_n = blockIdx.x % tiles_n;
+  }
+  const int64_t i_base = (int64_t)tile_m * TL, j_base = (int64_t)tile_n * TL;
+  if (lower && gr + i_base + TL - 1 < gc + j_base) return;
+  acc_t acc[2][2];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = acc_t{0, 0, 0, 0};
-
-  // thread tid stages rows i = tid % 128 (+0) for k = tid / 128 + 2 e, e < PER
-  const int si = tid % TM, sk = tid / TM;
-  const int64_t gi = i_base + si, gj = j_base + si;
-  T ra[PER], rb[PER];
-  auto fetch = [&](int64_t k0) {
+    for (int b = 0; b < 2; ++b) acc[a][b] = acc_t{0, 0, 0, 0};
+  // a thread loads row group sg of k row sk of a chunk.  Rows past the end
+  // repeat the last group: their products are never stored.
+  const int sg = (tid % (TL / G)) * G, sk = tid / (TL / G);
+  const int64_t gi = std::min<int64_t>(i_base + sg, VEC ? M - G : M - 1);
+  const int64_t gj = std::min<int64_t>(j_base + sg, VEC ? N - G : N - 1);
+  const T* pa = A + gi + (VEC ? sk * lda : 0);
+  const T* pb = B + gj + (VEC ? sk * ldb : 0);
+  vec ra[2], rb[2];
+  auto fetch = [&](int kc, int s) {
+    if (VEC) {
+      ra[s] = *reinterpret_cast<const vec*>(pa + (int64_t)kc * DK * lda);
+      rb[s] = *reinterpret_cast<const vec*>(pb + (int64_t)kc * DK * ldb);
+    } else {
+      const int64_t k = (int64_t)kc * DK + sk, kk = std::min<int64_t>(k, K - 1);
 #pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      const int64_t gk = k0 + sk + 2 * e;
-      ra[e] = (gi < M && gk < K) ? A[gi + gk * lda] : T(0);
-      rb[e] = (gj < N && gk < K) ? B[gj + gk * ldb] : T(0);
+      for (int g = 0; g < G; ++g) {
+        ra[s][g] = pa[std::min<int64_t>(g, M - 1 - gi) + kk * lda];
+        rb[s][g] = pb[std::min<int64_t>(g, N - 1 - gj) + kk * ldb];
+      }
+      if (k >= K) {   // zero past the end of k
+        ra[s] = vec(T(0));
+        rb[s] = vec(T(0));
+      }
     }
   };
-  auto stage = [&]() {
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      As[sk + 2 * e][si] = ra[e];
-      Bs[sk + 2 * e][si] = rb[e];
-    }
+  auto stage = [&](int buf, int s) {
+    *reinterpret_cast<vec*>(&As[buf][sk][sg]) = ra[s];
+    *reinterpret_cast<vec*>(&Bs[buf][sk][sg]) = rb[s];
   };
-  fetch(0);
-  stage();
-  __syncthreads();
-  for (int64_t k0 = 0; k0 < K; k0 += TK) {
-    const bool more = (k0 + TK < K);
-    if (more) fetch(k0 + TK);   // global loads in flight during the MFMAs below
+  auto product = [&](int buf) {
 #pragma unroll
-    for (int kk = 0; kk < TK; kk += 4) {
-      T a_op[4], b_op[4];
+    for (int kk = 0; kk < DK; kk += 4) {
+      T ao[2], bo[2];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        a_op[t] = As[kk + (lane >> 4)][wm + t * 16 + (lane & 15)];
-        b_op[t] = Bs[kk + (lane >> 4)][wn + t * 16 + (lane & 15)];
+      for (int t = 0; t < 2; ++t) {
+        ao[t] = As[buf][kk + lg][wm + 16 * t + li];
+        bo[t] = Bs[buf][kk + lg][wn + 16 * t + li];
       }
 #pragma unroll
-      for (int a = 0; a < 4; ++a)
+      for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = Mfma<T>::op(a_op[a], b_op[b], acc[a][b]);
+        for (int b = 0; b < 2; ++b) acc[a][b] = Mfma<T>::op(bo[b], ao[a], acc[a][b]);
     }
-    __syncthreads();
-    if (more) {
-      stage();
+  };
+  // chunk kc sits in buffer kc % 2 during its products; the registers of set
+  // 0 hold the next odd chunk, those of set 1 the next even one
+  const int nk = (int)((K + DK - 1) / DK);
+  fetch(0, 1);
+  stage(0, 1);
+  if (nk > 1) fetch(1, 0);
+  __syncthreads();
+  for (int kc = 0; kc < nk; kc += 2) {
+    if (kc + 2 < nk) fetch(kc + 2, 1);
+    product(0);
+    if (kc + 1 < nk) {
+      stage(1, 0);   // last read before the previous barrier
+      __syncthreads();
+      if (kc + 3 < nk) fetch(kc + 3, 0);
+      product(1);
+      if (kc + 2 < nk) stage(0, 1);
       __syncthreads();
     }
   }
-  // lane holds D[row(lane, r)][lane % 16] of each 16 x 16 tile.  The C loads
-  // of half a wave tile are issued together from clamped (always valid)
-  // addresses so that their latencies overlap; only the stores are predicated.
+  // acc[a][b][q]: row 16 a + li, column 16 b + row(lane, q) of the wave tile;
+  // loads from clamped addresses, issued together
 #pragma unroll
-  for (int h = 0; h < 4; h += 2) {
-    T cv[2][4][4];
+  for (int b = 0; b < 2; ++b) {
+    T cv[4][2];
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int q = 0; q < 4; ++q) {
+      const int64_t j = std::min<int64_t>(j_base + wn + 16 * b + Mfma<T>::row(lane, q), N - 1);
 #pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const int64_t j = std::min<int64_t>(j_base + wn + b * 16 + (lane & 15), N - 1);
+      for (int a = 0; a < 2; ++a) cv[q][a] = C[std::min<int64_t>(i_base + wm + 16 * a + li, M - 1) + j * ldc];
+    }
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int64_t i = std::min<int64_t>(i_base + wm + (h + a) * 16 + Mfma<T>::row(lane, r), M - 1);
-          cv[a][b][r] = C[i + j * ldc];
-        }
+    for (int q = 0; q < 4; ++q) {
+      const int64_t j = j_base + wn + 16 * b + Mfma<T>::row(lane, q);
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        const int64_t i = i_base + wm + 16 * a + li;
+        if (i < M && j < N) C[i + j * ldc] = cv[q][a] + alpha * acc[a][b][q];
       }
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const int64_t j = j_base + wn + b * 16 + (lane & 15);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int64_t i = i_base + wm + (h + a) * 16 + Mfma<T>::row(lane, r);
-          if (i < M && j < N) C[i + j * ldc] = cv[a][b][r] + alpha * acc[h + a][b][r];
-        }
-      }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// FP64 update kernel for K % 16 == 0: 256 x 128 tiles of 8 waves (4 x 2 wave
-// tiles of 64 x 64, two waves per SIMD), operand panels streamed straight from
-// global memory into a 3-stage LDS ring with global_load_lds_dwordx4 (no
-// staging registers), so two chunks are always in flight while the MFMAs of
-// the third run.  The operand reads from LDS are issued as inline asm with
-// explicit waits: the compiler treats the LDS DMA as a store that may alias
-// every LDS read and would otherwise wait for all outstanding DMA (including
-// the prefetches) before each read.
-// ---------------------------------------------------------------------------
-constexpr int DM = 256, DN = 128, DK = 16, DST = 3;
-#define HC_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
-
-__device__ inline uint32_t lds_addr(const void* p) {
-  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
-}
-
-__global__ __launch_bounds__(512) void k_gemm_nt_dma(double* __restrict__ C, int64_t ldc, const double* __restrict__ A,
-                                                     int64_t lda, const double* __restrict__ B, int64_t ldb, int64_t M,
-                                                     int64_t N, int64_t K, double alpha, int lower, int64_t gr,
-                                                     int64_t gc, int tiles_n) {
-  // one LDS block: the operand ring during the k loop, then the C staging
-  // area of the epilogue
-  __shared__ __align__(16) double smem[DST * DK * DM + DST * DK * DN];
-  double(*As)[DK][DM] = reinterpret_cast<double(*)[DK][DM]>(smem);
-  double(*Bs)[DK][DN] = reinterpret_cast<double(*)[DK][DN]>(smem + DST * DK * DM);
-  const int tile_m = blockIdx.x / tiles_n, tile_n = blockIdx.x % tiles_n;
-  const int64_t i_base = (int64_t)tile_m * DM, j_base = (int64_t)tile_n * DN;
-  if (lower && gr + i_base + DM - 1 < gc + j_base) return;   // tile strictly above the diagonal
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = (wave & 3) * 64, wn = (wave >> 2) * 64;
-  v4d acc[4][4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = v4d{0, 0, 0, 0};
-  // lane l loads rows (2l, 2l+1) of a 128-row half panel.  M and N are even
-  // here (the caller leaves odd last rows / columns to the edge kernel), so
-  // every pair below M is loaded whole; pairs past the end repeat the last
-  // pair, and their products land in rows / columns that are never stored.
-  const int64_t alast = (M - 2) & ~int64_t(1), blast = (N - 2) & ~int64_t(1);
-  const double* pa0 = A + std::min<int64_t>(i_base + 2 * lane, alast);
-  const double* pa1 = A + std::min<int64_t>(i_base + 128 + 2 * lane, alast);
-  const double* pb = B + std::min<int64_t>(j_base + 2 * lane, blast);
-  const int nk = (int)(K / DK);
-  auto issue = [&](int kc, int stg) {   // wave w fills k-rows 2w and 2w + 1 of the chunk
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const int k = wave * 2 + e;
-      const int64_t gk = (int64_t)kc * DK + k;
-      __builtin_amdgcn_global_load_lds((const void*)(pa0 + gk * lda), HC_LDS_PTR(&As[stg][k][0]), 16, 0, 0);
-      __builtin_amdgcn_global_load_lds((const void*)(pa1 + gk * lda), HC_LDS_PTR(&As[stg][k][128]), 16, 0, 0);
-      __builtin_amdgcn_global_load_lds((const void*)(pb + gk * ldb), HC_LDS_PTR(&Bs[stg][k][0]), 16, 0, 0);
-    }
-  };
-  const uint32_t a_off = lds_addr(&As[0][lane >> 4][wm + (lane & 15)]);
-  const uint32_t b_off = lds_addr(&Bs[0][lane >> 4][wn + (lane & 15)]);
-  constexpr uint32_t SA = DK * DM * 8, SB_ = DK * DN * 8;
-  issue(0, 0);
-  if (nk > 1) issue(1, 1);
-  for (int kc = 0; kc < nk; ++kc) {
-    // each wave has 6 loads per chunk in flight: vmcnt(6) leaves only the
-    // next chunk outstanding, i.e. chunk kc has landed
-    if (kc + 1 < nk) __builtin_amdgcn_s_waitcnt(0xF76);
-    else __builtin_amdgcn_s_waitcnt(0xF70);
-    __builtin_amdgcn_s_barrier();
-    if (kc + 2 < nk) issue(kc + 2, (kc + 2) % DST);   // that stage was last read before this barrier
-    const int stg = kc % DST;
-    const uint32_t sa = a_off + stg * SA, sb = b_off + stg * SB_;
-#pragma unroll
-    for (int kk = 0; kk < DK; kk += 4) {
-      double a0, a1, a2, a3, b0, b1, b2, b3;
-      const uint32_t ra = sa + kk * DM * 8, rb = sb + kk * DN * 8;
-      asm volatile("ds_read_b64 %0, %1 offset:0" : "=v"(a0) : "v"(ra));
-      asm volatile("ds_read_b64 %0, %1 offset:128" : "=v"(a1) : "v"(ra));
-      asm volatile("ds_read_b64 %0, %1 offset:256" : "=v"(a2) : "v"(ra));
-      asm volatile("ds_read_b64 %0, %1 offset:384" : "=v"(a3) : "v"(ra));
-      asm volatile("ds_read_b64 %0, %1 offset:0" : "=v"(b0) : "v"(rb));
-      asm volatile("ds_read_b64 %0, %1 offset:128" : "=v"(b1) : "v"(rb));
-      asm volatile("ds_read_b64 %0, %1 offset:256" : "=v"(b2) : "v"(rb));
-      asm volatile("ds_read_b64 %0, %1 offset:384" : "=v"(b3) : "v"(rb));
-      asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3), "+v"(b0), "+v"(b1), "+v"(b2),
-                   "+v"(b3));
-      const double ao[4] = {a0, a1, a2, a3}, bo[4] = {b0, b1, b2, b3};
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = Mfma<double>::op(ao[a], bo[b], acc[a][b]);
     }
   }
-  // epilogue through LDS, one half of the tile's columns at a time: the four
-  // waves owning those columns write their accumulators column-major (stride
-  // CS doubles: two-way bank conflicts on the write, none on the read), then
-  // all eight waves stream whole columns, lane l handling rows 4l .. 4l + 3
-  // with 16-byte loads and stores of C (full cache lines per wave instead of
-  // 32-byte pieces of 16 lines).  M and N are even here, so rows come in
-  // pairs and each 16-byte piece is either wholly inside or wholly outside.
-  constexpr int CS = DM + 2;
-  static_assert(DN / 2 * CS <= DST * DK * (DM + DN), "C staging fits the operand ring");
-  __syncthreads();   // every wave is done with the operand ring
-  double* Cs = smem;
-  const int64_t i0 = i_base + 4 * lane;
-  const bool lo_ok = i0 < M, hi_ok = i0 + 2 < M;
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    if (wn == 64 * h) {
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            Cs[(16 * b + (lane & 15)) * CS + wm + 16 * a + Mfma<double>::row(lane, r)] = acc[a][b][r];
-    }
-    __syncthreads();
-    v2d cg[8][2];
-#pragma unroll
-    for (int cc = 0; cc < 8; ++cc) {
-      const int64_t j = std::min<int64_t>(j_base + 64 * h + 8 * wave + cc, N - 1);
-      cg[cc][0] = *reinterpret_cast<const v2d*>(C + std::min<int64_t>(i0, M - 2) + j * ldc);
-      cg[cc][1] = *reinterpret_cast<const v2d*>(C + std::min<int64_t>(i0 + 2, M - 2) + j * ldc);
-    }
-#pragma unroll
-    for (int cc = 0; cc < 8; ++cc) {
-      const int col = 8 * wave + cc;
-      const int64_t j = j_base + 64 * h + col;
-      const v2d* cs = reinterpret_cast<const v2d*>(Cs + col * CS + 4 * lane);
-      const v2d u0 = cs[0], u1 = cs[1];
-      v2d* dst = reinterpret_cast<v2d*>(C + i0 + j * ldc);
-      if (j < N && lo_ok) dst[0] = cg[cc][0] + alpha * u0;
-      if (j < N && hi_ok) dst[1] = cg[cc][1] + alpha * u1;
-    }
-    __syncthreads();
-  }
-}
-
-// FP32 counterpart (mixed mode): 32-deep chunks, so one k-row of the A panel
-// (256 floats) is one dwordx4 DMA, and one dwordx4 DMA fills two adjacent
-// k-rows of the B panel (128 floats each: lanes 0-31 the first, 32-63 the
-// second); each wave fills 4 k-rows per chunk (6 loads in flight).
-constexpr int FK = 32;
-__global__ __launch_bounds__(512) void k_gemm_nt_dma32(float* __restrict__ C, int64_t ldc, const float* __restrict__ A,
-                                                       int64_t lda, const float* __restrict__ B, int64_t ldb,
-                                                       int64_t M, int64_t N, int64_t K, float alpha, int lower,
-                                                       int64_t gr, int64_t gc, int tiles_n) {
-  __shared__ __align__(16) float smem[DST * FK * DM + DST * FK * DN];
-  float(*As)[FK][DM] = reinterpret_cast<float(*)[FK][DM]>(smem);
-  float(*Bs)[FK][DN] = reinterpret_cast<float(*)[FK][DN]>(smem + DST * FK * DM);
-  const int tile_m = blockIdx.x / tiles_n, tile_n = blockIdx.x % tiles_n;
-  const int64_t i_base = (int64_t)tile_m * DM, j_base = (int64_t)tile_n * DN;
-  if (lower && gr + i_base + DM - 1 < gc + j_base) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = (wave & 3) * 64, wn = (wave >> 2) * 64;
-  v4f acc[4][4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = v4f{0, 0, 0, 0};
-  // lane l loads rows 4l..4l+3 of A, and rows 4 (l % 32) .. + 3 of B for
-  // k-row (l / 32) of a pair.  M and N are multiples of four here (the caller
-  // leaves the rest to the edge kernel); groups past the end repeat the last
-  // group and only feed entries that are never stored.
-  const int64_t alast = (M - 4) & ~int64_t(3), blast = (N - 4) & ~int64_t(3);
-  const float* pa = A + std::min<int64_t>(i_base + 4 * lane, alast);
-  const float* pb = B + std::min<int64_t>(j_base + 4 * (lane & 31), blast) + (int64_t)(lane >> 5) * ldb;
-  const int nk = (int)(K / FK);
-  auto issue = [&](int kc, int stg) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int k = wave * 4 + e;
-      const int64_t gk = (int64_t)kc * FK + k;
-      __builtin_amdgcn_global_load_lds((const void*)(pa + gk * lda), HC_LDS_PTR(&As[stg][k][0]), 16, 0, 0);
-    }
-#pragma unroll
-    for (int e = 0; e < 4; e += 2) {
-      const int k = wave * 4 + e;
-      const int64_t gk = (int64_t)kc * FK + k;
-      __builtin_amdgcn_global_load_lds((const void*)(pb + gk * ldb), HC_LDS_PTR(&Bs[stg][k][0]), 16, 0, 0);
-    }
-  };
-  const uint32_t a_off = lds_addr(&As[0][lane >> 4][wm + (lane & 15)]);
-  const uint32_t b_off = lds_addr(&Bs[0][lane >> 4][wn + (lane & 15)]);
-  constexpr uint32_t SA = FK * DM * 4, SB_ = FK * DN * 4;
-  issue(0, 0);
-  if (nk > 1) issue(1, 1);
-  for (int kc = 0; kc < nk; ++kc) {
-    if (kc + 1 < nk) __builtin_amdgcn_s_waitcnt(0xF76);   // vmcnt(6): chunk kc landed
-    else __builtin_amdgcn_s_waitcnt(0xF70);
-    __builtin_amdgcn_s_barrier();
-    if (kc + 2 < nk) issue(kc + 2, (kc + 2) % DST);
-    const int stg = kc % DST;
-    const uint32_t sa = a_off + stg * SA, sb = b_off + stg * SB_;
-#pragma unroll
-    for (int kk = 0; kk < FK; kk += 4) {
-      float a0, a1, a2, a3, b0, b1, b2, b3;
-      const uint32_t ra = sa + kk * DM * 4, rb = sb + kk * DN * 4;
-      asm volatile("ds_read_b32 %0, %1 offset:0" : "=v"(a0) : "v"(ra));
-      asm volatile("ds_read_b32 %0, %1 offset:64" : "=v"(a1) : "v"(ra));
-      asm volatile("ds_read_b32 %0, %1 offset:128" : "=v"(a2) : "v"(ra));
-      asm volatile("ds_read_b32 %0, %1 offset:192" : "=v"(a3) : "v"(ra));
-      asm volatile("ds_read_b32 %0, %1 offset:0" : "=v"(b0) : "v"(rb));
-      asm volatile("ds_read_b32 %0, %1 offset:64" : "=v"(b1) : "v"(rb));
-      asm volatile("ds_read_b32 %0, %1 offset:128" : "=v"(b2) : "v"(rb));
-      asm volatile("ds_read_b32 %0, %1 offset:192" : "=v"(b3) : "v"(rb));
-      asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3), "+v"(b0), "+v"(b1), "+v"(b2),
-                   "+v"(b3));
-      const float ao[4] = {a0, a1, a2, a3}, bo[4] = {b0, b1, b2, b3};
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = Mfma<float>::op(ao[a], bo[b], acc[a][b]);
-    }
-  }
-  // epilogue through LDS as in the FP64 kernel; M is a multiple of four
-  // here, so each lane's 16-byte piece of a column is wholly inside or
-  // wholly outside
-  constexpr int CS = DM + 4;
-  static_assert(DN / 2 * CS <= DST * FK * (DM + DN), "C staging fits the operand ring");
-  __syncthreads();
-  float* Cs = smem;
-  const int64_t i0 = i_base + 4 * lane;
-  const bool ok = i0 < M;
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    if (wn == 64 * h) {
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            Cs[(16 * b + (lane & 15)) * CS + wm + 16 * a + Mfma<float>::row(lane, r)] = acc[a][b][r];
-    }
-    __syncthreads();
-    v4f cg[8];
-#pragma unroll
-    for (int cc = 0; cc < 8; ++cc) {
-      const int64_t j = std::min<int64_t>(j_base + 64 * h + 8 * wave + cc, N - 1);
-      cg[cc] = *reinterpret_cast<const v4f*>(C + std::min<int64_t>(i0, M - 4) + j * ldc);
-    }
-#pragma unroll
-    for (int cc = 0; cc < 8; ++cc) {
-      const int col = 8 * wave + cc;
-      const int64_t j = j_base + 64 * h + col;
-      const v4f u = *reinterpret_cast<const v4f*>(Cs + col * CS + 4 * lane);
-      if (j < N && ok) *reinterpret_cast<v4f*>(C + i0 + j * ldc) = cg[cc] + alpha * u;
-    }
-    __syncthreads();
-  }
-}
-
-static bool dma32_ok(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t M, int64_t N, int64_t K) {
-  return K % FK == 0 && M >= 4 && N >= 4 && lda % 4 == 0 && ldb % 4 == 0 && ((uintptr_t)A % 16) == 0 &&
-         ((uintptr_t)B % 16) == 0;
-}
-
-static bool dma_ok(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t M, int64_t N, int64_t K) {
-  return K % DK == 0 && M >= 2 && N >= 2 && lda % 2 == 0 && ldb % 2 == 0 && ((uintptr_t)A % 16) == 0 &&
-         ((uintptr_t)B % 16) == 0;
-}
-
-// Entries of C outside the leading M' x N' block (rows [M', M) and columns
-// [N', N)) that the DMA kernels leave to this one: their loads come in whole
-// 16-byte groups of rows, so the last M % g rows and N % g columns (g = 2 for
-// FP64, 4 for FP32) are updated here, one thread per entry.
-template <typename T>
-__global__ __launch_bounds__(256) void k_gemm_nt_edge(T* __restrict__ C, int64_t ldc, const T* __restrict__ A,
-                                                      int64_t lda, const T* __restrict__ B, int64_t ldb, int64_t M,
-                                                      int64_t N, int64_t K, T alpha, int lower, int64_t gr,
-                                                      int64_t gc, int64_t Mp, int64_t Np) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t n_rows = (M - Mp) * N;          // rows [Mp, M), every column
-  const int64_t n_cols = Mp * (N - Np);         // rows [0, Mp), columns [Np, N)
-  if (e >= n_rows + n_cols) return;
-  int64_t i, j;
-  if (e < n_rows) {
-    i = Mp + e / N;
-    j = e % N;
-  } else {
-    i = (e - n_rows) % Mp;
-    j = Np + (e - n_rows) / Mp;
-  }
-  if (lower && gr + i < gc + j) return;
-  T acc = 0;
-  for (int64_t k = 0; k < K; ++k) acc += A[i + k * lda] * B[j + k * ldb];
-  C[i + j * ldc] += alpha * acc;
-}
-
-template <typename T>
-static void gemm_edge(T* C, int64_t ldc, const T* A, int64_t lda, const T* B, int64_t ldb, int64_t M, int64_t N,
-                      int64_t K, T alpha, bool lower, int64_t gr, int64_t gc, int64_t Mp, int64_t Np,
-                      hipStream_t st) {
-  const int64_t cnt = (M - Mp) * N + Mp * (N - Np);
-  if (cnt <= 0) return;
-  hipLaunchKernelGGL(k_gemm_nt_edge<T>, dim3((unsigned)ceil_div(cnt, 256)), dim3(256), 0, st, C, ldc, A, lda, B, ldb,
-                     M, N, K, alpha, lower ? 1 : 0, gr, gc, Mp, Np);
-  HC_LAUNCH_CHECK();
 }
 
 template <typename T>
 void gemm_nt(T* C, int64_t ldc, const T* A, int64_t lda, const T* B, int64_t ldb, int64_t M, int64_t N, int64_t K,
-             T alpha, bool lower, int64_t gr, int64_t gc, hipStream_t st) {
+             T alpha, bool lower, int64_t gr, int64_t gc, hipStream_t st, GemmRole role) {
   if (M <= 0 || N <= 0 || K <= 0) return;
-  if constexpr (std::is_same<T, double>::value) {
-    const int64_t Mp = M & ~int64_t(1), Np = N & ~int64_t(1);   // whole row pairs
-    if (dma_ok(A, lda, B, ldb, Mp, Np, K) && Mp >= 4 && ((uintptr_t)C % 16) == 0 && ldc % 2 == 0) {
-      const int tm = (int)ceil_div(Mp, DM), tn = (int)ceil_div(Np, DN);
-      hipLaunchKernelGGL(k_gemm_nt_dma, dim3(tm * tn), dim3(512), 0, st, C, ldc, A, lda, B, ldb, Mp, Np, K, alpha,
-                         lower ? 1 : 0, gr, gc, tn);
-      HC_LAUNCH_CHECK();
-      gemm_edge<T>(C, ldc, A, lda, B, ldb, M, N, K, alpha, lower, gr, gc, Mp, Np, st);
-      return;
-    }
-  } else {
-    const int64_t Mp = M & ~int64_t(3), Np = N & ~int64_t(3);   // whole groups of four rows
-    if (dma32_ok(A, lda, B, ldb, Mp, Np, K) && ((uintptr_t)C % 16) == 0 && ldc % 4 == 0) {
-      const int tm = (int)ceil_div(Mp, DM), tn = (int)ceil_div(Np, DN);
-      hipLaunchKernelGGL(k_gemm_nt_dma32, dim3(tm * tn), dim3(512), 0, st, C, ldc, A, lda, B, ldb, Mp, Np, K, alpha,
-                         lower ? 1 : 0, gr, gc, tn);
-      HC_LAUNCH_CHECK();
-      gemm_edge<T>(C, ldc, A, lda, B, ldb, M, N, K, alpha, lower, gr, gc, Mp, Np, st);
-      return;
-    }
-  }
-  const int tm = (int)ceil_div(M, TM), tn = (int)ceil_div(N, TN);
-  hipLaunchKernelGGL(k_gemm_nt<T>, dim3(tm * tn), dim3(256), 0, st, C, ldc, A, lda, B, ldb, M, N, K, alpha,
-                     lower ? 1 : 0, gr, gc, tn);
+  constexpr int G = 16 / sizeof(T);
+  const bool vec = M % G == 0 && N % G == 0 && lda % G == 0 && ldb % G == 0 && K % (64 / sizeof(T)) == 0 &&
+                   ((uintptr_t)A % 16) == 0 && ((uintptr_t)B % 16) == 0;
+  const int64_t tm = ceil_div(M, TL), tn = ceil_div(N, TL);
+  const bool tri = lower && M == N && gr == gc;
+  const int64_t tiles = tri ? tm * (tm + 1) / 2 : tm * tn;
+  const unsigned grid = (unsigned)tiles;
+  const int prio = role == GEMM_AHEAD ? 1 : 0;
+  const size_t pad = role == GEMM_BEHIND ? BEHIND_PAD : 0;
+  if (vec)
+    hipLaunchKernelGGL((k_gemm_nt<T, true>), dim3(grid), dim3(256), pad, st, C, ldc, A, lda, B, ldb, M, N, K, alpha,
+                       lower ? 1 : 0, tri ? 1 : 0, gr, gc, (int)tn, prio);
+  else
+    hipLaunchKernelGGL((k_gemm_nt<T, false>), dim3(grid), dim3(256), pad, st, C, ldc, A, lda, B, ldb, M, N, K, alpha,
+                       lower ? 1 : 0, tri ? 1 : 0, gr, gc, (int)tn, prio);
   HC_LAUNCH_CHECK();
 }
 
@@ -766,10 +924,10 @@ static double lower_entries(int64_t rc, int64_t cc, int64_t M, int64_t N) {
 // C -= A B' with every operand inside the one column-major matrix S
 template <typename T>
 static void gemm_nt_sub(T* S, int64_t ld, int64_t rc, int64_t cc, int64_t ra, int64_t rb, int64_t ka, int64_t M,
-                        int64_t N, int64_t K, bool lower, hipStream_t st, Prof* prof) {
+                        int64_t N, int64_t K, bool lower, hipStream_t st, Prof* prof, GemmRole role) {
   if (M <= 0 || N <= 0 || K <= 0) return;
   if (prof) HC_HIP(hipEventRecord(prof->next(), st));
-  gemm_nt<T>(S + rc + cc * ld, ld, S + ra + ka * ld, ld, S + rb + ka * ld, ld, M, N, K, T(-1), lower, rc, cc, st);
+  gemm_nt<T>(S + rc + cc * ld, ld, S + ra + ka * ld, ld, S + rb + ka * ld, ld, M, N, K, T(-1), lower, rc, cc, st, role);
   if (prof) {
     HC_HIP(hipEventRecord(prof->next(), st));
     prof->flops += 2.0 * (double)K * lower_entries(rc, cc, M, N);
@@ -802,29 +960,61 @@ static int64_t rows_below(const int64_t* last, int64_t n, int64_t j) {
   return std::min<int64_t>(n, ceil_div(std::max<int64_t>(last[j], j + 1), BS) * BS);
 }
 
-// factor the panel [K0, Kend): per 64-block the diagonal factor, the TRSM of
+// Factor the columns [K0, Kend).  Steps of 64 columns (k_panel_step) inside
+// inner panels of IB columns: the left-looking update of the next block column
+// reaches back to the start of the inner panel, and at its end one MFMA update
+// (K = IB) brings the columns up to Kend up to date.  The first of them is
+// already, by the last step.
+static void factor_panel(double* S, int64_t n, int64_t ld, double* Linv, double tol, double fix, unsigned long long* hits,
+                         int64_t K0, int64_t Kend, const int64_t* last, hipStream_t st, Prof* prof) {
+  hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(256), 0, st, S, ld, K0, n, Linv + (K0 / BS) * BS * BS, tol, fix,
+                     hits);
+  HC_LAUNCH_CHECK();
+  bool deferred = false;   // a tile of L waits in a Linv slot (k_panel_step)
+  for (int64_t I0 = K0; I0 < Kend; I0 += IB) {
+    const int64_t Iend = std::min<int64_t>(Kend, I0 + IB);
+    for (int64_t c = I0; c < Iend; c += BS) {
+      const int64_t c1 = std::min<int64_t>(n, c + BS);
+      const bool next = c1 < Kend;
+      int64_t R = rows_below(last, n, c1 - 1);
+      if (next) R = std::max(R, std::min<int64_t>(n, c1 + BS));   // the next diagonal block, also when it is not reached
+      if (R <= c1 && !deferred) continue;
+      const int64_t wgs = std::max<int64_t>(1, ceil_div(R - c1, BS));
+      const bool defer = next && wgs > 1;
+      hipLaunchKernelGGL(k_panel_step, dim3((unsigned)wgs), dim3(256), 0, st, S, ld, n, I0, c, R, Linv,
+                         next ? 1 : 0, deferred ? 1 : 0, defer ? 1 : 0, tol, fix, hits);
+      HC_LAUNCH_CHECK();
+      deferred = defer;
+    }
+    if (Iend < Kend) {
+      const int64_t c2 = Iend + BS, R = rows_below(last, n, Iend - 1);   // Iend's own block column is up to date
+      if (c2 < Kend && c2 < R)
+        gemm_nt_sub<double>(S, ld, c2, c2, c2, c2, I0, R - c2, std::min(Kend, R) - c2, Iend - I0, true, st, prof, GEMM_AHEAD);
+    }
+  }
+}
+
+// The same in FP32: per 64-block the diagonal factor, the TRSM of
 // the rows below (down to the envelope) and the eager update of the rest of
 // the panel
-template <typename T>
-static void factor_panel(T* S, int64_t n, int64_t ld, T* Linv, double tol, double fix, unsigned long long* hits,
-                         int64_t K0, int64_t Kend, const int64_t* last, hipStream_t st, Prof* prof) {
+static void factor_panel(float* S, int64_t n, int64_t ld, float* Linv, double tol, double fix, unsigned long long* hits,
+                         int64_t K0, int64_t Kend, const int64_t* last, hipStream_t st, Prof*) {
   for (int64_t c = K0; c < Kend; c += BS) {
     const int64_t cb = std::min<int64_t>(BS, n - c);
-    hipLaunchKernelGGL(k_chol_diag<T>, dim3(1), dim3(256), 0, st, S, ld, c, n, Linv + (c / BS) * BS * BS, tol,
+    hipLaunchKernelGGL(k_chol_diag32, dim3(1), dim3(256), 0, st, S, ld, c, n, Linv + (c / BS) * BS * BS, tol,
                        fix, hits);
     HC_LAUNCH_CHECK();
     const int64_t r0 = c + cb, R = rows_below(last, n, c + cb - 1);
     if (r0 < R) {
-      hipLaunchKernelGGL(k_trsm<T>, dim3((unsigned)ceil_div(R - r0, BS)), dim3(256), 0, st, S, ld, c, r0, R,
-                         (const T*)(Linv + (c / BS) * BS * BS));
+      hipLaunchKernelGGL(k_trsm32, dim3((unsigned)ceil_div(R - r0, BS)), dim3(256), 0, st, S, ld, c, r0, R,
+                         (const float*)(Linv + (c / BS) * BS * BS));
       HC_LAUNCH_CHECK();
     }
     if (r0 < Kend && r0 < R) {
-      // rows [r0, R) of the panel's remaining columns [r0, min(Kend, R)) (not in
-      // the profile's MFMA-update figures, which cover the large update kernels)
+      // rows [r0, R) of the panel's remaining columns [r0, min(Kend, R))
       const int64_t M = R - r0, N = std::min(Kend, R) - r0;
-      hipLaunchKernelGGL(k_gemm_panel<T>, dim3((unsigned)ceil_div(M, BS), (unsigned)ceil_div(N, BS)), dim3(256), 0,
-                         st, S + r0 + r0 * ld, ld, (const T*)(S + r0 + c * ld), ld, (const T*)(S + r0 + c * ld), ld,
+      hipLaunchKernelGGL(k_gemm_panel32, dim3((unsigned)ceil_div(M, BS), (unsigned)ceil_div(N, BS)), dim3(256), 0,
+                         st, S + r0 + r0 * ld, ld, (const float*)(S + r0 + c * ld), ld, (const float*)(S + r0 + c * ld), ld,
                          M, N, (int)cb, r0, r0);
       HC_LAUNCH_CHECK();
     }
@@ -844,45 +1034,55 @@ void dense_cholesky(T* S, int64_t n, int64_t ld, T* Linv, double tol, double fix
   // `st` before U1: the same launches, one at a time.
   const bool serial = aux->serial;
   hipStream_t side = st;
-  if (!serial) {
-    aux->init();
-    aux->used = 0;
-    side = aux->side;
-  }
-  const int64_t W = std::max<int64_t>(BS, aux->nb / BS * BS);   // panel width
-  if (!serial) {
-    hipEvent_t start = aux->next();
-    HC_HIP(hipEventRecord(start, st));
-    HC_HIP(hipStreamWaitEvent(side, start, 0));
-  }
+  bool started = false;
   hipEvent_t u2_done = nullptr;
-  for (int64_t K0 = 0; K0 < n; K0 += W) {
-    const int64_t Kend = std::min<int64_t>(n, K0 + W);
-    factor_panel<T>(S, n, ld, Linv, tol, fix, hits, K0, Kend, last, st, prof);
+  auto wait_u2 = [&] {
+    if (u2_done) HC_HIP(hipStreamWaitEvent(st, u2_done, 0));
+    u2_done = nullptr;
+  };
+  // rows from K on that an inner panel at K reaches; from single_from on they
+  // are few everywhere, the updates are short and one panel on `st` takes the rest
+  auto reach = [&](int64_t K) { return rows_below(last, n, std::min<int64_t>(n, K + IB) - 1) - K; };
+  constexpr bool fp64 = std::is_same<T, double>::value;
+  int64_t single_from = n;
+  for (int64_t K = (n - 1) / IB * IB; fp64 && K >= 0 && reach(K) <= LOOKAHEAD_MIN; K -= IB) single_from = K;
+  const int64_t wide = std::max<int64_t>(IB, aux->nb / IB * IB);
+  auto width = [&](int64_t K) {   // FP32: always wide, the order of its sums depends on it
+    return K >= single_from ? n - K : !fp64 || reach(K) >= WIDE_MIN ? wide : (int64_t)IB;
+  };
+  for (int64_t K0 = 0, Kend; K0 < n; K0 = Kend) {
+    Kend = std::min<int64_t>(n, K0 + width(K0));
+    factor_panel(S, n, ld, Linv, tol, fix, hits, K0, Kend, last, st, prof);
     if (Kend >= n) break;
-    const int64_t K1 = std::min<int64_t>(n, Kend + W);
+    const int64_t K1 = std::min<int64_t>(n, Kend + width(Kend));
     const int64_t R = rows_below(last, n, Kend - 1);
     const bool u2 = K1 < R;
-    if (u2) {
-      if (!serial) {
-        hipEvent_t factored = aux->next();
-        HC_HIP(hipEventRecord(factored, st));
-        HC_HIP(hipStreamWaitEvent(side, factored, 0));
+    if (u2 && !serial) {
+      if (!started) {
+        aux->init();
+        aux->used = 0;
+        side = aux->side;
+        started = true;
       }
-      // U2: rows and columns [K1, R)
-      gemm_nt_sub<T>(S, ld, K1, K1, K1, K1, K0, R - K1, R - K1, Kend - K0, true, side, prof);
+      hipEvent_t factored = aux->next();
+      HC_HIP(hipEventRecord(factored, st));
+      HC_HIP(hipStreamWaitEvent(side, factored, 0));
     }
-    if (u2_done) HC_HIP(hipStreamWaitEvent(st, u2_done, 0));
+    // U2: rows and columns [K1, R)
+    if (u2)
+      gemm_nt_sub<T>(S, ld, K1, K1, K1, K1, K0, R - K1, R - K1, Kend - K0, true, side, prof,
+                     serial ? GEMM_PLAIN : GEMM_BEHIND);
+    wait_u2();   // the previous U2 wrote the columns that U1 updates
     // U1 on the caller's stream: rows [Kend, R), columns [Kend, min(K1, R))
     if (Kend < R)
-      gemm_nt_sub<T>(S, ld, Kend, Kend, Kend, Kend, K0, R - Kend, std::min(K1, R) - Kend, Kend - K0, true, st, prof);
-    u2_done = nullptr;
+      gemm_nt_sub<T>(S, ld, Kend, Kend, Kend, Kend, K0, R - Kend, std::min(K1, R) - Kend, Kend - K0, true, st, prof,
+                     GEMM_AHEAD);
     if (u2 && !serial) {
       u2_done = aux->next();
       HC_HIP(hipEventRecord(u2_done, side));
     }
   }
-  if (u2_done) HC_HIP(hipStreamWaitEvent(st, u2_done, 0));
+  wait_u2();
 }
 
 // ---------------------------------------------------------------------------
@@ -1182,9 +1382,9 @@ template void dense_cholesky<double>(double*, int64_t, int64_t, double*, double,
 template void dense_cholesky<float>(float*, int64_t, int64_t, float*, double, double, unsigned long long*,
                                     hipStream_t, Prof*, Aux*, const int64_t*);
 template void gemm_nt<double>(double*, int64_t, const double*, int64_t, const double*, int64_t, int64_t, int64_t,
-                              int64_t, double, bool, int64_t, int64_t, hipStream_t);
+                              int64_t, double, bool, int64_t, int64_t, hipStream_t, GemmRole);
 template void gemm_nt<float>(float*, int64_t, const float*, int64_t, const float*, int64_t, int64_t, int64_t,
-                             int64_t, float, bool, int64_t, int64_t, hipStream_t);
+                             int64_t, float, bool, int64_t, int64_t, hipStream_t, GemmRole);
 template void dense_solve<double>(const double*, int64_t, int64_t, const double*, const double*, double*, double*,
                                   double*, int, hipStream_t, const int64_t*);
 template void dense_solve<float>(const float*, int64_t, int64_t, const float*, const float*, float*, float*, float*,
