@@ -42,17 +42,34 @@ void dense_cholesky(T* S, int64_t n, int64_t ld, T* Linv, double tol, double fix
                     hipStream_t st, Prof* prof, Aux* aux, const int64_t* last = nullptr);
 // flops of the envelope-limited factorisation (n^3 / 3 when last is null)
 double envelope_cholesky_flops(int64_t n, const int64_t* last);
-// Inverses X (and X') of the 256 x 256 diagonal blocks of the factor, from
-// the 64 x 64 block inverses; inv256_elems(n) entries each.
-template <typename T>
-void dense_block_inverses(const T* L, int64_t n, int64_t ld, const T* Linv, T* X, T* XT, hipStream_t st);
+// FP64 triangular solves with a factor: the inverses of its 128 x 128 diagonal
+// blocks, the array its workgroups exchange results in (both filled by
+// tri_prepare after each factorisation; one solve at a time) and, per
+// 128-block, the first block its rows couple to and the last one its columns
+// reach (tri_envelope; null for a dense factor).
+struct TriSolve {
+  int64_t n = 0;
+  double* inv = nullptr;    // tri_inv_elems(n)
+  double* ex = nullptr;     // tri_exchange_elems(n)
+  const int32_t *lo = nullptr, *hi = nullptr;
+};
+int64_t tri_inv_elems(int64_t n);
+int64_t tri_exchange_elems(int64_t n);
+void tri_envelope(int64_t n, const int64_t* last, std::vector<int32_t>& lo, std::vector<int32_t>& hi);
+// nf >= n: rows that were factored (Linv holds their 64 x 64 inverses)
+void tri_prepare(const TriSolve& t, const double* L, int64_t nf, int64_t ld, const double* Linv, hipStream_t st);
+// x_r = L^-T L^-1 b_r; b is read only
+void tri_solve(const TriSolve& t, const double* L, int64_t ld, const double* const* b, double* const* x, int nrhs,
+               hipStream_t st);
+// The FP32 mode's: inverses X (and X') of the 256 x 256 diagonal blocks of the
+// factor, from the 64 x 64 block inverses; inv256_elems(n) entries each.
+void dense_block_inverses(const float* L, int64_t n, int64_t ld, const float* Linv, float* X, float* XT, hipStream_t st);
 int64_t inv256_elems(int64_t n);
 // X = L^-T L^-1 B for nrhs <= 4 right-hand sides (column-major, leading dim
 // n); B and Y are overwritten (Y receives the forward result).  With the
 // factorisation's envelope `last` the updates skip the zero blocks.
-template <typename T>
-void dense_solve(const T* L, int64_t n, int64_t ld, const T* X256, const T* XT256, T* B, T* Y, T* X, int nrhs,
-                 hipStream_t st, const int64_t* last = nullptr);
+void dense_solve(const float* L, int64_t n, int64_t ld, const float* X256, const float* XT256, float* B, float* Y,
+                 float* X, int nrhs, hipStream_t st, const int64_t* last = nullptr);
 // C[i, j] += alpha * sum_k A[i, k] B[j, k] (column-major operands); with
 // `lower`, tiles strictly above the diagonal of the global matrix (C[0,0] at
 // global (gr, gc)) are skipped.

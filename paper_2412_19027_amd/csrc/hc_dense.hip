@@ -1086,6 +1086,348 @@ void dense_cholesky(T* S, int64_t n, int64_t ld, T* Linv, double tol, double fix
 }
 
 // ---------------------------------------------------------------------------
+// FP64 triangular solves: one launch per pass.  A workgroup takes a block of
+// TB = 128 rows (forward) or columns (backward) and runs along the other
+// blocks in the order in which their results appear, its 128 x 128 tile of L
+// loaded before it waits for the block's result; then the diagonal block's
+// stored inverse gives its own.
+// Results travel between workgroups in an exchange array that holds a marker
+// (a NaN of one bit pattern) until a value is there: a consumer polls the
+// values themselves, so an exchange costs one store and one load past the L2s
+// and no flag or barrier.  Blocks are dealt by a ticket, so a workgroup waits
+// only for ones that started before it, whatever the dispatch order or the
+// other streams' load; each wait is bounded all the same (POLL_MAX loads, and
+// one load per value once it has run out).
+// Bound: the chain of n / 128 exchanges (about 2 us each), then L's bytes.
+// A solve (both passes, one right-hand side): 500 / 1,856 / 5,056 / 20,032 rows
+// 26 / 79 / 204 / 1,113 us against 28 / 107 / 284 / 1,600 us of kernel time in
+// two launches per 256 rows and pass (and, launched one by one, as much again
+// at the small sizes); a second tile on its way ahead of the first one's
+// values changes nothing.  The 128-blocks' inverses take 22 us, the 256-blocks'
+// in one workgroup each took 337.
+// ---------------------------------------------------------------------------
+constexpr int TB = 128;
+constexpr int POLL_MAX = 1 << 20;
+constexpr unsigned long long EX_EMPTY = 0x7ff8dead0badbeefull;
+
+// values x[0..NV) from p[0..NV), once all of them are there in every lane
+template <int NV>
+__device__ __forceinline__ void ex_poll(const double* const* p, double (&x)[NV], int& budget) {
+  unsigned long long v[NV];
+  while (true) {
+    bool empty = false;
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+      v[i] = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p[i]), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) empty |= v[i] == EX_EMPTY;
+    if (!__any(empty) || budget <= 0) break;
+    --budget;
+  }
+#pragma unroll
+  for (int i = 0; i < NV; ++i) x[i] = __longlong_as_double((long long)v[i]);
+}
+__device__ inline void ex_put(double* p, double x) {
+  unsigned long long v = (unsigned long long)__double_as_longlong(x);
+  if (v == EX_EMPTY) v = 0x7ff8000000000000ull;   // any other NaN
+  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void ex_clear(double* p) { *reinterpret_cast<unsigned long long*>(p) = EX_EMPTY; }
+
+// Inverse of each 128 x 128 diagonal block, [Y0, 0; -Y1 L10 Y0, Y1] from the 64 x 64
+// ones (identity where there is no second one): a wave takes 16 columns, both
+// products on MFMA with the first one's output registers as the second's
+// operand.  n: factored rows; the exchange array's ne rows are emptied and the
+// tickets set to zero along the way.
+__global__ __launch_bounds__(256) void k_inv128(const double* __restrict__ L, int64_t ld, int64_t n,
+                                                const double* __restrict__ Linv, double* __restrict__ inv, int64_t ne,
+                                                double* __restrict__ ex, unsigned* __restrict__ ticket) {
+  typedef Mfma<double> M;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15;
+  const int64_t c = (int64_t)blockIdx.x * TB;
+  double* X = inv + (int64_t)blockIdx.x * TB * TB;
+  if (blockIdx.x == 0 && tid < 2) ticket[tid] = 0;
+  for (int e = tid; e < 4 * TB; e += 256) {
+    const int64_t i = c + (e & (TB - 1));
+    if (i < ne) ex_clear(ex + (e / TB) * ne + i);
+  }
+  const double* Y0 = Linv + (c / BS) * BS * BS;
+  const bool two = c + BS < n;
+  const double* Y1 = two ? Y0 + BS * BS : Y0;
+  for (int e = tid; e < BS * BS; e += 256) {
+    const int i = e % BS, j = e / BS;
+    X[i + j * TB] = Y0[e];
+    X[i + (BS + j) * TB] = 0.0;
+    X[BS + i + (BS + j) * TB] = two ? Y1[e] : (i == j ? 1.0 : 0.0);
+  }
+  v4d t[4];
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    t[a] = v4d{0, 0, 0, 0};
+    const int64_t row = c + BS + 16 * a + li;
+    const double* pl = L + std::min<int64_t>(row, n - 1) + c * ld;
+#pragma unroll 4
+    for (int q = 0; two && q < 16; ++q) {   // (without a second block the columns need not exist either)
+      const int m = 4 * q + (lane >> 4);
+      const double l = pl[m * ld];
+      t[a] = M::op(row < n ? l : 0.0, Y0[m + (16 * w + li) * BS], t[a]);
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    v4d y = v4d{0, 0, 0, 0};
+#pragma unroll
+    for (int b = 0; b <= a; ++b)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) y = M::op(Y1[(16 * a + li) + (16 * b + M::row(lane, q)) * BS], t[b][q], y);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) X[BS + 16 * a + M::row(lane, q) + (16 * w + li) * TB] = -y[q];
+  }
+}
+
+// y = L^-1 b.  Lane l holds rows l and l + 64 of its block, wave w the columns
+// 16 w .. 16 w + 15 of each tile; the waves' sums meet in LDS once per block.
+template <int NR>
+__global__ __launch_bounds__(512) void k_tri_fwd(const double* __restrict__ L, int64_t ld, int64_t n,
+                                                 const double* __restrict__ inv, const int32_t* __restrict__ lo,
+                                                 const double* __restrict__ b0, const double* __restrict__ b1,
+                                                 double* ex_y, double* __restrict__ ex_x,
+                                                 unsigned* __restrict__ ticket) {
+  __shared__ double part[8][NR][TB];
+  __shared__ double bb[NR][TB];
+  __shared__ int blk;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (tid == 0) blk = (int)atomicAdd(&ticket[0], 1u);
+  __syncthreads();
+  const int B = __builtin_amdgcn_readfirstlane(blk);
+  if (B == 0 && tid == 0) ticket[1] = 0;   // the backward pass's
+  const int64_t c = (int64_t)B * TB;
+  const int ri = tid & (TB - 1), rr = tid / TB;   // row and right-hand side of the block's vectors
+  const bool mine = rr < NR && c + ri < n;
+  if (mine) ex_clear(ex_x + rr * n + c + ri);
+  const double rhs = mine ? (rr == 0 ? b0 : b1)[c + ri] : 0.0;
+  const double* X = inv + (int64_t)B * TB * TB + lane + 16 * w * TB;
+  const double* p0 = L + std::min<int64_t>(c + lane, n - 1) + 16 * w * ld;
+  const double* p1 = L + std::min<int64_t>(c + 64 + lane, n - 1) + 16 * w * ld;
+  double l0[16], l1[16], x0[16], x1[16], acc[NR][2] = {};
+  auto load = [&](int k) {
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      l0[q] = p0[((int64_t)k * TB + q) * ld];
+      l1[q] = p1[((int64_t)k * TB + q) * ld];
+    }
+  };
+  const int k0 = lo ? lo[B] : 0;
+  if (k0 < B) load(k0);
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    x0[q] = X[q * TB];
+    x1[q] = X[q * TB + 64];
+  }
+  // lane 16 r + q of a wave polls y[q] of right-hand side r
+  const double* py = ex_y + ((lane >> 4) % NR) * n + 16 * w + (lane & 15);
+  int budget = POLL_MAX;
+  for (int k = k0; k < B; ++k) {
+    const double* const at[1] = {py + (int64_t)k * TB};
+    double y[1];
+    ex_poll<1>(at, y, budget);
+#pragma unroll
+    for (int q = 0; q < 16; ++q)
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const double yq = lane_bcast(y[0], 16 * r + q);
+        acc[r][0] = fma(l0[q], yq, acc[r][0]);
+        acc[r][1] = fma(l1[q], yq, acc[r][1]);
+      }
+    if (k + 1 < B) load(k + 1);
+  }
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    part[w][r][lane] = acc[r][0];
+    part[w][r][64 + lane] = acc[r][1];
+  }
+  __syncthreads();
+  if (rr < NR) {
+    double v = rhs;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v -= part[u][rr][ri];
+    bb[rr][ri] = mine ? v : 0.0;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const double t = bb[r][16 * w + q];
+      s0 = fma(x0[q], t, s0);
+      s1 = fma(x1[q], t, s1);
+    }
+    part[w][r][lane] = s0;
+    part[w][r][64 + lane] = s1;
+  }
+  __syncthreads();
+  if (mine) {
+    double v = 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v += part[u][rr][ri];
+    ex_put(ex_y + rr * n + c + ri, v);
+  }
+}
+
+// sums a[0..15] over the wave: lane l returns the total of a[l / 4]
+template <int H>
+__device__ __forceinline__ void halve_sums(double (&a)[16], int lane) {
+#pragma unroll
+  for (int q = 0; q < H; ++q) {
+    const bool up = lane & (4 * H);
+    const double keep = up ? a[q + H] : a[q], send = up ? a[q] : a[q + H];
+    a[q] = keep + __shfl_xor(send, 4 * H, 64);
+  }
+}
+__device__ __forceinline__ double wave_sum16(double (&a)[16], int lane) {
+  halve_sums<8>(a, lane);
+  halve_sums<4>(a, lane);
+  halve_sums<2>(a, lane);
+  halve_sums<1>(a, lane);
+  const double s = a[0] + __shfl_xor(a[0], 1, 64);
+  return s + __shfl_xor(s, 2, 64);
+}
+
+// x = L^-T y, last block first.  Lane l holds the rows l and l + 64 of a tile,
+// wave w the block's columns 16 w .. 16 w + 15, summed over the lanes at the end.
+template <int NR>
+__global__ __launch_bounds__(512) void k_tri_bwd(const double* __restrict__ L, int64_t ld, int64_t n,
+                                                 const double* __restrict__ inv, const int32_t* __restrict__ hi,
+                                                 double* __restrict__ ex_y, double* ex_x,
+                                                 unsigned* __restrict__ ticket, double* __restrict__ o0,
+                                                 double* __restrict__ o1) {
+  __shared__ double bb[NR][TB];
+  __shared__ int blk;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nb = (int)((n + TB - 1) / TB);
+  if (tid == 0) {
+    blk = nb - 1 - (int)atomicAdd(&ticket[1], 1u);
+    if (blk == nb - 1) ticket[0] = 0;   // the forward pass's
+  }
+  __syncthreads();
+  const int B = __builtin_amdgcn_readfirstlane(blk);
+  const int64_t c = (int64_t)B * TB;
+  const double* X = inv + (int64_t)B * TB * TB + lane + 16 * w * TB;
+  const double* pl = L + (c + 16 * w) * ld;
+  double l0[16], l1[16], x0[16], x1[16], acc[NR][16] = {};
+  auto load = [&](int k) {   // columns past n do not occur: a block with blocks after it is whole
+    const int64_t i = (int64_t)k * TB + lane;
+    const double *p0 = pl + std::min<int64_t>(i, n - 1), *p1 = pl + std::min<int64_t>(i + 64, n - 1);
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      l0[q] = p0[q * ld];
+      l1[q] = p1[q * ld];
+    }
+  };
+  const int kh = hi ? hi[B] : nb - 1;
+  if (kh > B) load(kh);
+  // y of this wave's columns, one per group of four lanes; then that place is emptied
+  const int64_t j = c + 16 * w + (lane >> 2);
+  double y[NR];
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    y[r] = j < n ? ex_y[r * n + j] : 0.0;
+    __builtin_amdgcn_wave_barrier();
+    if (j < n && (lane & 3) == 0) ex_clear(ex_y + r * n + j);
+  }
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    x0[q] = X[q * TB];
+    x1[q] = X[q * TB + 64];
+  }
+  int budget = POLL_MAX;
+  for (int k = kh; k > B; --k) {
+    const int64_t i = (int64_t)k * TB + lane;
+    const double* at[2 * NR];
+    at[0] = ex_x + std::min<int64_t>(i, n - 1);
+    at[1] = ex_x + std::min<int64_t>(i + 64, n - 1);
+    if constexpr (NR == 2) {
+      at[2] = at[0] + n;
+      at[3] = at[1] + n;
+    }
+    double v[2 * NR];
+    ex_poll<2 * NR>(at, v, budget);
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const double v0 = i < n ? v[2 * r] : 0.0;   // rows past n repeat the last one's entries of L
+      const double v1 = i + 64 < n ? v[2 * r + 1] : 0.0;
+#pragma unroll
+      for (int q = 0; q < 16; ++q) acc[r][q] = fma(l1[q], v1, fma(l0[q], v0, acc[r][q]));
+    }
+    if (k - 1 > B) load(k - 1);
+  }
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    const double s = wave_sum16(acc[r], lane);
+    if ((lane & 3) == 0) bb[r][16 * w + (lane >> 2)] = j < n ? y[r] - s : 0.0;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    const double t0 = bb[r][lane], t1 = bb[r][64 + lane];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) acc[r][q] = fma(x1[q], t1, x0[q] * t0);
+    const double s = wave_sum16(acc[r], lane);
+    if (j < n && (lane & 3) == 0) {
+      ex_put(ex_x + r * n + j, s);
+      (r == 0 ? o0 : o1)[j] = s;
+    }
+  }
+}
+
+int64_t tri_inv_elems(int64_t n) { return ceil_div(n, TB) * TB * TB; }
+int64_t tri_exchange_elems(int64_t n) { return 4 * n + 1; }
+
+void tri_envelope(int64_t n, const int64_t* last, std::vector<int32_t>& lo, std::vector<int32_t>& hi) {
+  const int64_t nb = ceil_div(n, TB);
+  lo.assign(nb, 0);
+  hi.assign(nb, 0);
+  for (int64_t k = 0; k < nb; ++k)
+    hi[k] = (int32_t)((rows_below(last, n, std::min<int64_t>(n, (k + 1) * TB) - 1) - 1) / TB);
+  for (int64_t b = 0, k = 0; b < nb; ++b) {   // hi is non-decreasing
+    while (hi[k] < b) ++k;
+    lo[b] = (int32_t)k;
+  }
+}
+
+void tri_prepare(const TriSolve& t, const double* L, int64_t nf, int64_t ld, const double* Linv, hipStream_t st) {
+  if (t.n <= 0) return;
+  hipLaunchKernelGGL(k_inv128, dim3((unsigned)ceil_div(t.n, TB)), dim3(256), 0, st, L, ld, nf, Linv, t.inv, t.n, t.ex,
+                     (unsigned*)(t.ex + 4 * t.n));
+  HC_LAUNCH_CHECK();
+}
+
+template <int NR>
+static void tri_solve_nr(const TriSolve& t, const double* L, int64_t ld, const double* b0, const double* b1, double* x0,
+                         double* x1, hipStream_t st) {
+  const unsigned nb = (unsigned)ceil_div(t.n, TB);
+  double *ey = t.ex, *exx = t.ex + 2 * t.n;
+  unsigned* ticket = (unsigned*)(t.ex + 4 * t.n);
+  hipLaunchKernelGGL((k_tri_fwd<NR>), dim3(nb), dim3(512), 0, st, L, ld, t.n, (const double*)t.inv, t.lo, b0, b1, ey,
+                     exx, ticket);
+  HC_LAUNCH_CHECK();
+  hipLaunchKernelGGL((k_tri_bwd<NR>), dim3(nb), dim3(512), 0, st, L, ld, t.n, (const double*)t.inv, t.hi, ey, exx,
+                     ticket, x0, x1);
+  HC_LAUNCH_CHECK();
+}
+
+void tri_solve(const TriSolve& t, const double* L, int64_t ld, const double* const* b, double* const* x, int nrhs,
+               hipStream_t st) {
+  if (t.n <= 0) return;
+  for (int r = 0; r + 1 < nrhs; r += 2) tri_solve_nr<2>(t, L, ld, b[r], b[r + 1], x[r], x[r + 1], st);
+  if (nrhs % 2) tri_solve_nr<1>(t, L, ld, b[nrhs - 1], nullptr, x[nrhs - 1], nullptr, st);
+}
+
+// ---------------------------------------------------------------------------
+// The FP32 mode's triangular solves (a launch per 256-row block and pass; like
+// its panel they keep their order of operations).
 // Inverses of the 256 x 256 diagonal blocks of L (one workgroup per block),
 // from the 64 x 64 block inverses:  X_ii = Linv_i,
 // X_ij = -Linv_i sum_{k=j}^{i-1} L_ik X_kj  (i > j).  X and X' are stored
@@ -1094,22 +1436,21 @@ void dense_cholesky(T* S, int64_t n, int64_t ld, T* Linv, double tol, double fix
 constexpr int SB = 256;   // rows per triangular-solve step
 constexpr int MAXRHS = 4;
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_inv256(const T* __restrict__ L, int64_t ld, const T* __restrict__ Linv,
-                                                int64_t n, T* __restrict__ Xall, T* __restrict__ XTall) {
-  __shared__ T Tt[BS][BS + 1];
+__global__ __launch_bounds__(256) void k_inv256(const float* __restrict__ L, int64_t ld, const float* __restrict__ Linv,
+                                                int64_t n, float* __restrict__ Xall, float* __restrict__ XTall) {
+  __shared__ float Tt[BS][BS + 1];
   const int tid = threadIdx.x;
   const int64_t c = (int64_t)blockIdx.x * SB;
   const int cb = (int)std::min<int64_t>(SB, n - c);
   const int nsub = (cb + BS - 1) / BS;
-  T* X = Xall + (int64_t)blockIdx.x * SB * SB;
-  T* XT = XTall + (int64_t)blockIdx.x * SB * SB;
+  float* X = Xall + (int64_t)blockIdx.x * SB * SB;
+  float* XT = XTall + (int64_t)blockIdx.x * SB * SB;
   for (int e = tid; e < SB * SB; e += 256) {
     const int i = e % SB, j = e / SB;
-    T v = 0;
+    float v = 0;
     if (i / BS == j / BS) {
       if (i / BS < nsub) v = Linv[((c + (i / BS) * BS) / BS) * BS * BS + (i % BS) + (j % BS) * BS];
-      else v = (i == j) ? T(1) : T(0);
+      else v = (i == j) ? float(1) : float(0);
     }
     X[i + j * SB] = v;
   }
@@ -1117,14 +1458,14 @@ __global__ __launch_bounds__(256) void k_inv256(const T* __restrict__ L, int64_t
   const int i0 = 4 * (tid % 16), j0 = 4 * (tid / 16);
   for (int jb = 0; jb < nsub; ++jb)
     for (int ib = jb + 1; ib < nsub; ++ib) {
-      T acc[4][4] = {};
+      float acc[4][4] = {};
       for (int kb = jb; kb < ib; ++kb)
         for (int p = 0; p < BS; ++p) {
-          T la[4], xb[4];
+          float la[4], xb[4];
 #pragma unroll
           for (int a = 0; a < 4; ++a) {
             const int row = ib * BS + i0 + a;   // local row inside the 256 block
-            la[a] = (row < cb && kb * BS + p < cb) ? L[(c + row) + (c + kb * BS + p) * ld] : T(0);
+            la[a] = (row < cb && kb * BS + p < cb) ? L[(c + row) + (c + kb * BS + p) * ld] : float(0);
           }
 #pragma unroll
           for (int q = 0; q < 4; ++q) xb[q] = X[(kb * BS + p) + (jb * BS + j0 + q) * SB];
@@ -1138,10 +1479,10 @@ __global__ __launch_bounds__(256) void k_inv256(const T* __restrict__ L, int64_t
 #pragma unroll
         for (int q = 0; q < 4; ++q) Tt[i0 + a][j0 + q] = acc[a][q];
       __syncthreads();
-      const T* Li = X + (ib * BS) + (ib * BS) * SB;   // Linv_ib sits on X's diagonal
-      T out[4][4] = {};
+      const float* Li = X + (ib * BS) + (ib * BS) * SB;   // Linv_ib sits on X's diagonal
+      float out[4][4] = {};
       for (int p = 0; p < BS; ++p) {
-        T la[4], tb[4];
+        float la[4], tb[4];
 #pragma unroll
         for (int a = 0; a < 4; ++a) la[a] = Li[(i0 + a) + p * SB];
 #pragma unroll
@@ -1165,17 +1506,16 @@ __global__ __launch_bounds__(256) void k_inv256(const T* __restrict__ L, int64_t
 
 int64_t inv256_elems(int64_t n) { return ceil_div(n, SB) * SB * SB; }
 
-template <typename T>
-void dense_block_inverses(const T* L, int64_t n, int64_t ld, const T* Linv, T* X, T* XT, hipStream_t st) {
+void dense_block_inverses(const float* L, int64_t n, int64_t ld, const float* Linv, float* X, float* XT, hipStream_t st) {
   if (n <= 0) return;
-  hipLaunchKernelGGL(k_inv256<T>, dim3((unsigned)ceil_div(n, SB)), dim3(256), 0, st, L, ld, Linv, n, X, XT);
+  hipLaunchKernelGGL(k_inv256, dim3((unsigned)ceil_div(n, SB)), dim3(256), 0, st, L, ld, Linv, n, X, XT);
   HC_LAUNCH_CHECK();
 }
 
 // ---------------------------------------------------------------------------
 // triangular solves, nrhs <= 4 right-hand sides stored column-major with
 // leading dimension n:  forward Y = L^-1 B (B overwritten), backward
-// X = L^-T Y (Y overwritten).  Per 256-row block: one workgroup applies the
+// X = L^-float Y (Y overwritten).  Per 256-row block: one workgroup applies the
 // block inverse (a 256 x 256 triangular matvec), then a bandwidth-bound kernel
 // updates the rows below (forward) or the columns to the left (backward).
 // ---------------------------------------------------------------------------
@@ -1185,26 +1525,26 @@ void dense_block_inverses(const T* L, int64_t n, int64_t ld, const T* Linv, T* X
 // and the 16 partial sums meet in LDS.  The stored inverse is zero outside
 // its triangle and bb is zero past cb, so loads and products need no masks.
 constexpr int DIAG_ROWS = 16;
-template <typename T, int NR>
-__global__ __launch_bounds__(256) void k_trsv_diag(const T* __restrict__ Xinv, int64_t c, int64_t n,
-                                                   const T* __restrict__ Bin, T* __restrict__ Yout, int nrhs) {
-  __shared__ T bb[SB][NR];
-  __shared__ T part[16][DIAG_ROWS][NR];
+template <int NR>
+__global__ __launch_bounds__(256) void k_trsv_diag(const float* __restrict__ Xinv, int64_t c, int64_t n,
+                                                   const float* __restrict__ Bin, float* __restrict__ Yout, int nrhs) {
+  __shared__ float bb[SB][NR];
+  __shared__ float part[16][DIAG_ROWS][NR];
   const int tid = threadIdx.x;
   const int cb = (int)std::min<int64_t>(SB, n - c);
   const int il = tid % DIAG_ROWS, g = tid / DIAG_ROWS;
   const int i = blockIdx.x * DIAG_ROWS + il;
   // the inverse's entries do not depend on the previous kernel: their loads
   // are issued before the right-hand side's, so the two latencies overlap
-  T x[16];
+  float x[16];
 #pragma unroll
   for (int q = 0; q < 16; ++q) x[q] = Xinv[i + (int64_t)(g * 16 + q) * SB];
   for (int e = tid; e < SB * NR; e += 256) {
     const int ie = e % SB, r = e / SB;
-    bb[ie][r] = (ie < cb && r < nrhs) ? Bin[(c + ie) + r * n] : T(0);
+    bb[ie][r] = (ie < cb && r < nrhs) ? Bin[(c + ie) + r * n] : float(0);
   }
   __syncthreads();
-  T acc[NR] = {};
+  float acc[NR] = {};
 #pragma unroll
   for (int q = 0; q < 16; ++q) {
     const int k = g * 16 + q;
@@ -1216,7 +1556,7 @@ __global__ __launch_bounds__(256) void k_trsv_diag(const T* __restrict__ Xinv, i
   __syncthreads();
   if (tid < DIAG_ROWS * NR) {
     const int row = tid % DIAG_ROWS, r = tid / DIAG_ROWS;
-    T v = 0;
+    float v = 0;
 #pragma unroll
     for (int gg = 0; gg < 16; ++gg) v += part[gg][row][r];
     const int ig = blockIdx.x * DIAG_ROWS + row;
@@ -1228,31 +1568,31 @@ __global__ __launch_bounds__(256) void k_trsv_diag(const T* __restrict__ Xinv, i
 // rows; wave w sums columns [16 w, 16 w + 16) with one lane per row (each
 // column read is 512 contiguous bytes, 16 loads in flight per lane), and the
 // 16 partial sums meet in LDS.
-template <typename T, int NR>
-__global__ __launch_bounds__(1024) void k_trsv_fwd_update(const T* __restrict__ L, int64_t ld, int64_t c, int64_t n,
-                                                          T* __restrict__ B, const T* __restrict__ Y, int nrhs) {
-  __shared__ T yb[SB][NR];
-  __shared__ T part[16][64][NR];
+template <int NR>
+__global__ __launch_bounds__(1024) void k_trsv_fwd_update(const float* __restrict__ L, int64_t ld, int64_t c, int64_t n,
+                                                          float* __restrict__ B, const float* __restrict__ Y, int nrhs) {
+  __shared__ float yb[SB][NR];
+  __shared__ float part[16][64][NR];
   const int tid = threadIdx.x;
   const int cb = (int)std::min<int64_t>(SB, n - c);
   const int lane = tid & 63, w = tid >> 6;
   const int64_t row = c + cb + (int64_t)blockIdx.x * 64 + lane;
   const int64_t rowc = std::min<int64_t>(row, n - 1);
   // L's entries do not depend on the previous kernel: loaded before y
-  T l[16];
+  float l[16];
 #pragma unroll
   for (int q = 0; q < 16; ++q) l[q] = L[rowc + (c + std::min(w * 16 + q, cb - 1)) * ld];   // yb is zero past cb
   // the entry of B this thread updates at the end (final before this kernel)
   const int64_t rw = c + cb + (int64_t)blockIdx.x * 64 + (tid % 64);
   const int rr = tid / 64;
   const bool writer = tid < 64 * NR && rw < n && rr < nrhs;
-  const T bold = writer ? B[rw + rr * n] : T(0);
+  const float bold = writer ? B[rw + rr * n] : float(0);
   for (int e = tid; e < SB * NR; e += 1024) {
     const int i = e % SB, r = e / SB;
-    yb[i][r] = (i < cb && r < nrhs) ? Y[(c + i) + r * n] : T(0);
+    yb[i][r] = (i < cb && r < nrhs) ? Y[(c + i) + r * n] : float(0);
   }
   __syncthreads();
-  T acc[NR] = {};
+  float acc[NR] = {};
 #pragma unroll
   for (int q = 0; q < 16; ++q) {
     const int k = w * 16 + q;
@@ -1264,7 +1604,7 @@ __global__ __launch_bounds__(1024) void k_trsv_fwd_update(const T* __restrict__ 
   __syncthreads();
   if (tid < 64 * NR) {
     const int ln = tid % 64;
-    T v = 0;
+    float v = 0;
 #pragma unroll
     for (int ww = 0; ww < 16; ++ww) v += part[ww][ln][rr];
     if (writer) B[rw + rr * n] = bold - v;
@@ -1274,17 +1614,17 @@ __global__ __launch_bounds__(1024) void k_trsv_fwd_update(const T* __restrict__ 
 // columns left of the block: Y[j] -= sum_i L[c + i, j] x[i]; each wave takes
 // four columns (16 loads in flight per lane), lanes run over i
 constexpr int BWD_COLS = 4;
-template <typename T, int NR>
-__global__ __launch_bounds__(256) void k_trsv_bwd_update(const T* __restrict__ L, int64_t ld, int64_t c, int64_t n,
-                                                         int64_t j_begin, T* __restrict__ Yv, const T* __restrict__ X,
+template <int NR>
+__global__ __launch_bounds__(256) void k_trsv_bwd_update(const float* __restrict__ L, int64_t ld, int64_t c, int64_t n,
+                                                         int64_t j_begin, float* __restrict__ Yv, const float* __restrict__ X,
                                                          int nrhs) {
-  __shared__ T xb[SB][NR];
+  __shared__ float xb[SB][NR];
   const int tid = threadIdx.x;
   const int cb = (int)std::min<int64_t>(SB, n - c);
   const int lane = tid & 63;
   const int64_t j0 = j_begin + ((int64_t)blockIdx.x * 4 + (tid >> 6)) * BWD_COLS;
   // L's entries do not depend on the previous kernel: loaded before x
-  T l[BWD_COLS][SB / 64];
+  float l[BWD_COLS][SB / 64];
 #pragma unroll
   for (int cc = 0; cc < BWD_COLS; ++cc) {
     const int64_t j = std::min<int64_t>(j0 + cc, c - 1);
@@ -1292,7 +1632,7 @@ __global__ __launch_bounds__(256) void k_trsv_bwd_update(const T* __restrict__ L
     for (int q = 0; q < SB / 64; ++q) l[cc][q] = L[(c + std::min(lane + 64 * q, cb - 1)) + j * ld];   // xb is zero past cb
   }
   // the entries of Y lane 0 updates at the end (final before this kernel)
-  T yold[BWD_COLS][NR] = {};
+  float yold[BWD_COLS][NR] = {};
   if (lane == 0)
 #pragma unroll
     for (int cc = 0; cc < BWD_COLS; ++cc)
@@ -1302,10 +1642,10 @@ __global__ __launch_bounds__(256) void k_trsv_bwd_update(const T* __restrict__ L
           if (r < nrhs) yold[cc][r] = Yv[(j0 + cc) + r * n];
   for (int e = tid; e < SB * NR; e += 256) {
     const int i = e % SB, r = e / SB;
-    xb[i][r] = (i < cb && r < nrhs) ? X[(c + i) + r * n] : T(0);
+    xb[i][r] = (i < cb && r < nrhs) ? X[(c + i) + r * n] : float(0);
   }
   __syncthreads();
-  T acc[BWD_COLS][NR] = {};
+  float acc[BWD_COLS][NR] = {};
 #pragma unroll
   for (int cc = 0; cc < BWD_COLS; ++cc) {
 #pragma unroll
@@ -1319,7 +1659,7 @@ __global__ __launch_bounds__(256) void k_trsv_bwd_update(const T* __restrict__ L
   for (int cc = 0; cc < BWD_COLS; ++cc)
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-      T v = acc[cc][r];
+      float v = acc[cc][r];
       for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
       acc[cc][r] = v;
     }
@@ -1335,32 +1675,32 @@ __global__ __launch_bounds__(256) void k_trsv_bwd_update(const T* __restrict__ L
 // With an envelope (`last`, see dense_cholesky) the forward updates stop at
 // the rows a block's columns reach and the backward updates start at the
 // first column its rows reach: entries outside are zero.
-template <typename T, int NR>
-static void dense_solve_nr(const T* L, int64_t n, int64_t ld, const T* X256, const T* XT256, T* B, T* Y, T* X,
+template <int NR>
+static void dense_solve_nr(const float* L, int64_t n, int64_t ld, const float* X256, const float* XT256, float* B, float* Y, float* X,
                            int nrhs, const int64_t* last, hipStream_t st) {
   for (int64_t c = 0; c < n; c += SB) {
-    const T* Xi = X256 + (c / SB) * SB * SB;
-    hipLaunchKernelGGL((k_trsv_diag<T, NR>), dim3(SB / DIAG_ROWS), dim3(256), 0, st, Xi, c, n, (const T*)B, Y, nrhs);
+    const float* Xi = X256 + (c / SB) * SB * SB;
+    hipLaunchKernelGGL((k_trsv_diag<NR>), dim3(SB / DIAG_ROWS), dim3(256), 0, st, Xi, c, n, (const float*)B, Y, nrhs);
     HC_LAUNCH_CHECK();
     const int64_t cend = std::min<int64_t>(n, c + SB);
     const int64_t below = rows_below(last, n, cend - 1) - cend;
     if (below > 0) {
-      hipLaunchKernelGGL((k_trsv_fwd_update<T, NR>), dim3((unsigned)ceil_div(below, 64)), dim3(1024), 0, st, L, ld, c,
-                         n, B, (const T*)Y, nrhs);
+      hipLaunchKernelGGL((k_trsv_fwd_update<NR>), dim3((unsigned)ceil_div(below, 64)), dim3(1024), 0, st, L, ld, c,
+                         n, B, (const float*)Y, nrhs);
       HC_LAUNCH_CHECK();
     }
   }
   const int64_t lastb = ((n - 1) / SB) * SB;
   for (int64_t c = lastb; c >= 0; c -= SB) {
-    const T* XTi = XT256 + (c / SB) * SB * SB;
-    hipLaunchKernelGGL((k_trsv_diag<T, NR>), dim3(SB / DIAG_ROWS), dim3(256), 0, st, XTi, c, n, (const T*)Y, X, nrhs);
+    const float* XTi = XT256 + (c / SB) * SB * SB;
+    hipLaunchKernelGGL((k_trsv_diag<NR>), dim3(SB / DIAG_ROWS), dim3(256), 0, st, XTi, c, n, (const float*)Y, X, nrhs);
     HC_LAUNCH_CHECK();
     // first column with a nonzero in rows >= c (last is non-decreasing)
     int64_t jb = 0;
     if (last) jb = (std::upper_bound(last, last + c, c) - last) / (4 * BWD_COLS) * (4 * BWD_COLS);
     if (c > jb) {
-      hipLaunchKernelGGL((k_trsv_bwd_update<T, NR>), dim3((unsigned)ceil_div(c - jb, 4 * BWD_COLS)), dim3(256), 0, st,
-                         L, ld, c, n, jb, Y, (const T*)X, nrhs);
+      hipLaunchKernelGGL((k_trsv_bwd_update<NR>), dim3((unsigned)ceil_div(c - jb, 4 * BWD_COLS)), dim3(256), 0, st,
+                         L, ld, c, n, jb, Y, (const float*)X, nrhs);
       HC_LAUNCH_CHECK();
     }
   }
@@ -1368,13 +1708,12 @@ static void dense_solve_nr(const T* L, int64_t n, int64_t ld, const T* X256, con
 
 // kernels specialised for one right-hand side (the iteration's case) and for
 // up to MAXRHS
-template <typename T>
-void dense_solve(const T* L, int64_t n, int64_t ld, const T* X256, const T* XT256, T* B, T* Y, T* X, int nrhs,
+void dense_solve(const float* L, int64_t n, int64_t ld, const float* X256, const float* XT256, float* B, float* Y, float* X, int nrhs,
                  hipStream_t st, const int64_t* last) {
   if (n <= 0) return;
-  if (nrhs == 1) dense_solve_nr<T, 1>(L, n, ld, X256, XT256, B, Y, X, nrhs, last, st);
-  else if (nrhs == 2) dense_solve_nr<T, 2>(L, n, ld, X256, XT256, B, Y, X, nrhs, last, st);
-  else dense_solve_nr<T, MAXRHS>(L, n, ld, X256, XT256, B, Y, X, nrhs, last, st);
+  if (nrhs == 1) dense_solve_nr<1>(L, n, ld, X256, XT256, B, Y, X, nrhs, last, st);
+  else if (nrhs == 2) dense_solve_nr<2>(L, n, ld, X256, XT256, B, Y, X, nrhs, last, st);
+  else dense_solve_nr<MAXRHS>(L, n, ld, X256, XT256, B, Y, X, nrhs, last, st);
 }
 
 template void dense_cholesky<double>(double*, int64_t, int64_t, double*, double, double, unsigned long long*,
@@ -1385,14 +1724,6 @@ template void gemm_nt<double>(double*, int64_t, const double*, int64_t, const do
                               int64_t, double, bool, int64_t, int64_t, hipStream_t, GemmRole);
 template void gemm_nt<float>(float*, int64_t, const float*, int64_t, const float*, int64_t, int64_t, int64_t,
                              int64_t, float, bool, int64_t, int64_t, hipStream_t, GemmRole);
-template void dense_solve<double>(const double*, int64_t, int64_t, const double*, const double*, double*, double*,
-                                  double*, int, hipStream_t, const int64_t*);
-template void dense_solve<float>(const float*, int64_t, int64_t, const float*, const float*, float*, float*, float*,
-                                 int, hipStream_t, const int64_t*);
-template void dense_block_inverses<double>(const double*, int64_t, int64_t, const double*, double*, double*,
-                                           hipStream_t);
-template void dense_block_inverses<float>(const float*, int64_t, int64_t, const float*, float*, float*, hipStream_t);
-
 int64_t linv_elems(int64_t n) { return ceil_div(n, BS) * BS * BS; }
 
 // factor flops of a dense n x n Cholesky

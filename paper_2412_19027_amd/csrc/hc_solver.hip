@@ -129,6 +129,7 @@ struct hc_solver {
   // two-level split of the Schur complement (leaf blocks + dense tail)
   int64_t nt = 0;                  // tail columns
   std::vector<int64_t> tail_last;  // envelope of the tail (see dense_cholesky), padded to ld
+  std::vector<int32_t> tri_lo, tri_hi;   // and by the triangular solves' blocks (tri_envelope)
   bool leaves = false;             // any leaf block
   std::vector<int32_t> col_leaf, col_loc, tail_cols, leaf_size, leaf_cols, leaf_ccnt, leaf_clist;
   std::vector<int64_t> leaf_lval_off, leaf_lcol_off, leaf_clist_off, leaf_cval_off;
@@ -173,7 +174,7 @@ struct hc_solver {
   double *uT = nullptr, *xT = nullptr;   // compact tail vectors
   double *uTb = nullptr, *xTb = nullptr; // and those of a second right-hand side
   float *dS32 = nullptr, *dLinv32 = nullptr;
-  double *dX256 = nullptr, *dXT256 = nullptr;
+  TriSolve tri;                     // FP64 triangular solves with the tail's factor
   float *dX256f = nullptr, *dXT256f = nullptr;
   unsigned long long* dhits = nullptr;
   int* dpd = nullptr;
@@ -189,7 +190,7 @@ struct hc_solver {
   double *Px, *Ax, *Atz, *rdv, *rpv;   // rdv = Px + A'z + q tau ; rpv = -Ax - s + b tau
   double *x2, *z2, *x1, *z1, *dx, *dz, *dsv, *dsrhs, *dxa, *dza, *dsa;
   double *r1, *r2, *irx, *irz, *irxn, *irzn, *irbx, *irbz, *irrx, *irrz, *kx, *kz, *t1, *t2, *u1, *w1;
-  double *sb, *sy, *sx;             // dense solve buffers (two right-hand sides of n_T)
+  double* sb;                       // diagonal of the tail (mixed mode)
   // the second system's refinement vectors (kkt_solve_pair) and the constant
   // system's first block
   double *jrx, *jrz, *jrxn, *jrzn, *jrbx, *jrbz, *jrrx, *jrrz, *jkx, *jkz, *u1b, *r1c;
@@ -1086,6 +1087,7 @@ void setup_host(hc_solver* S, const hc_problem* p) {
   build_lowrank(S, nd);
   S->ld = ((S->nt + 63) / 64) * 64;
   for (int64_t t = S->nt; t < S->ld; ++t) S->tail_last.push_back(t + 1);   // identity padding
+  tri_envelope(S->nt, S->tail_last.data(), S->tri_lo, S->tri_hi);
   if (S->st.static_reg <= 0) S->st.static_reg = S->mixed ? 3.4526698300124393e-04 : 1e-8;
   if (S->st.dyn_reg < 0) S->st.dyn_reg = S->mixed ? std::ldexp(1.0, -46) : std::ldexp(1.0, -104);
   if (S->st.ir_mu_frac < 0) S->st.ir_mu_frac = S->mixed ? 1e-3 : 0.0;
@@ -1940,11 +1942,11 @@ void factor(hc_solver* S, bool fp64 = false) {
     lower_to_f32(ntp, S->ld, S->dS, S->dS32, st);
     dense_cholesky<float>(S->dS32, ntp, S->ld, S->dLinv32, tol, S->delta, S->dhits, st, pf, lookahead(S),
                           S->tail_last.data());
-    dense_block_inverses<float>(S->dS32, ntp, S->ld, S->dLinv32, S->dX256f, S->dXT256f, st);
+    dense_block_inverses(S->dS32, ntp, S->ld, S->dLinv32, S->dX256f, S->dXT256f, st);
   } else {
     dense_cholesky<double>(S->dS, ntp, S->ld, S->dLinv, tol, S->delta, S->dhits, st, pf, lookahead(S),
                            S->tail_last.data());
-    dense_block_inverses<double>(S->dS, ntp, S->ld, S->dLinv, S->dX256, S->dXT256, st);
+    tri_prepare(S->tri, S->dS, ntp, S->ld, S->dLinv, st);
   }
   S->info.factorizations++;
   if (pf) {
@@ -1991,16 +1993,11 @@ void schur_solve_n(hc_solver* S, int k, const double* const* u, double* const* x
       combine_max(nb, S->dpart, S->dscal + r, st);
       to_f32(nt, ut[r], S->dscal + r, S->sb32 + r * nt, st);
     }
-    dense_solve<float>(S->dS32, nt, S->ld, S->dX256f, S->dXT256f, S->sb32, S->sy32, S->sx32, k, st,
+    dense_solve(S->dS32, nt, S->ld, S->dX256f, S->dXT256f, S->sb32, S->sy32, S->sx32, k, st,
                        S->tail_last.data());
     for (int r = 0; r < k; ++r) from_f32(nt, S->sx32 + r * nt, S->dscal + r, xt[r], st);
-  } else if (k == 1) {
-    vcopy(nt, ut[0], S->sb, st);
-    dense_solve<double>(S->dS, nt, S->ld, S->dX256, S->dXT256, S->sb, S->sy, xt[0], 1, st, S->tail_last.data());
   } else {
-    for (int r = 0; r < k; ++r) vcopy(nt, ut[r], S->sb + r * nt, st);
-    dense_solve<double>(S->dS, nt, S->ld, S->dX256, S->dXT256, S->sb, S->sy, S->sx, k, st, S->tail_last.data());
-    for (int r = 0; r < k; ++r) vcopy(nt, S->sx + r * nt, xt[r], st);
+    tri_solve(S->tri, S->dS, S->ld, ut, xt, k, st);
   }
   if (S->leaves)
     for (int r = 0; r < k; ++r) {
@@ -2705,8 +2702,11 @@ void alloc_all(hc_solver* S, Buf& buf, hipStream_t st) {
   const int64_t nt = S->nt, ntp = S->ld;   // the tail is factored padded to ld
   S->dS = buf.take<double>((size_t)S->ld * ntp);
   S->dLinv = buf.take<double>(linv_elems(ntp));
-  S->dX256 = buf.take<double>(inv256_elems(ntp));
-  S->dXT256 = buf.take<double>(inv256_elems(ntp));
+  S->tri.n = nt;
+  S->tri.inv = buf.take<double>(tri_inv_elems(nt));
+  S->tri.ex = buf.take<double>(tri_exchange_elems(nt));
+  S->tri.lo = upload(buf, S->tri_lo, st);
+  S->tri.hi = upload(buf, S->tri_hi, st);
   if (S->mixed) {
     S->dS32 = buf.take<float>((size_t)S->ld * ntp);
     S->dLinv32 = buf.take<float>(linv_elems(ntp));
@@ -2819,9 +2819,7 @@ void alloc_all(hc_solver* S, Buf& buf, hipStream_t st) {
   S->t2 = buf.take<double>(L);
   S->u1 = buf.take<double>(L);
   S->w1 = buf.take<double>(L);
-  S->sb = buf.take<double>(2 * nt);
-  S->sy = buf.take<double>(2 * nt);
-  S->sx = buf.take<double>(2 * nt);
+  S->sb = buf.take<double>(nt);
   // the second system of kkt_solve_pair
   double** vecs2[] = {&S->jrx, &S->jrz, &S->jrxn, &S->jrzn, &S->jrbx, &S->jrbz, &S->jrrx, &S->jrrz,
                       &S->jkx, &S->jkz, &S->u1b, &S->r1c};

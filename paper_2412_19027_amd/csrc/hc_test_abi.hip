@@ -330,22 +330,39 @@ int32_t hc_test_dense_chol_solve_env(int32_t precision, int64_t n, int64_t ld, d
         dense_cholesky<float>(A32, n, ld, L32, 0.0, 1e-8, hits, st, nullptr, &aux, last);
         float* X32 = (float*)al(inv256_elems(n) * 4);
         float* XT32 = (float*)al(inv256_elems(n) * 4);
-        dense_block_inverses<float>(A32, n, ld, L32, X32, XT32, st);
+        dense_block_inverses(A32, n, ld, L32, X32, XT32, st);
         double* one = (double*)al(8);
         const double h1 = 1.0;
         HC_HIP(hipMemcpyAsync(one, &h1, 8, hipMemcpyHostToDevice, st));
         to_f32((int64_t)n * nrhs, B, one, b32, st);
-        dense_solve<float>(A32, n, ld, X32, XT32, b32, y32, x32, nrhs, st, last);
+        dense_solve(A32, n, ld, X32, XT32, b32, y32, x32, nrhs, st, last);
         from_f32((int64_t)n * nrhs, x32, one, B, st);
       } else {
         double* Li = (double*)al(linv_elems(n) * 8);
-        double* y = (double*)al((size_t)n * nrhs * 8);
         double* x = (double*)al((size_t)n * nrhs * 8);
         dense_cholesky<double>(A, n, ld, Li, 0.0, 1e-8, hits, st, nullptr, &aux, last);
-        double* X64 = (double*)al(inv256_elems(n) * 8);
-        double* XT64 = (double*)al(inv256_elems(n) * 8);
-        dense_block_inverses<double>(A, n, ld, Li, X64, XT64, st);
-        dense_solve<double>(A, n, ld, X64, XT64, B, y, x, nrhs, st, last);
+        TriSolve t;
+        t.n = n;
+        t.inv = (double*)al(tri_inv_elems(n) * 8);
+        t.ex = (double*)al(tri_exchange_elems(n) * 8);
+        std::vector<int32_t> lo, hi;
+        if (last) {
+          tri_envelope(n, last, lo, hi);
+          int32_t* env = (int32_t*)al(2 * lo.size() * 4);
+          HC_HIP(hipMemcpyAsync(env, lo.data(), lo.size() * 4, hipMemcpyHostToDevice, st));
+          HC_HIP(hipMemcpyAsync(env + lo.size(), hi.data(), hi.size() * 4, hipMemcpyHostToDevice, st));
+          HC_HIP(hipStreamSynchronize(st));
+          t.lo = env;
+          t.hi = env + lo.size();
+        }
+        tri_prepare(t, A, n, ld, Li, st);
+        const double* bs[4];
+        double* xs[4];
+        for (int r = 0; r < nrhs; ++r) {
+          bs[r] = B + (int64_t)r * n;
+          xs[r] = x + (int64_t)r * n;
+        }
+        tri_solve(t, A, ld, bs, xs, nrhs, st);
         HC_HIP(hipMemcpyAsync(B, x, (size_t)n * nrhs * 8, hipMemcpyDeviceToDevice, st));
       }
       unsigned long long h = 0;

@@ -43,3 +43,27 @@ def test_pivot_guard_in_a_panel():
     assert hits == 2
     d = torch.tril(L).diagonal()
     assert abs(d[130].item() ** 2 - 1e-8) <= 1e-22 and abs(d[131].item() ** 2 - 1e-8) <= 1e-22
+
+
+@pytest.mark.parametrize("n,nrhs,width", [(1, 1, 0), (127, 2, 0), (128, 1, 0), (129, 3, 0), (257, 2, 1), (640, 4, 64),
+                                          (901, 2, 130), (2049, 1, 300)])
+def test_triangular_solves(n, nrhs, width):
+    """Both passes over 128-row blocks: partial last blocks, one to four
+    right-hand sides (in pairs), dense (width 0) and with an envelope that
+    leaves blocks uncoupled; two factorisations in a row on new data."""
+    for seed in (1, 2):
+        g = torch.Generator(device="cuda").manual_seed(10 * n + seed)
+        G = torch.randn(n, n, dtype=torch.float64, device="cuda", generator=g)
+        i = torch.arange(n, device="cuda")
+        if width:
+            G = torch.where((i[:, None] - i[None, :]).clamp(min=0) <= width // 2, torch.tril(G), 0.0)
+        A = G @ G.t() / (width or n)
+        A.diagonal().add_(0.5)
+        last = None
+        if width:   # rows a column reaches, non-decreasing
+            last = torch.clamp(i + width // 2 * 2 + 1, max=n).cpu().numpy()
+        B = torch.randn(n, nrhs, dtype=torch.float64, device="cuda", generator=g)
+        X, _, hits = HC.test_dense_chol_solve(A, B.clone(), ld=(n + 63) // 64 * 64, last=last)
+        tol = 24 * (n + 1) * 2.0 ** -53 * A.diagonal().max().item()
+        assert hits == 0
+        assert ((A @ X - B).abs().amax(0) <= tol * X.abs().sum(0)).all()
