@@ -34,13 +34,32 @@ void cone_mblock(const SegDev& g, double delta, double* work, hipStream_t st);
 // over every segment, all but the PSD ones in one launch
 void cone_mblock_all(const std::vector<SegDev>& segs, double delta, double* work, hipStream_t st);
 int64_t cone_mblock_work(const SegDev& g);
-// y[rows] = H x[rows]  (mode 0) or (H + delta I)^-1 x[rows] (mode 1), spectral form.
-void cone_apply(const SegDev& g, int mode, double delta, const double* x, double* y, hipStream_t st);
-// y[rows] = -ds[rows] - H x[rows]  (direction recovery of Delta s)
-void cone_recover_ds(const SegDev& g, const double* dsrhs, const double* dz, double* out, hipStream_t st);
-// cone_apply (dsr null) or cone_recover_ds (dsr given, mode 0) over every
-// segment: the lane-per-cone families (zero, nonneg, SOC up to SOC_DMAX,
-// exp, pow) in one launch, PSD and larger SOC segments by their own kernels
+// v = H x (mode 0) or (H + delta I)^-1 x (mode 1) over every segment, spectral
+// form, for one or two vectors side by side, each with what its caller does
+// with v:
+//   EPI_PUT   y = v
+//   EPI_ADD   y = a + v
+//   EPI_RESID y = b - (a - v), and max |y| of its block in pmax (NaN stays NaN)
+//   EPI_NEG   y = -a - v        (recovery of Delta s from a = d_s)
+// The lane-per-cone families (zero, nonneg, SOC up to SOC_DMAX, exp, pow) run
+// in one launch for all segments and vectors, PSD segments in one each, larger
+// SOCs in one per vector (for EPI_ADD and EPI_RESID these two leave v in y and
+// the common launch finishes the rows).  cone_apply_parts: partials per vector
+// (EPI_RESID), at most 1,024 per segment.
+enum { EPI_PUT = 0, EPI_ADD = 1, EPI_RESID = 2, EPI_NEG = 3 };
+struct ApplySys {
+  const double* x;
+  double* y;
+  const double *a, *b;
+  double* pmax;
+};
+struct ApplySys2 {
+  ApplySys s[2];
+};
+void cone_apply_sys(const std::vector<SegDev>& segs, int mode, double delta, int epi, const ApplySys* sys, int ns,
+                    hipStream_t st);
+int64_t cone_apply_parts(const std::vector<SegDev>& segs);
+// one vector: y = v, or with dsr y = -dsr - v
 void cone_apply_all(const std::vector<SegDev>& segs, int mode, double delta, const double* x, const double* dsr,
                     double* y, hipStream_t st);
 // combined-step d_s (eq. ds-correction-step) from the scaling state

@@ -467,24 +467,25 @@ constexpr int FUSED_SEGS = 8;
 // ===========================================================================
 __device__ inline double fsel(int mode, double lam, double delta) { return mode == 0 ? lam : 1.0 / (lam + delta); }
 
-// one cone (or zero/nonneg row) i of segment g: y = H x (mode 0) or
-// (H + delta I)^-1 x (mode 1); with dsr (mode 0): y = -dsr - H x, the
-// direction recovery of Delta s
+// one cone (or zero/nonneg row) i of segment g: put(row, v) for the rows of
+// v = H x (mode 0) or (H + delta I)^-1 x
+template <typename F>
 __device__ inline void cone_apply_one(const SegDev& g, int64_t i, int mode, double delta, const double* __restrict__ x,
-                                      const double* __restrict__ dsr, double* __restrict__ y) {
+                                      F&& put) {
   const int64_t N = g.count;
   switch (g.kind) {
     case HC_CONE_ZERO:
-      y[g.base + i] = dsr ? -dsr[g.base + i] : ((mode == 0) ? 0.0 : x[g.base + i] / delta);
+      put(g.base + i, (mode == 0) ? 0.0 : x[g.base + i] / delta);
       break;
     case HC_CONE_NONNEG: {
       const double h = g.state[i], xv = x[g.base + i];
-      y[g.base + i] = dsr ? -dsr[g.base + i] - h * xv : ((mode == 0) ? h * xv : (1.0 / (h + delta)) * xv);
+      put(g.base + i, (mode == 0) ? h * xv : (1.0 / (h + delta)) * xv);
       break;
     }
     case HC_CONE_SOC: {
       const int d = g.dim;
-      double wb[SOC_DMAX], xv[SOC_DMAX], yv[SOC_DMAX];
+      // cleared: rows above d would be carried from one cone to the next (244 VGPRs, not 122)
+      double wb[SOC_DMAX] = {}, xv[SOC_DMAX] = {}, yv[SOC_DMAX] = {};
       for (int j = 0; j < d; ++j) {
         wb[j] = g.state[j * N + i];
         xv[j] = x[g.base + j * N + i];
@@ -493,7 +494,7 @@ __device__ inline void cone_apply_one(const SegDev& g, int64_t i, int mode, doub
       const SocSpec sp = soc_spec(wb, d, eta);
       soc_spec_apply(wb, d, sp, fsel(mode, sp.lp, delta), fsel(mode, sp.lm, delta), fsel(mode, sp.lo, delta), xv,
                      yv);
-      for (int j = 0; j < d; ++j) y[g.base + j * N + i] = dsr ? -dsr[g.base + j * N + i] - yv[j] : yv[j];
+      for (int j = 0; j < d; ++j) put(g.base + j * N + i, yv[j]);
       break;
     }
     case HC_CONE_EXP:
@@ -506,10 +507,8 @@ __device__ inline void cone_apply_one(const SegDev& g, int64_t i, int mode, doub
       }
       double p[3];
       for (int r = 0; r < 3; ++r) p[r] = lam[r] * (V[0 * 3 + r] * xv[0] + V[1 * 3 + r] * xv[1] + V[2 * 3 + r] * xv[2]);
-      for (int j = 0; j < 3; ++j) {
-        const double hv = V[j * 3 + 0] * p[0] + V[j * 3 + 1] * p[1] + V[j * 3 + 2] * p[2];
-        y[g.base + j * N + i] = dsr ? -dsr[g.base + j * N + i] - hv : hv;
-      }
+      for (int j = 0; j < 3; ++j)
+        put(g.base + j * N + i, V[j * 3 + 0] * p[0] + V[j * 3 + 1] * p[1] + V[j * 3 + 2] * p[2]);
       break;
     }
     default:
@@ -517,10 +516,15 @@ __device__ inline void cone_apply_one(const SegDev& g, int64_t i, int mode, doub
   }
 }
 
-__global__ __launch_bounds__(CONE_BLOCK) void k_cone_apply(SegDev g, int mode, double delta, const double* __restrict__ x,
-                             double* __restrict__ y) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < g.count) cone_apply_one(g, i, mode, delta, x, nullptr, y);
+// v is rounded before it is added (no fused multiply-add with the product it
+// may be), as when the application and the sum were two launches
+template <int EPI>
+__device__ inline double epilogue(const ApplySys& s, int64_t r, double v) {
+  if (EPI == EPI_NEG) return -s.a[r] - v;
+  {
+#pragma clang fp contract(off)
+    return EPI == EPI_PUT ? v : EPI == EPI_ADD ? s.a[r] + v : s.b[r] - (s.a[r] - v);
+  }
 }
 
 // every lane-per-cone segment in one launch: block b belongs to the segment s
@@ -530,31 +534,56 @@ struct SegTable {
   int32_t first[FUSED_SEGS + 1];
   int32_t nseg;
 };
+constexpr int SEG_ROWS = -1;     // SegDev::kind of rows whose v is in y already
+constexpr int SEG_BLOCKS = 1024; // blocks per segment of k_cone_apply_fused
 
-__global__ __launch_bounds__(CONE_BLOCK) void k_cone_apply_fused(SegTable tb, int mode, double delta, const double* __restrict__ x,
-                                   const double* __restrict__ dsr, double* __restrict__ y) {
+template <int EPI>
+__global__ __launch_bounds__(CONE_BLOCK) void k_cone_apply_fused(SegTable tb, int mode, double delta, ApplySys2 ss) {
+  __shared__ double red[CONE_BLOCK / 64];
+  const ApplySys& sy = ss.s[blockIdx.y];
   int s = 0;
   while (s + 1 < tb.nseg && (int)blockIdx.x >= tb.first[s + 1]) ++s;
-  const int64_t i = (int64_t)(blockIdx.x - tb.first[s]) * blockDim.x + threadIdx.x;
-  if (i < tb.g[s].count) cone_apply_one(tb.g[s], i, mode, delta, x, dsr, y);
+  const SegDev& g = tb.g[s];
+  const int64_t stride = (int64_t)(tb.first[s + 1] - tb.first[s]) * CONE_BLOCK;
+  double mx = 0.0;
+  auto put = [&](int64_t r, double v) {
+    const double y = epilogue<EPI>(sy, r, v);
+    sy.y[r] = y;
+    if (EPI == EPI_RESID) mx = (mx != mx || y != y) ? NAN : fmax(mx, fabs(y));
+  };
+  for (int64_t i = (int64_t)(blockIdx.x - tb.first[s]) * CONE_BLOCK + threadIdx.x; i < g.count; i += stride) {
+    if (g.kind == SEG_ROWS) put(g.base + i, sy.y[g.base + i]);
+    else cone_apply_one(g, i, mode, delta, sy.x, put);
+  }
+  if (EPI == EPI_RESID) {
+    for (int off = 32; off > 0; off >>= 1) {
+      const double o = __shfl_xor(mx, off, 64);
+      mx = (mx != mx || o != o) ? NAN : fmax(mx, o);
+    }
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      for (int w = 1; w < CONE_BLOCK / 64; ++w) mx = (mx != mx || red[w] != red[w]) ? NAN : fmax(mx, red[w]);
+      sy.pmax[blockIdx.x] = mx;
+    }
+  }
 }
 
 // Spectral application, one workgroup per cone (one lane per cone would pay
 // k^3 dependent LDS round trips for each of the four k x k products): one
 // wave up to side 12, four above.  The threads split every product by output
 // entry; Q, X and the two intermediate products live in LDS (row stride
-// KM + 1).  With dsr the kernel returns the direction recovery -dsr - H dz
-// instead (mode 0).
+// KM + 1).  blockIdx.y selects the vector.
 template <int KM>
-__global__ __launch_bounds__(KM <= 12 ? 64 : 256) void k_psd_apply_wave(SegDev g, int mode, double delta, const double* __restrict__ x,
-                                                       const double* __restrict__ dsr, double* __restrict__ y) {
+__global__ __launch_bounds__(KM <= 12 ? 64 : 256) void k_psd_apply_wave(SegDev g, int mode, double delta, int epi, ApplySys2 ss) {
   constexpr int LD = KM + 1;
   __shared__ double Q[KM * LD], X[KM * LD], T[KM * LD], U[KM * LD], m[KM];
   const int k = g.k, lane = threadIdx.x, sd = g.dim;
   const int64_t N = g.count, kk = (int64_t)k * k;
   constexpr int NT = KM <= 12 ? 64 : 256;   // four waves per cone above side 12
+  const ApplySys& sy = ss.s[blockIdx.y];
   for (int64_t c = blockIdx.x; c < N; c += gridDim.x) {
-    const double* xc = x + g.base + c * sd;
+    const double* xc = sy.x + g.base + c * sd;
     __syncthreads();   // the previous cone's readers are done
     for (int e = lane; e < k * k; e += NT) Q[(e / k) * LD + e % k] = g.state[(2 * kk + e) * N + c];
     for (int e = lane; e < k; e += NT) m[e] = g.state[(3 * kk + k + e) * N + c];
@@ -610,79 +639,82 @@ __global__ __launch_bounds__(KM <= 12 ? 64 : 256) void k_psd_apply_wave(SegDev g
       const int i = p - j * (j + 1) / 2;
       const double v = X[i * LD + j] * (i == j ? 1.0 : 1.41421356237309504880);
       const int64_t r = g.base + c * sd + p;
-      y[r] = dsr ? -dsr[r] - v : v;
+      sy.y[r] = epi == EPI_NEG ? -sy.a[r] - v : v;
     }
   }
-}
-
-void cone_apply(const SegDev& g, int mode, double delta, const double* x, double* y, hipStream_t st) {
-  if (g.count == 0) return;
-  if (soc_large(g.kind, g.dim))
-    lsoc_apply(g, mode, delta, x, nullptr, y, st);
-  else if (g.kind == HC_CONE_PSD)
-    if (g.k <= PSD_KSMALL)
-      hipLaunchKernelGGL(k_psd_apply_wave<PSD_KSMALL>, dim3((unsigned)std::min<int64_t>(g.count, 4096)), dim3(64), 0,
-                         st, g, mode, delta, x, (const double*)nullptr, y);
-    else
-      hipLaunchKernelGGL(k_psd_apply_wave<PSD_KLARGE>, dim3((unsigned)std::min<int64_t>(g.count, 4096)), dim3(256), 0,
-                         st, g, mode, delta, x, (const double*)nullptr, y);
-  else
-    hipLaunchKernelGGL(k_cone_apply, dim3(cone_blocks(g)), dim3(CONE_BLOCK), 0, st, g, mode, delta, x, y);
-  HC_LAUNCH_CHECK();
-}
-
-__global__ __launch_bounds__(CONE_BLOCK) void k_cone_recover(SegDev g, const double* __restrict__ dsr, const double* __restrict__ dz,
-                               double* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < g.count) cone_apply_one(g, i, 0, 0.0, dz, dsr, out);
-}
-
-void cone_recover_ds(const SegDev& g, const double* dsrhs, const double* dz, double* out, hipStream_t st) {
-  if (g.count == 0) return;
-  if (soc_large(g.kind, g.dim))
-    lsoc_apply(g, 0, 0.0, dz, dsrhs, out, st);
-  else if (g.kind == HC_CONE_PSD)
-    if (g.k <= PSD_KSMALL)
-      hipLaunchKernelGGL(k_psd_apply_wave<PSD_KSMALL>, dim3((unsigned)std::min<int64_t>(g.count, 4096)), dim3(64), 0,
-                         st, g, 0, 0.0, dz, dsrhs, out);
-    else
-      hipLaunchKernelGGL(k_psd_apply_wave<PSD_KLARGE>, dim3((unsigned)std::min<int64_t>(g.count, 4096)), dim3(256), 0,
-                         st, g, 0, 0.0, dz, dsrhs, out);
-  else
-    hipLaunchKernelGGL(k_cone_recover, dim3(cone_blocks(g)), dim3(CONE_BLOCK), 0, st, g, dsrhs, dz, out);
-  HC_LAUNCH_CHECK();
 }
 
 bool lane_per_cone(const SegDev& g) {
   return g.count > 0 && g.kind != HC_CONE_PSD && !soc_large(g.kind, g.dim);
 }
 
-void cone_apply_all(const std::vector<SegDev>& segs, int mode, double delta, const double* x, const double* dsr,
-                    double* y, hipStream_t st) {
+// blocks a segment's rows take in the common launch
+static int seg_blocks(const SegDev& g) {
+  return (int)std::min<int64_t>(SEG_BLOCKS, ceil_div(lane_per_cone(g) ? g.count : g.count * g.dim, CONE_BLOCK));
+}
+int64_t cone_apply_parts(const std::vector<SegDev>& segs) {
+  int64_t n = 0;
+  for (const SegDev& g : segs) n += g.count > 0 ? seg_blocks(g) : 0;
+  return n;
+}
+
+void cone_apply_sys(const std::vector<SegDev>& segs, int mode, double delta, int epi, const ApplySys* sys, int ns,
+                    hipStream_t st) {
+  ApplySys2 ss{};
+  for (int r = 0; r < ns; ++r) ss.s[r] = sys[r];
+  const bool finish = epi == EPI_ADD || epi == EPI_RESID;   // PSD and large SOC rows still take the epilogue
+  for (const SegDev& g : segs) {
+    if (g.count == 0) continue;
+    if (soc_large(g.kind, g.dim)) {
+      for (int r = 0; r < ns; ++r) lsoc_apply(g, mode, delta, sys[r].x, epi == EPI_NEG ? sys[r].a : nullptr, sys[r].y, st);
+    } else if (g.kind == HC_CONE_PSD) {
+      const dim3 grid((unsigned)std::min<int64_t>(g.count, 4096), (unsigned)ns);
+      if (g.k <= PSD_KSMALL)
+        hipLaunchKernelGGL(k_psd_apply_wave<PSD_KSMALL>, grid, dim3(64), 0, st, g, mode, delta, epi, ss);
+      else
+        hipLaunchKernelGGL(k_psd_apply_wave<PSD_KLARGE>, grid, dim3(256), 0, st, g, mode, delta, epi, ss);
+      HC_LAUNCH_CHECK();
+    }
+  }
   SegTable tb{};
   int nb = 0;
   auto flush = [&]() {
     if (tb.nseg == 0) return;
     tb.first[tb.nseg] = nb;
-    hipLaunchKernelGGL(k_cone_apply_fused, dim3((unsigned)nb), dim3(CONE_BLOCK), 0, st, tb, mode, delta, x, dsr, y);
+    const dim3 grid((unsigned)nb, (unsigned)ns);
+    switch (epi) {
+      case EPI_PUT: hipLaunchKernelGGL(k_cone_apply_fused<EPI_PUT>, grid, dim3(CONE_BLOCK), 0, st, tb, mode, delta, ss); break;
+      case EPI_ADD: hipLaunchKernelGGL(k_cone_apply_fused<EPI_ADD>, grid, dim3(CONE_BLOCK), 0, st, tb, mode, delta, ss); break;
+      case EPI_RESID: hipLaunchKernelGGL(k_cone_apply_fused<EPI_RESID>, grid, dim3(CONE_BLOCK), 0, st, tb, mode, delta, ss); break;
+      default: hipLaunchKernelGGL(k_cone_apply_fused<EPI_NEG>, grid, dim3(CONE_BLOCK), 0, st, tb, mode, delta, ss);
+    }
     HC_LAUNCH_CHECK();
+    for (int r = 0; r < ns; ++r)
+      if (ss.s[r].pmax) ss.s[r].pmax += nb;
     tb.nseg = 0;
     nb = 0;
   };
   for (const SegDev& g : segs) {
     if (g.count == 0) continue;
-    if (!lane_per_cone(g)) {   // PSD and large SOC keep their own kernels
-      if (dsr) cone_recover_ds(g, dsr, x, y, st);
-      else cone_apply(g, mode, delta, x, y, st);
-      continue;
+    SegDev t = g;
+    if (!lane_per_cone(g)) {
+      if (!finish) continue;
+      t.kind = SEG_ROWS;
+      t.count = g.count * g.dim;
     }
     if (tb.nseg == FUSED_SEGS) flush();
-    tb.g[tb.nseg] = g;
+    tb.g[tb.nseg] = t;
     tb.first[tb.nseg] = nb;
     tb.nseg++;
-    nb += (int)ceil_div(g.count, CONE_BLOCK);
+    nb += seg_blocks(g);
   }
   flush();
+}
+
+void cone_apply_all(const std::vector<SegDev>& segs, int mode, double delta, const double* x, const double* dsr,
+                    double* y, hipStream_t st) {
+  const ApplySys s{x, y, dsr, nullptr, nullptr};
+  cone_apply_sys(segs, mode, delta, dsr ? EPI_NEG : EPI_PUT, &s, 1, st);
 }
 
 __global__ __launch_bounds__(CONE_BLOCK) void k_sym_scale_fused(SegTable tb, const double* __restrict__ s, const double* __restrict__ z,

@@ -24,6 +24,7 @@
 //     scale 1/max(1, mean column max of P, |Dq|_inf);
 //   * dual-infeasibility test multiplies by q'x.
 #include <array>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -64,6 +65,47 @@ struct Buf {   // bump allocator over one device block; `dry` only counts bytes
 };
 
 }  // namespace
+
+// Device time of one factorisation: an event pair on the stream it runs on, or
+// (the allocation-free call creates no events) host time with a wait.
+struct FactorClock {
+  hipEvent_t a = nullptr, b = nullptr;
+  bool events = true;
+  double t0 = 0, ms = 0;
+  static double now() {
+    return std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now().time_since_epoch()).count();
+  }
+  void start(hipStream_t st) {
+    if (!events) {
+      t0 = now();
+      return;
+    }
+    if (!a) {
+      HC_HIP(hipEventCreate(&a));
+      HC_HIP(hipEventCreate(&b));
+    }
+    HC_HIP(hipEventRecord(a, st));
+  }
+  void stop(hipStream_t st) {
+    if (events) {
+      HC_HIP(hipEventRecord(b, st));
+      return;
+    }
+    HC_HIP(hipStreamSynchronize(st));
+    ms = now() - t0;
+  }
+  double read_ms() {
+    if (!events) return ms;
+    float t = 0;
+    HC_HIP(hipEventSynchronize(b));
+    HC_HIP(hipEventElapsedTime(&t, a, b));
+    return t;
+  }
+  ~FactorClock() {
+    if (a) (void)hipEventDestroy(a);
+    if (b) (void)hipEventDestroy(b);
+  }
+};
 
 struct hc_solver {
   hc_settings st{};
@@ -182,6 +224,9 @@ struct hc_solver {
   int64_t npart = 0;                // capacity of the partial buffers (two reductions, or every segment's step partials)
   double* dpart = nullptr;          // reduction partials
   double* hpart = nullptr;          // pinned host copy
+  double* hmap = nullptr;           // device address of hpart (null: not mapped, values come by copy)
+  unsigned long long rb_seq = 0;    // last value collect() wrote to hpart's flag
+  double nb_const = 0;              // max(|q|, |b|), the constant system's right-hand side (scaled)
   bool own_stage = false;           // hpart/hmask allocated here (no caller staging)
   unsigned long long *dmask = nullptr, *hmask = nullptr;
   // iterate and work vectors
@@ -200,6 +245,8 @@ struct hc_solver {
   hc_info info{};
   int status = 0;
   double delta = 0;
+  bool px_zero = false;             // Px holds the zeros of a problem without P
+  FactorClock clock;                // the factorisation's time (info.factor_ms)
   double xPx_cache = 0;             // x'Px of the current iterate (from residuals)
   std::unique_ptr<Prof> prof;
   std::unique_ptr<Prof> cprof;      // events around the cone-layer launches (settings.profile)
@@ -1677,6 +1724,43 @@ Csr upload_csr(Buf& buf, const HostCsr& h, hipStream_t st) {
 // ===========================================================================
 // device-side building blocks of one iteration
 // ===========================================================================
+// hpart: combined values in [0, 32), the flag after them
+constexpr int RB_FLAG = 32;
+
+// Combines partials on the device and brings the values to the host.  Where
+// the staging is mapped, the kernel writes them there and the host watches the
+// flag behind them (no copy, no stream synchronisation); otherwise a copy.
+// The wait falls back to the stream's own after WATCH_US, and so reports a
+// device error.  (A copy with its synchronisation took 10 to 20 us of host
+// time; an iteration reads back about ten times.)
+constexpr double WATCH_US = 200.0;
+void fetch(hc_solver* S, const Collect& c, double* out) {
+  hipStream_t st = S->stream;
+  if (c.n == 0) return;
+  if (S->hmap) {
+    volatile unsigned long long* flag = (volatile unsigned long long*)(S->hpart + RB_FLAG);
+    const unsigned long long seq = ++S->rb_seq;
+    collect(c, S->hmap, (unsigned long long*)(S->hmap + RB_FLAG), seq, st);
+    const auto t0 = std::chrono::steady_clock::now();
+    int spins = 0;
+    while (*flag != seq) {
+      __builtin_ia32_pause();
+      if (++spins % 256 == 0 &&
+          std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count() > WATCH_US) {
+        HC_HIP(hipStreamSynchronize(st));
+        break;
+      }
+    }
+    std::atomic_thread_fence(std::memory_order_acquire);
+  } else {
+    double* dev = (double*)S->dmask;   // not in use between two step trials
+    collect(c, dev, nullptr, 0, st);
+    HC_HIP(hipMemcpyAsync(S->hpart, dev, c.n * sizeof(double), hipMemcpyDeviceToHost, st));
+    HC_HIP(hipStreamSynchronize(st));
+  }
+  for (int i = 0; i < c.n; ++i) out[i] = S->hpart[i];
+}
+
 struct Red {
   hc_solver* S;
   RedOps ops{};
@@ -1691,70 +1775,25 @@ struct Red {
     ops.op[ops.nops] = RedOp{divide ? RED_MAX_DIV : RED_MAX_MUL, x, y, yc, w};
     return ops.nops++;
   }
-  // launch into dpart + off; returns the partials it will write
-  int64_t launch(int64_t off) {
-    if (n == 0 || ops.nops == 0) return 0;
-    nblk = reduce_launch(n, ops, S->dpart + off, S->stream);
-    base = off;
+  // launches the reduction into dpart + off and lists its partials; returns how many there are
+  int64_t launch(int64_t off, Collect& c) {
+    if (n == 0) {   // nothing to reduce: zeros
+      for (int o = 0; o < ops.nops; ++o) c.add(S->dpart, 0, 1, ops.op[o].kind == RED_DOT ? COLLECT_SUM : COLLECT_MAX);
+      return 0;
+    }
+    const int nblk = reduce_launch(n, ops, S->dpart + off, S->stream);
+    for (int o = 0; o < ops.nops; ++o)
+      c.add(S->dpart + off + o, nblk, ops.nops, ops.op[o].kind == RED_DOT ? COLLECT_SUM : COLLECT_MAX);
     return (int64_t)nblk * ops.nops;
   }
-  // combine this reduction's partials (already copied to hpart)
-  std::vector<double> collect() const {
-    std::vector<double> out(ops.nops, 0.0);
-    if (n == 0 || ops.nops == 0) return out;
-    for (int o = 0; o < ops.nops; ++o) {
-      double acc = 0.0;
-      for (int bk = 0; bk < nblk; ++bk) {
-        const double v = S->hpart[base + (size_t)bk * ops.nops + o];
-        if (ops.op[o].kind == RED_DOT) acc += v;
-        else acc = (std::isnan(v) || std::isnan(acc)) ? NAN : std::max(acc, v);
-      }
-      out[o] = acc;
-    }
+  std::vector<double> run() {
+    Collect c;
+    launch(0, c);
+    std::vector<double> out(std::max(1, c.n), 0.0);
+    fetch(S, c, out.data());
     return out;
   }
-  std::vector<double> run() {
-    const int64_t cnt = launch(0);
-    if (cnt) {
-      HC_HIP(hipMemcpyAsync(S->hpart, S->dpart, cnt * sizeof(double), hipMemcpyDeviceToHost, S->stream));
-      HC_HIP(hipStreamSynchronize(S->stream));
-    }
-    return collect();
-  }
-  int nblk = 0;
-  int64_t base = 0;
 };
-
-// two reductions (over lengths n and m) with one host round trip
-void run_pair(Red& a, Red& b, std::vector<double>& va, std::vector<double>& vb) {
-  const int64_t ca = a.launch(0);
-  const int64_t cb = b.launch(ca);
-  if (ca + cb) {
-    HC_HIP(hipMemcpyAsync(a.S->hpart, a.S->dpart, (ca + cb) * sizeof(double), hipMemcpyDeviceToHost, a.S->stream));
-    HC_HIP(hipStreamSynchronize(a.S->stream));
-  }
-  va = a.collect();
-  vb = b.collect();
-}
-
-// max(|x|_inf, |y|_inf) for vectors of lengths n and m, one host round trip
-double maxabs2(hc_solver* S, const double* x, int64_t n, const double* y, int64_t m) {
-  RedOps ox{}, oy{};
-  ox.nops = oy.nops = 1;
-  ox.op[0] = RedOp{RED_MAX_MUL, x, nullptr, 0.0, nullptr};
-  oy.op[0] = RedOp{RED_MAX_MUL, y, nullptr, 0.0, nullptr};
-  const int na = n > 0 ? reduce_launch(n, ox, S->dpart, S->stream) : 0;
-  const int nb = m > 0 ? reduce_launch(m, oy, S->dpart + na, S->stream) : 0;
-  if (na + nb == 0) return 0.0;
-  HC_HIP(hipMemcpyAsync(S->hpart, S->dpart, (size_t)(na + nb) * sizeof(double), hipMemcpyDeviceToHost, S->stream));
-  HC_HIP(hipStreamSynchronize(S->stream));
-  double acc = 0.0;
-  for (int i = 0; i < na + nb; ++i) {
-    const double v = S->hpart[i];
-    acc = (std::isnan(v) || std::isnan(acc)) ? NAN : std::max(acc, v);
-  }
-  return acc;
-}
 
 void A_mul(hc_solver* S, const double* x, double* y, double alpha, double beta) {
   spmv(S->dA, x, y, alpha, beta, S->stream);
@@ -1790,8 +1829,8 @@ double cone_op_bytes(const SegDev& g, ConeOp op) {
 struct ConeProbe {
   hc_solver* S;
   // which: 0 every segment, 1 the symmetric ones, 2 exp/pow
-  // (only: that segment alone)
-  explicit ConeProbe(hc_solver* S_, ConeOp op, int which = 0, const SegDev* only = nullptr) : S(S_) {
+  // (only: that segment alone); vectors: applied to side by side
+  explicit ConeProbe(hc_solver* S_, ConeOp op, int which = 0, const SegDev* only = nullptr, int vectors = 1) : S(S_) {
     if (!S->st.profile || !S->cprof) return;
     HC_HIP(hipEventRecord(S->cprof->next(), S->stream));
     for (const SegDev& g : S->sdev) {
@@ -1799,7 +1838,7 @@ struct ConeProbe {
       if ((which == 1 && ns) || (which == 2 && !ns) || (only && only != &g)) continue;
       const double b = cone_op_bytes(g, op);
       if (b > 0.0) {
-        S->info.cone_bytes += b;
+        S->info.cone_bytes += vectors * b;
         S->info.cone_launches++;
       }
     }
@@ -1846,15 +1885,18 @@ Aux* lookahead(hc_solver* S) {
 // -(H_c + delta I) are inverted exactly in FP64), so the proportional term
 // takes max|S_ii| of the last FP32-factored S; `fp64` redoes the whole
 // factorisation with the FP64 regularisation (the refinement fallback).
-void factor(hc_solver* S, bool fp64 = false) {
+// hmax: max |H_ii| where the caller has it (< 0: reduced here).
+void factor(hc_solver* S, bool fp64 = false, double hmax = -1.0) {
   hipStream_t st = S->stream;
   const bool low = S->mixed && !fp64;
   if (low) {
     S->delta = S->st.static_reg + S->st.dyn_reg * std::max(S->maxPdiag, S->sdiag_max);
   } else {
-    Red r(S, S->m);
-    r.maxabs(S->dhdiag);
-    const double hmax = r.run()[0];
+    if (!(hmax >= 0.0)) {
+      Red r(S, S->m);
+      r.maxabs(S->dhdiag);
+      hmax = r.run()[0];
+    }
     const double ds = S->mixed ? 1e-8 : S->st.static_reg;
     const double dd = S->mixed ? std::ldexp(1.0, -104) : S->st.dyn_reg;
     S->delta = ds + dd * std::max(S->maxPdiag, hmax);
@@ -2019,9 +2061,18 @@ void solve_reg(hc_solver* S, const double* r1, const double* r2, double* x, doub
   H_apply(S, 1, S->w1, z);
 }
 
-// iterative refinement against the unregularised K; result in (xo, zo)
-int64_t kkt_solve_once(hc_solver* S, const double* r1, const double* r2, double* xo, double* zo, double* best_out,
-                       double* nb_out);
+// y = a x + b c over n entries
+RowJob lin_job(int64_t n, double a, const double* x, double b, const double* c, double* y) {
+  RowJob j;
+  j.nrows = (int32_t)n;
+  j.alpha = a;
+  j.x = x;
+  j.beta = b;
+  j.c = c;
+  j.y = y;
+  return j;
+}
+
 // the residual at which the refinement stops: the fixed tolerances, or (with
 // ir_mu_frac) a fraction of the iteration's mu relative to the right-hand side
 double ir_target(const hc_solver* S, double nb) {
@@ -2029,113 +2080,65 @@ double ir_target(const hc_solver* S, double nb) {
                   S->st.ir_mu_frac * std::min(S->info.mu, 1.0) * (1.0 + nb));
 }
 
-int64_t kkt_solve(hc_solver* S, const double* r1, const double* r2, double* xo, double* zo) {
-  double best = 0, nb = 0;
-  int64_t k = kkt_solve_once(S, r1, r2, xo, zo, &best, &nb);
-  if (S->mixed && !S->use64 && !(best <= std::max(1e-6 * (1.0 + nb), ir_target(S, nb)))) {
-    fallback_fp64(S);
-    k += kkt_solve_once(S, r1, r2, xo, zo, &best, &nb);
-  }
-  return k;
-}
-
-int64_t kkt_solve_once(hc_solver* S, const double* r1, const double* r2, double* xo, double* zo, double* best_out,
-                       double* nb_out) {
-  hipStream_t st = S->stream;
-  const int64_t n = S->n, m = S->m;
-  double nb;
-  nb = maxabs2(S, r1, n, r2, m);
-  double* x = S->irx;
-  double* z = S->irz;
-  double* xn = S->irxn;
-  double* zn = S->irzn;
-  vfill(n, 0.0, x, st);
-  vfill(m, 0.0, z, st);
-  vcopy(n, r1, S->irrx, st);
-  vcopy(m, r2, S->irrz, st);
-  double best = nb, rnorm = nb;
-  const double target = ir_target(S, nb);
-  bool have_best = false;
-  int64_t solves = 0;
-  for (int it = 0; it <= S->st.ir_max; ++it) {
-    solve_reg(S, S->irrx, S->irrz, S->kx, S->kz);   // correction in kx, kz
-    vlin3(n, 1.0, x, 1.0, S->kx, 0.0, nullptr, xn, st);
-    vlin3(m, 1.0, z, 1.0, S->kz, 0.0, nullptr, zn, st);
-    ++solves;
-    // residual r - K [xn; zn] with the unregularised K
-    P_mul(S, xn, S->kx, 1.0, 0.0);
-    At_mul(S, zn, S->kx, 1.0, 1.0);
-    A_mul(S, xn, S->kz, 1.0, 0.0);
-    H_apply(S, 0, zn, S->t2);
-    vaxpby(m, -1.0, S->t2, 1.0, S->kz, st);         // kz = A xn - H zn
-    vlin3(n, 1.0, r1, -1.0, S->kx, 0.0, nullptr, S->kx, st);
-    vlin3(m, 1.0, r2, -1.0, S->kz, 0.0, nullptr, S->kz, st);
-    const double rn = maxabs2(S, S->kx, n, S->kz, m);
-    if (rn < best || !have_best) {
-      if (rn < best) {
-        vcopy(n, xn, S->irbx, st);
-        vcopy(m, zn, S->irbz, st);
-        best = rn;
-        have_best = true;
-      }
-    }
-    if (rn <= target) break;
-    if (it > 0 && rn > 0.5 * rnorm) break;
-    std::swap(x, xn);
-    std::swap(z, zn);
-    std::swap(S->irrx, S->kx);
-    std::swap(S->irrz, S->kz);
-    rnorm = rn;
-  }
-  if (have_best) {
-    vcopy(n, S->irbx, xo, st);
-    vcopy(m, S->irbz, zo, st);
-  } else {
-    vfill(n, 0.0, xo, st);
-    vfill(m, 0.0, zo, st);
-  }
-  S->irx = x;
-  S->irz = z;
-  S->irxn = xn;
-  S->irzn = zn;
-  S->info.ir_solves += solves;
-  *best_out = have_best ? best : NAN;
-  *nb_out = nb;
-  if (S->st.verbose >= 2) {
-    std::printf("      kkt solve: |rhs| %.3e best residual %.3e (%s) solves %lld\n", nb, have_best ? best : NAN,
-                S->mixed && !S->use64 ? "fp32 factor" : "fp64 factor", (long long)solves);
-    std::fflush(stdout);
-  }
-  return solves;
-}
-
-// Two systems K [x; z] = [r1; r2] refined in lockstep (kkt_solve_once's
-// rule for each): every step's two Schur solves share one pass of the dense
-// triangular solves; a system leaves the loop under its own stopping test.
-// Results in (xa, za) and (xb, zb); the mixed mode's FP64 fallback as in
-// kkt_solve, per system.
+// One system K [x; z] = [r1; r2] under refinement.  The iterate, the next one
+// and the best one take turns in three buffers per vector; at the end the best
+// one changes places with *xo, *zo (so nothing is copied).
 struct IRSys {
   const double *r1, *r2;
-  double *xo, *zo, *x, *z, *xn, *zn, *bx, *bz, *rx, *rz, *kx, *kz, *u;
-  double nb = 0, best = 0, rnorm = 0, target = 0;
-  bool have_best = false, done = false;
+  double **xo, **zo;
+  double nb;                       // max |r1|, |r2| (< 0: reduced at the start)
+  double *xb[3], *zb[3];           // x, z buffers
+  double *rxb, *rzb;               // residual
+  double *kx, *u, *t, *w;          // correction, Schur right-hand side, M rz, A x
+  const double *rx = nullptr, *rz = nullptr;   // current residual (r1, r2 at first)
+  double best = 0, rnorm = 0, target = 0;
+  int cur = -1, bst = -1;          // -1: zero, none
+  bool done = false;
+  int next() const { return cur != 0 && bst != 0 ? 0 : cur != 1 && bst != 1 ? 1 : 2; }
 };
-int64_t kkt_solve_pair(hc_solver* S, const double* r1a, const double* r2a, double* xa, double* za, const double* r1b,
-                       const double* r2b, double* xb, double* zb) {
+IRSys ir_first(hc_solver* S, const double* r1, const double* r2, double** xo, double** zo, double nb = -1.0) {
+  return IRSys{r1, r2, xo, zo, nb, {S->irx, S->irxn, S->irbx}, {S->irz, S->irzn, S->irbz}, S->irrx, S->irrz,
+               S->kx, S->u1, S->t1, S->w1};
+}
+IRSys ir_second(hc_solver* S, const double* r1, const double* r2, double** xo, double** zo, double nb = -1.0) {
+  return IRSys{r1, r2, xo, zo, nb, {S->jrx, S->jrxn, S->jrbx}, {S->jrz, S->jrzn, S->jrbz}, S->jrrx, S->jrrz,
+               S->jkx, S->u1b, S->kz, S->jkz};
+}
+
+// Iterative refinement against the unregularised K of one system or of two in
+// lockstep: each step's Schur solves share one pass of the triangular solves
+// and its products, cone applications and sums go side by side in common
+// launches (a step is eight of them, and one read-back of the residual norms);
+// a system leaves the loop under its own stopping test.
+int64_t refine(hc_solver* S, IRSys* sy, int ns) {
   hipStream_t st = S->stream;
   const int64_t n = S->n, m = S->m;
-  const bool low = S->mixed && !S->use64;
-  IRSys sy[2];
-  sy[0] = IRSys{r1a, r2a, xa, za, S->irx, S->irz, S->irxn, S->irzn, S->irbx, S->irbz, S->irrx, S->irrz, S->kx,
-                S->kz, S->u1};
-  sy[1] = IRSys{r1b, r2b, xb, zb, S->jrx, S->jrz, S->jrxn, S->jrzn, S->jrbx, S->jrbz, S->jrrx, S->jrrz, S->jkx,
-                S->jkz, S->u1b};
-  for (IRSys& y : sy) {
-    y.nb = maxabs2(S, y.r1, n, y.r2, m);
-    vfill(n, 0.0, y.x, st);
-    vfill(m, 0.0, y.z, st);
-    vcopy(n, y.r1, y.rx, st);
-    vcopy(m, y.r2, y.rz, st);
+  const int nd = (int)S->drows.size();
+  const int64_t ncol = S->leaves ? S->nt : n;                       // columns the dense rows are stored on
+  const int32_t* dcols = S->leaves ? S->cm.tcols : nullptr;
+  {
+    Collect c;
+    int64_t off = 0;
+    for (int r = 0; r < ns; ++r)
+      if (sy[r].nb < 0) {
+        Red a(S, n), b(S, m);
+        a.maxabs(sy[r].r1);
+        b.maxabs(sy[r].r2);
+        off += a.launch(off, c);
+        off += b.launch(off, c);
+      }
+    double v[4];
+    fetch(S, c, v);
+    for (int r = 0, k = 0; r < ns; ++r)
+      if (sy[r].nb < 0) {
+        sy[r].nb = std::isnan(v[k]) || std::isnan(v[k + 1]) ? NAN : std::max(v[k], v[k + 1]);
+        k += 2;
+      }
+  }
+  for (int r = 0; r < ns; ++r) {
+    IRSys& y = sy[r];
+    y.rx = y.r1;
+    y.rz = y.r2;
     y.best = y.rnorm = y.nb;
     y.target = ir_target(S, y.nb);
   }
@@ -2143,107 +2146,231 @@ int64_t kkt_solve_pair(hc_solver* S, const double* r1a, const double* r2a, doubl
   for (int it = 0; it <= S->st.ir_max; ++it) {
     IRSys* act[2];
     int k = 0;
-    for (IRSys& y : sy)
-      if (!y.done) act[k++] = &y;
+    for (int r = 0; r < ns; ++r)
+      if (!sy[r].done) act[k++] = &sy[r];
     if (k == 0) break;
+    ApplySys as[2];
     const double* us[2];
     double* xs[2];
-    for (int r = 0; r < k; ++r) {   // Schur right-hand side r1 + A' M r2 of the residual
-      IRSys& y = *act[r];
-      H_apply(S, 1, y.rz, S->t1);
-      vcopy(n, y.rx, y.u, st);
-      At_mul(S, S->t1, y.u, 1.0, 1.0);
-      us[r] = y.u;
-      xs[r] = y.kx;
+    // Schur right-hand side u = r1 + A' M r2 of the residual
+    for (int r = 0; r < k; ++r) as[r] = ApplySys{act[r]->rz, act[r]->t, nullptr, nullptr, nullptr};
+    {
+      ConeProbe probe(S, CO_APPLY, 0, nullptr, k);
+      cone_apply_sys(S->sdev, 1, S->delta, EPI_PUT, as, k, st);
     }
-    schur_solve_n(S, k, us, xs);
+    RowJobs ju;
     for (int r = 0; r < k; ++r) {
       IRSys& y = *act[r];
-      A_mul(S, y.kx, S->w1, 1.0, 0.0);           // correction z = M (A x - r2)
-      vaxpby(m, -1.0, y.rz, 1.0, S->w1, st);
-      H_apply(S, 1, S->w1, y.kz);
-      vlin3(n, 1.0, y.x, 1.0, y.kx, 0.0, nullptr, y.xn, st);
-      vlin3(m, 1.0, y.z, 1.0, y.kz, 0.0, nullptr, y.zn, st);
-      ++solves;
-      P_mul(S, y.xn, y.kx, 1.0, 0.0);            // residual with the unregularised K
-      At_mul(S, y.zn, y.kx, 1.0, 1.0);
-      A_mul(S, y.xn, y.kz, 1.0, 0.0);
-      H_apply(S, 0, y.zn, S->t2);
-      vaxpby(m, -1.0, S->t2, 1.0, y.kz, st);
-      vlin3(n, 1.0, y.r1, -1.0, y.kx, 0.0, nullptr, y.kx, st);
-      vlin3(m, 1.0, y.r2, -1.0, y.kz, 0.0, nullptr, y.kz, st);
-      const double rn = maxabs2(S, y.kx, n, y.kz, m);
+      RowJob j(ROW_MUL, S->dAt, y.t, y.u);
+      j.c = y.rx;
+      j.beta = 1.0;
+      ju.add(j);
+      us[r] = y.u;
+      xs[r] = y.cur < 0 ? y.xb[y.next()] : y.kx;
+    }
+    row_jobs(ju, st);
+    for (int r = 0; r < k && nd; ++r)
+      dense_rows_gemv_t(nd, ncol, S->dAd, S->ddrows, dcols, act[r]->t, act[r]->u, 1.0, S->dDrT, st);
+    schur_solve_n(S, k, us, xs);
+    // correction's z = M (A x - r2), on top of the iterate
+    RowJobs jw;
+    for (int r = 0; r < k; ++r) {
+      IRSys& y = *act[r];
+      RowJob j(ROW_MUL, S->dA, xs[r], y.w);
+      if (!nd) {
+        j.c = y.rz;
+        j.beta = -1.0;
+      }
+      jw.add(j);
+      if (y.cur >= 0) jw.add(lin_job(n, 1.0, y.xb[y.cur], 1.0, y.kx, y.xb[y.next()]));
+    }
+    row_jobs(jw, st);
+    if (nd) {   // the dense rows' part, then - r2
+      RowJobs js;
+      for (int r = 0; r < k; ++r) {
+        dense_rows_gemv(nd, ncol, S->dAd, S->ddrows, dcols, xs[r], act[r]->w, 1.0, st);
+        js.add(lin_job(m, -1.0, act[r]->rz, 1.0, act[r]->w, act[r]->w));
+      }
+      row_jobs(js, st);
+    }
+    const bool first = act[0]->cur < 0;   // of both, if there are two
+    for (int r = 0; r < k; ++r) {
+      IRSys& y = *act[r];
+      as[r] = ApplySys{y.w, y.zb[y.next()], first ? nullptr : y.zb[y.cur], nullptr, nullptr};
+    }
+    {
+      ConeProbe probe(S, CO_APPLY, 0, nullptr, k);
+      cone_apply_sys(S->sdev, 1, S->delta, first ? EPI_PUT : EPI_ADD, as, k, st);
+    }
+    solves += k;
+    // residual r - K [x; z] with the unregularised K, and its norm
+    Collect c;
+    RowJobs jp, jr, jd;
+    int64_t off = 0;
+    for (int r = 0; r < k; ++r) {
+      IRSys& y = *act[r];
+      double *xn = y.xb[y.next()], *zn = y.zb[y.next()];
+      RowJob j(nd ? ROW_SUM : ROW_RESID, S->dAt, zn, y.rxb);
+      j.c = y.r1;
+      if (S->dP.nnz > 0 && RowJob::pairs(S->dAt, S->dP)) {
+        j.second(S->dP, xn);
+      } else if (S->dP.nnz > 0) {
+        jp.add(RowJob(ROW_MUL, S->dP, xn, y.kx));
+        j.addp = y.kx;
+      }
+      RowJob d = lin_job(n, -1.0, y.rxb, 1.0, y.r1, y.rxb);   // with dense rows: r1 - (P x + A' z) once they are in
+      RowJob& fin = nd ? d : j;
+      fin.pmax = S->dpart + off;
+      c.add(fin.pmax, fin.blocks(), 1, COLLECT_MAX);
+      off += fin.blocks();
+      if (nd) jd.add(d);
+      jr.add(j);
+      jr.add(RowJob(ROW_MUL, S->dA, xn, y.w));
+    }
+    row_jobs(jp, st);
+    row_jobs(jr, st);
+    for (int r = 0; r < k && nd; ++r) {
+      IRSys& y = *act[r];
+      dense_rows_gemv_t(nd, ncol, S->dAd, S->ddrows, dcols, y.zb[y.next()], y.rxb, 1.0, S->dDrT, st);
+      dense_rows_gemv(nd, ncol, S->dAd, S->ddrows, dcols, y.xb[y.next()], y.w, 1.0, st);
+    }
+    row_jobs(jd, st);
+    const int64_t zparts = cone_apply_parts(S->sdev);
+    for (int r = 0; r < k; ++r) {
+      IRSys& y = *act[r];
+      as[r] = ApplySys{y.zb[y.next()], y.rzb, y.w, y.r2, S->dpart + off};
+      c.add(S->dpart + off, zparts, 1, COLLECT_MAX);
+      off += zparts;
+    }
+    {
+      ConeProbe probe(S, CO_APPLY, 0, nullptr, k);
+      cone_apply_sys(S->sdev, 0, S->delta, EPI_RESID, as, k, st);
+    }
+    double v[4];
+    fetch(S, c, v);
+    for (int r = 0; r < k; ++r) {
+      IRSys& y = *act[r];
+      const double a = v[r], b = v[k + r];
+      const double rn = std::isnan(a) || std::isnan(b) ? NAN : std::max(a, b);
+      const int nx = y.next();
       if (rn < y.best) {
-        vcopy(n, y.xn, y.bx, st);
-        vcopy(m, y.zn, y.bz, st);
         y.best = rn;
-        y.have_best = true;
+        y.bst = nx;
       }
       if (rn <= y.target || (it > 0 && rn > 0.5 * y.rnorm)) {
         y.done = true;
         continue;
       }
-      std::swap(y.x, y.xn);
-      std::swap(y.z, y.zn);
-      std::swap(y.rx, y.kx);
-      std::swap(y.rz, y.kz);
+      y.cur = nx;
+      y.rx = y.rxb;
+      y.rz = y.rzb;
       y.rnorm = rn;
     }
   }
-  for (IRSys& y : sy) {
-    if (y.have_best) {
-      vcopy(n, y.bx, y.xo, st);
-      vcopy(m, y.bz, y.zo, st);
+  for (int r = 0; r < ns; ++r) {
+    IRSys& y = sy[r];
+    if (y.bst >= 0) {
+      std::swap(*y.xo, y.xb[y.bst]);
+      std::swap(*y.zo, y.zb[y.bst]);
     } else {
-      vfill(n, 0.0, y.xo, st);
-      vfill(m, 0.0, y.zo, st);
+      vfill(n, 0.0, *y.xo, st);
+      vfill(m, 0.0, *y.zo, st);
     }
   }
-  S->irx = sy[0].x, S->irz = sy[0].z, S->irxn = sy[0].xn, S->irzn = sy[0].zn;
-  S->irrx = sy[0].rx, S->irrz = sy[0].rz, S->kx = sy[0].kx, S->kz = sy[0].kz;
-  S->jrx = sy[1].x, S->jrz = sy[1].z, S->jrxn = sy[1].xn, S->jrzn = sy[1].zn;
-  S->jrrx = sy[1].rx, S->jrrz = sy[1].rz, S->jkx = sy[1].kx, S->jkz = sy[1].kz;
-  S->info.ir_solves += solves;
-  if (S->st.verbose >= 2) {
-    std::printf("      kkt solve pair: |rhs| %.3e / %.3e best residual %.3e / %.3e solves %lld\n", sy[0].nb, sy[1].nb,
-                sy[0].have_best ? sy[0].best : NAN, sy[1].have_best ? sy[1].best : NAN, (long long)solves);
-    std::fflush(stdout);
+  S->irx = sy[0].xb[0], S->irxn = sy[0].xb[1], S->irbx = sy[0].xb[2];
+  S->irz = sy[0].zb[0], S->irzn = sy[0].zb[1], S->irbz = sy[0].zb[2];
+  if (ns > 1) {
+    S->jrx = sy[1].xb[0], S->jrxn = sy[1].xb[1], S->jrbx = sy[1].xb[2];
+    S->jrz = sy[1].zb[0], S->jrzn = sy[1].zb[1], S->jrbz = sy[1].zb[2];
   }
-  if (low)
-    for (IRSys& y : sy) {   // the mixed mode's fallback, per system
-      if (y.have_best && y.best <= std::max(1e-6 * (1.0 + y.nb), ir_target(S, y.nb))) continue;
-      if (!S->use64) fallback_fp64(S);
-      double best = 0, nb = 0;
-      solves += kkt_solve_once(S, y.r1, y.r2, y.xo, y.zo, &best, &nb);
+  S->info.ir_solves += solves;
+  if (S->st.verbose >= 2)
+    for (int r = 0; r < ns; ++r) {
+      std::printf("      kkt solve: |rhs| %.3e best residual %.3e (%s) solves %lld\n", sy[r].nb,
+                  sy[r].bst >= 0 ? sy[r].best : NAN, S->mixed && !S->use64 ? "fp32 factor" : "fp64 factor",
+                  (long long)solves);
+      std::fflush(stdout);
     }
   return solves;
 }
 
+// the refined solution is good enough, or the mixed mode's factor has to be
+// redone in FP64
+bool needs_fp64(const hc_solver* S, const IRSys& y) {
+  return !(y.bst >= 0 && y.best <= std::max(1e-6 * (1.0 + y.nb), ir_target(S, y.nb)));
+}
+
+// *nb_out: max |r1|, |r2|
+int64_t kkt_solve(hc_solver* S, const double* r1, const double* r2, double** xo, double** zo,
+                  double* nb_out = nullptr) {
+  const bool low = S->mixed && !S->use64;
+  IRSys y = ir_first(S, r1, r2, xo, zo);
+  int64_t k = refine(S, &y, 1);
+  if (nb_out) *nb_out = y.nb;
+  if (low && needs_fp64(S, y)) {
+    fallback_fp64(S);
+    y = ir_first(S, r1, r2, xo, zo, y.nb);
+    k += refine(S, &y, 1);
+  }
+  return k;
+}
+
+// two systems refined in lockstep; the mixed mode's fallback per system
+int64_t kkt_solve_pair(hc_solver* S, IRSys a, IRSys b) {
+  const bool low = S->mixed && !S->use64;
+  IRSys sy[2] = {a, b};
+  int64_t k = refine(S, sy, 2);
+  if (low)
+    for (IRSys& y : sy) {
+      if (!needs_fp64(S, y)) continue;
+      if (!S->use64) fallback_fp64(S);
+      y = ir_first(S, y.r1, y.r2, y.xo, y.zo, y.nb);
+      k += refine(S, &y, 1);
+    }
+  return k;
+}
+
 struct Resid {
   double xPx, qx, bz, sz, rd_n, rp_n, x_n, s_n, z_n, atz_n, px_n, axs_n;
+  double nb;   // of the affine system's right-hand side (r1, r2)
 };
 
-// Px, Ax, A'z, r_d and r_p vectors and all norms of the termination tests
+// Px, Ax, A'z, the residual vectors, the affine system's right-hand side
+// r1 = gx = -rd, r2 = -(gz - s) = rp + s and all norms of the termination tests
 Resid residuals(hc_solver* S) {
   hipStream_t st = S->stream;
   const int64_t n = S->n, m = S->m;
-  P_mul(S, S->x, S->Px, 1.0, 0.0);
-  A_mul(S, S->x, S->Ax, 1.0, 0.0);
-  At_mul(S, S->z, S->Atz, 1.0, 0.0);
-  vlin3(n, 1.0, S->Px, 1.0, S->Atz, S->tau, S->dq, S->rdv, st);        // P x + A'z + q tau
-  vlin3(m, -1.0, S->Ax, -1.0, S->s, S->tau, S->db, S->rpv, st);        // -A x - s + b tau
-  Red rn(S, n), rm(S, m);
-  const int i_xPx = rn.dot(S->x, S->Px), i_qx = rn.dot(S->dq, S->x), i_rd = rn.maxabs(S->rdv, S->dD, true),
-            i_x = rn.maxabs(S->x, S->dD, false), i_atz = rn.maxabs(S->Atz, S->dD, true),
-            i_px = rn.maxabs(S->Px, S->dD, true);
-  const int i_bz = rm.dot(S->db, S->z), i_sz = rm.dot(S->s, S->z), i_rp = rm.maxabs(S->rpv, S->dE, true),
-            i_s = rm.maxabs(S->s, S->dE, true), i_z = rm.maxabs(S->z, S->dE, false),
-            i_axs = rm.maxabs(S->Ax, S->dE, true, S->s, 1.0);
-  std::vector<double> a, b;
-  run_pair(rn, rm, a, b);
+  const int nd = (int)S->drows.size();
+  RowJobs j;
+  if (S->dP.nnz > 0) j.add(RowJob(ROW_MUL, S->dP, S->x, S->Px));
+  else if (!S->px_zero) {   // no P: Px stays zero
+    vfill(n, 0.0, S->Px, st);
+    S->px_zero = true;
+  }
+  j.add(RowJob(ROW_MUL, S->dA, S->x, S->Ax));
+  j.add(RowJob(ROW_MUL, S->dAt, S->z, S->Atz));
+  row_jobs(j, st);
+  if (nd) {
+    const int64_t ncol = S->leaves ? S->nt : n;
+    const int32_t* dcols = S->leaves ? S->cm.tcols : nullptr;
+    dense_rows_gemv(nd, ncol, S->dAd, S->ddrows, dcols, S->x, S->Ax, 1.0, st);
+    dense_rows_gemv_t(nd, ncol, S->dAd, S->ddrows, dcols, S->z, S->Atz, 1.0, S->dDrT, st);
+  }
+  ResidArgs a{n, m, S->Px, S->Atz, S->dq, S->x, S->dD, S->rdv, S->r1, S->Ax, S->s, S->db, S->z, S->dE, S->rpv, S->r2,
+              S->tau};
+  int nbn = 0, nbm = 0;
+  resid_launch(a, S->dpart, &nbn, &nbm, st);
+  Collect c;
+  for (int side = 0; side < 2; ++side)
+    for (int o = 0; o < RESID_VALS; ++o)
+      c.add(S->dpart + (side ? (int64_t)nbn * 8 : 0) + o, side ? nbm : nbn, 8, o < 2 ? COLLECT_SUM : COLLECT_MAX);
+  double v[2 * RESID_VALS];
+  fetch(S, c, v);
+  const double* w = v + RESID_VALS;
   Resid R;
-  R.xPx = a[i_xPx]; R.qx = a[i_qx]; R.rd_n = a[i_rd]; R.x_n = a[i_x]; R.atz_n = a[i_atz]; R.px_n = a[i_px];
-  R.bz = b[i_bz]; R.sz = b[i_sz]; R.rp_n = b[i_rp]; R.s_n = b[i_s]; R.z_n = b[i_z]; R.axs_n = b[i_axs];
+  R.xPx = v[0]; R.qx = v[1]; R.rd_n = v[2]; R.x_n = v[3]; R.atz_n = v[4]; R.px_n = v[5];
+  R.bz = w[0]; R.sz = w[1]; R.rp_n = w[2]; R.s_n = w[3]; R.z_n = w[4]; R.axs_n = w[5];
+  R.nb = std::isnan(v[6]) || std::isnan(w[6]) ? NAN : std::max(v[6], w[6]);
   return R;
 }
 
@@ -2269,16 +2396,25 @@ int check(hc_solver* S, const Resid& R) {
   return 0;
 }
 
-void scale_all(hc_solver* S, double mu, bool force_dual, int* pd_count) {
-  vfill(1, 0.0, (double*)S->dpd, S->stream);   // both counters (fill kernels, not memsets, throughout)
+// the cone scalings; returns max |H_ii| (-1 where the FP64 regularisation
+// does not ask for it), *pd_count the exp/pow cones on the primal-dual scaling
+double scale_all(hc_solver* S, double mu, bool force_dual, int* pd_count) {
+  if (S->has_nonsym) vfill(1, 0.0, (double*)S->dpd, S->stream);   // both counters (fill kernels, not memsets, throughout)
   {
     ConeProbe probe(S, CO_SCALE);
     cone_scale_all(S->sdev, S->s, S->z, mu, force_dual ? 1 : 0, S->dhdiag, S->dpd, S->stream);
   }
-  int h = 0;
-  HC_HIP(hipMemcpyAsync(&h, S->dpd, sizeof(int), hipMemcpyDeviceToHost, S->stream));
-  HC_HIP(hipStreamSynchronize(S->stream));
-  *pd_count = h;
+  Collect c;
+  if (!S->mixed) {
+    Red r(S, S->m);
+    r.maxabs(S->dhdiag);
+    r.launch(0, c);
+  }
+  if (S->has_nonsym) c.add((const double*)S->dpd, 1, 1, COLLECT_INT);
+  double v[2] = {0.0, 0.0};
+  fetch(S, c, v);
+  *pd_count = S->has_nonsym ? (int)v[c.n - 1] : 0;
+  return S->mixed ? -1.0 : v[0];
 }
 
 struct Dir {
@@ -2291,22 +2427,24 @@ Dir direction(hc_solver* S, const double* r1, const double* r2, double dtau_rhs,
               const double* ds_rhs, double* dxo, double* dzo, double* dso) {
   hipStream_t st = S->stream;
   const int64_t n = S->n, m = S->m;
-  if (r1) kkt_solve(S, r1, r2, S->x1, S->z1);
+  if (r1) kkt_solve(S, r1, r2, &S->x1, &S->z1);
   // w = 2 P xi + q with xi = x / tau:  w'x1, w'x2 ; b'z1, b'z2
-  Red rn(S, n), rm(S, m);
-  const double ti = 1.0 / S->tau;
-  vlin3(n, 2.0 * ti, S->Px, 1.0, S->dq, 0.0, nullptr, S->t2, st);
-  const int a1 = rn.dot(S->t2, S->x1), a2 = rn.dot(S->t2, S->x2);
-  const int b1 = rm.dot(S->db, S->z1), b2 = rm.dot(S->db, S->z2);
-  std::vector<double> va, vb;
-  run_pair(rn, rm, va, vb);
+  int nbn = 0, nbm = 0;
+  dir_dots(n, m, 2.0 / S->tau, S->Px, S->dq, S->x1, S->x2, S->db, S->z1, S->z2, S->dpart, &nbn, &nbm, st);
+  Collect c;
+  for (int o = 0; o < 4; ++o)
+    c.add(S->dpart + (o < 2 ? 0 : 2 * (int64_t)nbn) + (o & 1), o < 2 ? nbn : nbm, 2, COLLECT_SUM);
+  double v[4];   // w'x1, w'x2, b'z1, b'z2
+  fetch(S, c, v);
   Dir d;
   const double xPx = S->xPx_cache;
-  const double num = dtau_rhs - dkap_rhs / S->tau + va[a1] + vb[b1];
-  const double den = S->kappa / S->tau + xPx / (S->tau * S->tau) - va[a2] - vb[b2];
+  const double num = dtau_rhs - dkap_rhs / S->tau + v[0] + v[2];
+  const double den = S->kappa / S->tau + xPx / (S->tau * S->tau) - v[1] - v[3];
   d.dtau = num / den;
-  vlin3(n, 1.0, S->x1, d.dtau, S->x2, 0.0, nullptr, dxo, st);
-  vlin3(m, 1.0, S->z1, d.dtau, S->z2, 0.0, nullptr, dzo, st);
+  RowJobs j;
+  j.add(lin_job(n, 1.0, S->x1, d.dtau, S->x2, dxo));
+  j.add(lin_job(m, 1.0, S->z1, d.dtau, S->z2, dzo));
+  row_jobs(j, st);
   {
     ConeProbe probe(S, CO_RECOVER);
     cone_apply_all(S->sdev, 0, 0.0, dzo, ds_rhs, dso, st);
@@ -2339,9 +2477,11 @@ double step_length(hc_solver* S, const Step& d, bool combined) {
       off = cone_step_sym_all(S->sdev, S->s, S->z, d.ds, d.dz, S->dpart, st);
     }
     if (off) {
-      HC_HIP(hipMemcpyAsync(S->hpart, S->dpart, off * sizeof(double), hipMemcpyDeviceToHost, st));
-      HC_HIP(hipStreamSynchronize(st));
-      for (int64_t i = 0; i < off; ++i) a = std::min(a, S->hpart[i]);
+      Collect c;
+      c.add(S->dpart, off, 1, COLLECT_MIN);
+      double v;
+      fetch(S, c, &v);
+      a = std::min(a, v);
     }
   }
   if (!S->has_nonsym) return a;
@@ -2463,7 +2603,16 @@ void init_point(hc_solver* S) {
   hipStream_t st = S->stream;
   const int64_t n = S->n, m = S->m;
   S->tau = S->kappa = 1.0;
+  vlin3(n, -1.0, S->dq, 0.0, nullptr, 0.0, nullptr, S->r1c, st);   // the constant system's [-q; b]
   if (S->has_nonsym) {
+    Red a(S, n), b(S, m);
+    a.maxabs(S->r1c);
+    b.maxabs(S->db);
+    Collect c;
+    b.launch(a.launch(0, c), c);
+    double v[2];
+    fetch(S, c, v);
+    S->nb_const = std::isnan(v[0]) || std::isnan(v[1]) ? NAN : std::max(v[0], v[1]);
     vfill(n, 0.0, S->x, st);
     for (auto& g : S->sdev) {
       cone_unit(g, S->s, st);
@@ -2476,20 +2625,19 @@ void init_point(hc_solver* S) {
     HC_LAUNCH_CHECK();
   }
   factor(S);
-  vlin3(n, -1.0, S->dq, 0.0, nullptr, 0.0, nullptr, S->r1, st);
-  kkt_solve(S, S->r1, S->db, S->x, S->z);
+  kkt_solve(S, S->r1c, S->db, &S->x, &S->z, &S->nb_const);
   vaxpby(m, -1.0, S->z, 0.0, S->s, st);                      // s = -z
   for (auto& g : S->sdev)
     if (g.kind == HC_CONE_ZERO) vfill(g.count, 0.0, S->s + g.base, st);
   for (int which = 0; which < 2; ++which) {
     double* v = which == 0 ? S->s : S->z;
     double amax = -INFINITY;
-    for (auto& g : S->sdev) {
-      const int nb = cone_max_neg_eig(g, v, S->dpart, st);
-      if (!nb) continue;
-      HC_HIP(hipMemcpyAsync(S->hpart, S->dpart, nb * sizeof(double), hipMemcpyDeviceToHost, st));
-      HC_HIP(hipStreamSynchronize(st));
-      for (int i = 0; i < nb; ++i) amax = std::max(amax, S->hpart[i]);
+    int64_t off = 0;
+    for (auto& g : S->sdev) off += cone_max_neg_eig(g, v, S->dpart + off, st);
+    if (off) {
+      Collect c;
+      c.add(S->dpart, off, 1, COLLECT_TOP);
+      fetch(S, c, &amax);
     }
     if (amax >= 0)
       for (auto& g : S->sdev) cone_add_e(g, 1.0 + amax, v, st);
@@ -2516,19 +2664,24 @@ int iterate(hc_solver* S, const Resid& R) {
   for (int attempt = 0; attempt < 2; ++attempt) {
     double t0 = now_ms();
     int pd = 0;
-    scale_all(S, mu, force_dual, &pd);
+    const double hmax = scale_all(S, mu, force_dual, &pd);
     double t1 = now_ms();
-    factor(S);
-    HC_HIP(hipStreamSynchronize(st));
-    double t2 = now_ms();
+    S->clock.start(st);
+    factor(S, false, hmax);
+    S->clock.stop(st);
     S->info.cone_ms += t1 - t0;
-    S->info.factor_ms += t2 - t1;
-    // constant system K [x2; z2] = [-q; b] and the affine one, r1 = gx,
-    // r2 = -(gz - s) = rpv + s, refined together
-    vlin3(n, -1.0, S->dq, 0.0, nullptr, 0.0, nullptr, S->r1c, st);
-    vlin3(n, -1.0, S->rdv, 0.0, nullptr, 0.0, nullptr, S->r1, st);
-    vlin3(m, 1.0, S->rpv, 1.0, S->s, 0.0, nullptr, S->r2, st);
-    kkt_solve_pair(S, S->r1c, S->db, S->x2, S->z2, S->r1, S->r2, S->x1, S->z1);
+    // constant system K [x2; z2] = [-q; b] and the affine one (r1, r2 from the
+    // residuals), refined together
+    if (attempt > 0) {   // the combined system's right-hand side took r1 and r2
+      RowJobs j;
+      j.add(lin_job(n, -1.0, S->rdv, 0.0, nullptr, S->r1));
+      j.add(lin_job(m, 1.0, S->rpv, 1.0, S->s, S->r2));
+      row_jobs(j, st);
+    }
+    kkt_solve_pair(S, ir_first(S, S->r1c, S->db, &S->x2, &S->z2, S->nb_const),
+                   ir_second(S, S->r1, S->r2, &S->x1, &S->z1, R.nb));
+    const double fms = S->clock.read_ms();   // (done: the refinement has read its norms back)
+    S->info.factor_ms += fms;
     const Dir da = direction(S, nullptr, nullptr, gt, S->kappa * S->tau, S->s, S->dxa, S->dza, S->dsa);
     alpha_a = step_length(S, Step{S->dsa, S->dza, da.dtau, da.dkappa}, false);
     sigma = (1.0 - alpha_a) * (1.0 - alpha_a) * (1.0 - alpha_a);
@@ -2539,12 +2692,15 @@ int iterate(hc_solver* S, const Resid& R) {
       cone_ds_all(S->sdev, S->s, S->z, S->dsa, S->dza, sigma * mu, S->dsrhs, st);
     }
     const double f = 1.0 - sigma;
-    vlin3(n, -f, S->rdv, 0.0, nullptr, 0.0, nullptr, S->r1, st);
-    // r2 = -(f gz - ds) = f rpv + ds
-    vlin3(m, f, S->rpv, 1.0, S->dsrhs, 0.0, nullptr, S->r2, st);
+    {
+      RowJobs j;   // r2 = -(f gz - ds) = f rpv + ds
+      j.add(lin_job(n, -f, S->rdv, 0.0, nullptr, S->r1));
+      j.add(lin_job(m, f, S->rpv, 1.0, S->dsrhs, S->r2));
+      row_jobs(j, st);
+    }
     dc = direction(S, S->r1, S->r2, f * gt, dk, S->dsrhs, S->dx, S->dz, S->dsv);
     alpha_c = step_length(S, Step{S->dsv, S->dz, dc.dtau, dc.dkappa}, true);
-    S->info.solve_kkt_ms += now_ms() - t2;
+    S->info.solve_kkt_ms += std::max(0.0, now_ms() - t1 - fms);
     if (alpha_c < 0.1 && pd > 0 && !force_dual) {
       force_dual = true;
       S->info.dual_switches++;
@@ -2560,9 +2716,13 @@ int iterate(hc_solver* S, const Resid& R) {
   }
   if (alpha_c < 1e-4) return HC_STATUS_INSUFFICIENT_PROGRESS;
   const double a = S->st.step_fraction * alpha_c;
-  vaxpby(n, a, S->dx, 1.0, S->x, st);
-  vaxpby(m, a, S->dsv, 1.0, S->s, st);
-  vaxpby(m, a, S->dz, 1.0, S->z, st);
+  {
+    RowJobs j;
+    j.add(lin_job(n, 1.0, S->x, a, S->dx, S->x));
+    j.add(lin_job(m, 1.0, S->s, a, S->dsv, S->s));
+    j.add(lin_job(m, 1.0, S->z, a, S->dz, S->z));
+    row_jobs(j, st);
+  }
   S->tau += a * dc.dtau;
   S->kappa += a * dc.dkappa;
   return 0;
@@ -2583,6 +2743,7 @@ void begin_solve(hc_solver* S) {
   S->info.factor_flops = keep.factor_flops;
   vfill(1, 0.0, (double*)S->dhits, S->stream);
   S->sdiag_max = 0;
+  S->px_zero = false;
   init_point(S);
   if (S->st.warm_start && S->have_warm) {   // parametric re-solve from the last solution (Sec. 4.6)
     const int64_t L = std::max(S->n, S->m);
@@ -2880,6 +3041,13 @@ void bind(hc_solver* S, const hc_device* dev) {
     HC_HIP(hipHostMalloc((void**)&S->hmask, S->npart * sizeof(unsigned long long), hipHostMallocDefault));
     S->own_stage = true;
   }
+  if (S->own_stage) {
+    void* d = nullptr;
+    if (hipHostGetDevicePointer(&d, S->hpart, 0) == hipSuccess) S->hmap = (double*)d;
+    else (void)hipGetLastError();
+    S->hpart[RB_FLAG] = 0.0;   // all bits clear, as rb_seq
+  }
+  S->clock.events = S->own_stage;
   vfill(1, 0.0, (double*)S->dhits, st);
   if (S->K1 + S->K2 > 0) {   // zero padding rows of the dense-row operand, zero rank-2 rows
     vfill((S->K1 + S->K2) * S->nt, 0.0, S->dBd, st);
@@ -3816,7 +3984,7 @@ int32_t hc_test_kkt_solve(hc_solver* S, double mu, int32_t force_dual, const dou
     HC_HIP(hipMemcpyAsync(S->r1, r1, n * 8, hipMemcpyHostToDevice, st));
     HC_HIP(hipMemcpyAsync(S->r2, r2, m * 8, hipMemcpyHostToDevice, st));
     const int64_t before = S->info.ir_solves, fb = S->info.fp64_fallbacks;
-    kkt_solve(S, S->r1, S->r2, S->x1, S->z1);
+    kkt_solve(S, S->r1, S->r2, &S->x1, &S->z1);
     HC_HIP(hipMemcpyAsync(xo, S->x1, n * 8, hipMemcpyDeviceToHost, st));
     HC_HIP(hipMemcpyAsync(zo, S->z1, m * 8, hipMemcpyDeviceToHost, st));
     HC_HIP(hipStreamSynchronize(st));

@@ -7,7 +7,6 @@ namespace hc {
 int choose_lanes(double mean_nnz);
 void vlin3(int64_t n, double a, const double* x, double b, const double* y, double c, const double* w, double* z,
            hipStream_t st);
-void vscale_by(int64_t n, const double* x, const double* w, bool divide, double* y, hipStream_t st);
 
 enum { RED_DOT = 0, RED_MAX_MUL = 1, RED_MAX_DIV = 2 };
 // DOT: sum x*y.  MAX_MUL / MAX_DIV: max |(x + yc*y) * w| or |(x + yc*y) / w|
@@ -25,6 +24,79 @@ struct RedOps {
   RedOp op[MAX_RED_OPS];
 };
 int reduce_launch(int64_t n, const RedOps& ops, double* partial, hipStream_t st);   // returns blocks
+// Independent row jobs in one launch, each on a block range of its own:
+//   ROW_MUL    y = alpha A x + beta c        (c unused when beta == 0)
+//   ROW_SUM    y = A x + p                   p: A2 x2 (second()), addp[row] or 0
+//   ROW_RESID  y = c - (A x + p)
+//   ROW_LIN    y = alpha x + beta c          (no matrix; alpha x rounded first)
+// Sums run in spmv's order.  With pmax, block b of the job (blocks() of them) leaves max |y| over its
+// rows in pmax[b] (a NaN stays a NaN).  c may be y.  Rows above A's long_nnz
+// take a workgroup each; A2 must have none, and no more lanes per row than A.
+enum { ROW_MUL = 0, ROW_SUM = 1, ROW_RESID = 2, ROW_LIN = 3 };
+struct RowJob {
+  int32_t kind = ROW_LIN, nrows = 0, lanes = 1, long_nnz = 0x7fffffff, nlong = 0, lanes2 = 1;
+  const int32_t *rp = nullptr, *ci = nullptr, *longrows = nullptr;
+  const double *v = nullptr, *x = nullptr;
+  const int32_t *rp2 = nullptr, *ci2 = nullptr;
+  const double *v2 = nullptr, *x2 = nullptr, *addp = nullptr;
+  const double* c = nullptr;
+  double* y = nullptr;
+  double alpha = 1.0, beta = 0.0;
+  double* pmax = nullptr;
+  RowJob() = default;
+  RowJob(int kind_, const Csr& A, const double* x_, double* y_);
+  static bool pairs(const Csr& A, const Csr& B) { return B.nlong == 0 && B.lanes <= A.lanes; }
+  void second(const Csr& B, const double* xb) { lanes2 = B.lanes, rp2 = B.rowptr, ci2 = B.col, v2 = B.val, x2 = xb; }
+  int row_blocks() const;
+  int blocks() const;
+};
+constexpr int MAX_ROW_JOBS = 6;
+struct RowJobs {
+  RowJob j[MAX_ROW_JOBS];
+  int32_t first[MAX_ROW_JOBS + 1];
+  int32_t rows[MAX_ROW_JOBS];   // row blocks (the rest take long rows)
+  int32_t n = 0;
+  void add(const RowJob& job) { j[n++] = job; }
+};
+void row_jobs(RowJobs& J, hipStream_t st);
+// Reductions of the termination tests and of the affine right-hand side, with
+// the vectors they are taken of, in one launch (partials: 8 per block, the n
+// side's blocks first):
+//   rd = Px + A'z + tau q, r1 = -rd:  x'Px, q'x, |rd / D|, |D x|, |A'z / D|, |Px / D|, |r1|
+//   rp = -Ax - s + tau b, r2 = rp + s: b'z, s'z, |rp / E|, |s / E|, |E z|, |(Ax + s) / E|, |r2|
+struct ResidArgs {
+  int64_t n, m;
+  const double *Px, *Atz, *q, *x, *D;
+  double *rd, *r1;
+  const double *Ax, *s, *b, *z, *E;
+  double *rp, *r2;
+  double tau;
+};
+constexpr int RESID_VALS = 7;
+void resid_launch(const ResidArgs& a, double* partial, int* nbn, int* nbm, hipStream_t st);
+// w'x1, w'x2 with w = pc Px + q over n, b'z1, b'z2 over m (partials: 2 per block)
+void dir_dots(int64_t n, int64_t m, double pc, const double* Px, const double* q, const double* x1, const double* x2,
+              const double* b, const double* z1, const double* z2, double* partial, int* nbn, int* nbm,
+              hipStream_t st);
+// Combines partials, op by op in a fixed order, into out[0 .. n) and then
+// writes seq to *flag (when given): with out and flag in pinned host memory
+// the host has the values without a copy.
+// MAX: of magnitudes (from 0, a NaN stays a NaN); MIN, TOP: smallest, largest
+// value (NaN ignored); INT: *(int*)p
+enum { COLLECT_SUM = 0, COLLECT_MAX = 1, COLLECT_MIN = 2, COLLECT_TOP = 3, COLLECT_INT = 4 };
+struct CollectOp {
+  const double* p;
+  int32_t cnt, stride, kind;
+};
+constexpr int MAX_COLLECT = 16;
+struct Collect {
+  CollectOp op[MAX_COLLECT];
+  int32_t n = 0;
+  void add(const double* p, int64_t cnt, int stride, int kind) {
+    op[n++] = CollectOp{p, (int32_t)cnt, stride, kind};
+  }
+};
+void collect(const Collect& c, double* out, unsigned long long* flag, unsigned long long seq, hipStream_t st);
 void combine_max(int nb, const double* partial, double* out, hipStream_t st);
 void to_f32(int64_t n, const double* x, const double* scale, float* y, hipStream_t st);
 void from_f32(int64_t n, const float* x, const double* scale, double* y, hipStream_t st);
