@@ -141,8 +141,10 @@ struct hc_solver {
   // pair tasks below keep only what the groups do not take
   std::vector<int64_t> ga_rows_off, ga_u_off, ga_m_off, ga_t_off, ga_gm, ga_c_ptr;
   std::vector<int32_t> ga_rows, ga_u, ga_c_b, ga_c_k, ga_rgrp, ga_rloc;
-  std::vector<int64_t> ga_e_t, ga_e_u;   // per entry of A': its T row and column list
-  std::vector<int32_t> ga_e_s;           // and the list's length (0: row in no group)
+  std::vector<int64_t> ga_e_t, ga_e_u;   // per entry of A': its T row and column list, from the entry's column on
+  std::vector<int32_t> ga_e_s;           // and the length left (0: row in no group)
+  std::vector<int32_t> ga_wide;          // groups of GROUP_WIDE entries of T or more
+  int ga_wide_rows = 0;
   int64_t ga_ng = 0, ga_t_total = 0;
   GroupPlan gplan;
   std::vector<int32_t> tra, trb;   // Schur assembly tasks: short ones first, then
@@ -1146,14 +1148,15 @@ void setup_host(hc_solver* S, const hc_problem* p) {
 // large SOC) form a group g, with U_g the sorted union of their columns.  Per
 // iteration T_g = M_g A_g and each column of S gathers A[r][j] T_r over the
 // rows of that column of A (group_T, group_gather: one writer per entry, a
-// fixed order).  When a column of S fits two LDS chunks (n <= 2 GATHER_CHUNK)
-// every group is taken, so the whole assembly has one writer per entry and a
-// fixed order; on larger problems only groups of at least GROUP_MIN_ROWS rows
-// (PSD cones: many row pairs, each S entry hit by many of them) are taken, and
-// the rest keep their pair tasks, which are cheaper there (a gather over a
-// 20,000-row column in five chunks costs more than the few atomics a 3-row
+// fixed order).  Up to GROUP_ALL_NMAX columns (two LDS chunks at most) every
+// group is taken, so the whole assembly has one writer per entry and a fixed
+// order; on larger problems only groups of at least GROUP_MIN_ROWS rows (PSD
+// cones: many row pairs, each S entry hit by many of them) are taken, and the
+// rest keep their pair tasks, which are cheaper there (a gather over a
+// 20,000-row column in four chunks costs more than the few atomics a 3-row
 // cone adds).  A group whose T_g would exceed GROUP_T_MAX entries keeps its
 // pair tasks.
+constexpr int64_t GROUP_ALL_NMAX = 8192;
 constexpr int64_t GROUP_MIN_ROWS = 6;
 constexpr int64_t GROUP_T_MAX = int64_t(1) << 22;
 void build_groups(hc_solver* S) {
@@ -1170,6 +1173,8 @@ void build_groups(hc_solver* S) {
   S->ga_c_k.clear();
   S->ga_rgrp.clear();
   S->ga_rloc.clear();
+  S->ga_wide.clear();
+  S->ga_wide_rows = 0;
   if (S->leaves || S->tra.empty()) return;
   const HostCsr& A = S->A;
   const int64_t m = A.nrows, nt = (int64_t)S->tra.size();
@@ -1207,6 +1212,7 @@ void build_groups(hc_solver* S) {
     int32_t col, k, b;   // column, index in A, group-local row
   };
   std::vector<Ent> ent;   // the group's entries in row order
+  std::vector<int32_t> upos(A.ci.size(), 0);   // per entry of A: its column's place in the group's list
   for (size_t g = 0; g < rows.size(); ++g) {
     ent.clear();
     for (int32_t r : rows[g])
@@ -1216,7 +1222,7 @@ void build_groups(hc_solver* S) {
     std::sort(u.begin(), u.end());
     u.erase(std::unique(u.begin(), u.end()), u.end());
     const int64_t nr = (int64_t)rows[g].size(), s = (int64_t)u.size();
-    if ((A.ncols > 2 * GATHER_CHUNK && nr < GROUP_MIN_ROWS) || nr * s > GROUP_T_MAX) continue;
+    if ((A.ncols > GROUP_ALL_NMAX && nr < GROUP_MIN_ROWS) || nr * s > GROUP_T_MAX) continue;
     const int32_t id = (int32_t)S->ga_ng++;
     S->ga_m_off.push_back((int64_t)S->ga_gm.size());
     S->ga_t_off.push_back(S->ga_t_total);
@@ -1233,6 +1239,11 @@ void build_groups(hc_solver* S) {
     for (size_t e = 0; e < ent.size(); ++e) {
       pos[e] = (int32_t)(std::lower_bound(u.begin(), u.end(), ent[e].col) - u.begin());
       cnt[pos[e] + 1]++;
+      upos[ent[e].k] = pos[e];
+    }
+    if (nr * s >= GROUP_WIDE) {
+      S->ga_wide.push_back(id);
+      S->ga_wide_rows = std::max(S->ga_wide_rows, (int)nr);
     }
     for (int64_t q = 0; q < s; ++q) cnt[q + 1] += cnt[q];
     const int64_t base = (int64_t)S->ga_c_b.size();
@@ -1271,18 +1282,25 @@ void build_groups(hc_solver* S) {
   S->tm.resize(keep);
   S->ntask_short = keep_short;
   // per entry p of A' (row r of column j): the T row of r's group (offset in
-  // T), that group's column list and length, 0 length when r is in no group
+  // T), that group's column list and length, all from column j on (only rows
+  // i >= j of the column are gathered), 0 length when r is in no group
+  std::vector<int32_t> next(A.rp.begin(), A.rp.end() - 1);   // A' lists each row's entries in column order
   const HostCsr& At = S->At;
+  int64_t j = 0;
   S->ga_e_t.assign(At.ci.size(), 0);
   S->ga_e_u.assign(At.ci.size(), 0);
   S->ga_e_s.assign(At.ci.size(), 0);
   for (size_t p = 0; p < At.ci.size(); ++p) {
     const int32_t r = At.ci[p], g = S->ga_rgrp[r];
+    while (p >= (size_t)At.rp[j + 1]) ++j;
     if (g < 0) continue;
+    int32_t k = next[r]++;
+    if (A.ci[k] != j)   // row not sorted by column
+      for (k = A.rp[r]; A.ci[k] != j;) ++k;
     const int64_t uo = S->ga_u_off[g], sz = S->ga_u_off[g + 1] - uo;
-    S->ga_e_t[p] = S->ga_t_off[g] + (int64_t)S->ga_rloc[r] * sz;
-    S->ga_e_u[p] = uo;
-    S->ga_e_s[p] = (int32_t)sz;
+    S->ga_e_t[p] = S->ga_t_off[g] + (int64_t)S->ga_rloc[r] * sz + upos[k];
+    S->ga_e_u[p] = uo + upos[k];
+    S->ga_e_s[p] = (int32_t)sz - upos[k];
   }
 }
 
@@ -2837,6 +2855,9 @@ void alloc_all(hc_solver* S, Buf& buf, hipStream_t st) {
   {
     GroupPlan& gp = S->gplan;
     gp.ng = S->ga_ng;
+    gp.nwide = (int64_t)S->ga_wide.size();
+    gp.wide_rows = S->ga_wide_rows;
+    gp.wide = upload(buf, S->ga_wide, st);
     gp.rows_off = upload(buf, S->ga_rows_off, st);
     gp.u_off = upload(buf, S->ga_u_off, st);
     gp.m_off = upload(buf, S->ga_m_off, st);

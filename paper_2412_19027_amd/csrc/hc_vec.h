@@ -130,22 +130,28 @@ void dense_T_gather(int64_t n, const int32_t* erp, const int32_t* ee, const int3
 // Schur contribution A' M A of the cone rows as a gather (no atomics, a fixed
 // order).  The rows the cones couple form groups g (one per cone; one per row
 // of a zero or nonneg segment) with the sorted union U_g of their columns.
-// group_T: T_g = M_g A_g (|R_g| x |U_g|, row-major at T + t_off[g]), one wave
-// per group, a lane per column of U_g summing over that column's entries of
-// the group's rows (c_ptr / c_b / c_k: per entry of the concatenated U lists,
-// the group-local row b and the index k of the entry in A), in row order; gm
-// (|R_g|^2 per group at m_off[g]) holds the index of M_g[a][b] in mval or -1.
+// group_T: T_g = M_g A_g (|R_g| x |U_g|, row-major at T + t_off[g]), a lane per
+// column of U_g summing over that column's entries of the group's rows (c_ptr /
+// c_b / c_k: per entry of the concatenated U lists, the group-local row b and
+// the index k of the entry in A), in row order; gm (|R_g|^2 per group at
+// m_off[g]) holds the index of M_g[a][b] in mval or -1.  The groups with
+// GROUP_WIDE entries of T or more (wide, nwide; wide_rows the largest |R_g|
+// among them) take workgroups, the others a wave.
 // group_gather: column j of S (rows i >= j) gains sum over the rows r of
 // column j of A, in order, of A[r][j] T_r[i]; one wave per column, the column
-// in LDS chunks of GATHER_CHUNK rows.
-constexpr int GATHER_CHUNK = 4096;
+// in LDS chunks of at most GATHER_CHUNK rows.
+constexpr int GATHER_CHUNK = 5120;
+constexpr int64_t GROUP_WIDE = 1024;
 struct GroupPlan {
-  int64_t ng = 0;
+  int64_t ng = 0, nwide = 0;
+  int wide_rows = 0;
   const int64_t *rows_off = nullptr, *u_off = nullptr, *m_off = nullptr, *t_off = nullptr, *gm = nullptr,
                 *c_ptr = nullptr;
-  const int32_t *rows = nullptr, *u = nullptr, *c_b = nullptr, *c_k = nullptr, *rgrp = nullptr, *rloc = nullptr;
-  // per entry of A' (the column gather's rows): offset of the row's T row,
-  // its group's column list, that list's length (0: the row is in no group)
+  const int32_t *rows = nullptr, *u = nullptr, *c_b = nullptr, *c_k = nullptr, *rgrp = nullptr, *rloc = nullptr,
+                *wide = nullptr;
+  // per entry (r, j) of A' (the column gather's rows): offsets into the row's T
+  // row and its group's column list, both from column j on, and how many
+  // follow (0: the row is in no group)
   const int64_t *e_t = nullptr, *e_u = nullptr;
   const int32_t* e_s = nullptr;
   double* T = nullptr;

@@ -464,9 +464,11 @@ __device__ inline double combine(int kind, double a, double v) {
   return kind == COLLECT_MAX ? nmax(a, v) : kind == COLLECT_MIN ? fmin(a, v) : fmax(a, v);
 }
 // one wave per op.  Extrema: lane-strided, then a shuffle tree; sums: partial
-// after partial (at most 512 of them), the order they had on the host.
+// after partial (at most 512 of them, from LDS: 8 cycles each), the order they
+// had on the host.
 __global__ __launch_bounds__(64 * MAX_COLLECT) void k_collect(Collect c, double* out, unsigned long long* flag,
                                                               unsigned long long seq) {
+  __shared__ double part[MAX_COLLECT][512];
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   if (w < c.n) {
     const CollectOp op = c.op[w];
@@ -474,13 +476,28 @@ __global__ __launch_bounds__(64 * MAX_COLLECT) void k_collect(Collect c, double*
     if (op.kind == COLLECT_INT) {
       acc = (double)*(const int*)op.p;
     } else if (op.kind == COLLECT_SUM) {
-      for (int i = 0; i < op.cnt; i += 64) {
-        const double v = i + lane < op.cnt ? op.p[(int64_t)(i + lane) * op.stride] : 0.0;
-        const int k = min(64, op.cnt - i);
-        for (int l = 0; l < k; ++l) acc += __shfl(v, l, 64);
+      double* ls = part[w];
+      for (int i0 = 0; i0 < op.cnt; i0 += 512) {
+        const int k = min(512, op.cnt - i0);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          const int i = 64 * q + lane;
+          const double v = op.p[(int64_t)(i0 + min(i, k - 1)) * op.stride];
+          ls[i] = i < k ? v : 0.0;
+        }
+        __builtin_amdgcn_wave_barrier();   // read across lanes of the wave
+        for (int i = 0; i < k; i += 8)
+#pragma unroll
+          for (int l = 0; l < 8; ++l) acc += ls[i + l];
       }
     } else {
-      for (int i = lane; i < op.cnt; i += 64) acc = combine(op.kind, acc, op.p[(int64_t)i * op.stride]);
+      for (int i = lane; i < op.cnt; i += 512) {
+        double v[8];   // the last partial more than once changes no extremum
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = op.p[(int64_t)min(i + 64 * q, op.cnt - 1) * op.stride];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) acc = combine(op.kind, acc, v[q]);
+      }
       for (int off = 32; off > 0; off >>= 1) acc = combine(op.kind, acc, __shfl_xor(acc, off, 64));
     }
     if (lane == 0) {
@@ -638,31 +655,50 @@ void assemble_pairs(int64_t ntask, const int32_t* tra, const int32_t* trb, const
 // (M_c symmetric, stored as its lower triangle: entry (a, b), a >= b, at
 // moff + (a (a + 1) / 2 + b) count + c).  One workgroup per row, a thread per
 // column the cone touches summing that column's entries in row order.
+// One workgroup per cone and PT_ROWS rows of T.  Those rows of M_c are staged in
+// LDS (M is packed by cone, so its entries lie `count` apart), a thread takes a
+// column and loads each of its entries once for all PT_ROWS rows; with a row of
+// T per workgroup, every term was two loads of scattered lines.  30 cones each
+// of sides 20 and 32 on 1,800 columns, both segments: 826 -> 241 us.
+constexpr int PT_ROWS = 8;
 __global__ __launch_bounds__(256) void k_psd_dense_T(int32_t dim, int64_t count, int64_t coff, int64_t moff,
                                                      const double* __restrict__ mval, PsdCols pc,
                                                      const double* __restrict__ av, int64_t n,
                                                      double* __restrict__ T) {
-  const int64_t rows = count * dim;
-  for (int64_t e = blockIdx.x; e < rows; e += gridDim.x) {
-    const int64_t c = e / dim;
-    const int a = (int)(e % dim);
-    for (int64_t u = pc.cu_off[coff + c] + threadIdx.x; u < pc.cu_off[coff + c + 1]; u += blockDim.x) {
-      double acc = 0.0;
+  extern __shared__ double ms[];   // row b of the cone: PT_ROWS entries M[a0 .., b]
+  const int64_t nblk = (dim + PT_ROWS - 1) / PT_ROWS;
+  for (int64_t w = blockIdx.x; w < count * nblk; w += gridDim.x) {
+    const int64_t c = w / nblk;
+    const int a0 = (int)(w % nblk) * PT_ROWS, na = min(PT_ROWS, dim - a0);
+    __syncthreads();   // the previous rows' readers are done
+    for (int i = threadIdx.x; i < PT_ROWS * dim; i += 256) {
+      const int q = i / dim, b = i - q * dim, a = a0 + min(q, na - 1);
+      const int hi = a > b ? a : b, lo = a > b ? b : a;
+      ms[b * PT_ROWS + q] = mval[moff + ((int64_t)hi * (hi + 1) / 2 + lo) * count + c];
+    }
+    __syncthreads();
+    const int64_t u1 = pc.cu_off[coff + c + 1];
+    for (int64_t u = pc.cu_off[coff + c] + threadIdx.x; u < u1; u += 256) {
+      double acc[PT_ROWS] = {};
       for (int64_t k = pc.cu_ptr[u]; k < pc.cu_ptr[u + 1]; ++k) {
-        const int b = pc.cu_b[k];
-        const int hi = a > b ? a : b, lo = a > b ? b : a;
-        acc += mval[moff + ((int64_t)hi * (hi + 1) / 2 + lo) * count + c] * av[pc.cu_p[k]];
+        const double* m = ms + pc.cu_b[k] * PT_ROWS;
+        const double x = av[pc.cu_p[k]];
+#pragma unroll
+        for (int q = 0; q < PT_ROWS; ++q) acc[q] += m[q] * x;
       }
-      T[e * n + pc.cu_col[u]] = acc;
+      double* t = T + (c * dim + a0) * n + pc.cu_col[u];
+#pragma unroll
+      for (int q = 0; q < PT_ROWS; ++q)
+        if (q < na) t[q * n] = acc[q];
     }
   }
 }
 void psd_dense_T(int32_t dim, int64_t count, int64_t coff, int64_t moff, const double* mval, const PsdCols& pc,
                  const double* av, int64_t n, double* T, hipStream_t st) {
-  const int64_t rows = count * dim;
-  if (rows == 0) return;
-  hipLaunchKernelGGL(k_psd_dense_T, dim3((unsigned)std::min<int64_t>(rows, 16384)), dim3(256), 0, st, dim, count,
-                     coff, moff, mval, pc, av, n, T);
+  const int64_t wgs = count * ceil_div(dim, PT_ROWS);
+  if (wgs == 0) return;
+  hipLaunchKernelGGL(k_psd_dense_T, dim3((unsigned)std::min<int64_t>(wgs, 65536)), dim3(256),
+                     (size_t)dim * PT_ROWS * sizeof(double), st, dim, count, coff, moff, mval, pc, av, n, T);
   HC_LAUNCH_CHECK();
 }
 
@@ -714,38 +750,53 @@ void ordered_sum(const OrderedSum& os, const double* mval, const double* av, con
   }
 }
 
-// S[j, k] += sum_e A[row(e), j] T[e, k] for k <= j: one workgroup per column
-// j of A (row j of S), lanes over k, so each entry has one writer and the T
-// rows are read contiguously
+// S[j, k] += sum_e A[row(e), j] T[e, k] for k <= j: a workgroup takes TG_COLS
+// columns j of A (rows j of S) and 256 columns k of S, a thread one k, so each
+// entry has one writer, the T rows are read contiguously and a thread writes
+// TG_COLS neighbours of S's column k (one entry each, the writes of a wave went
+// to 64 lines; the workload of psd_dense_T: 436 -> 373 us, 1.3 GB of T).
+constexpr int TG_COLS = 8;
 __global__ __launch_bounds__(256) void k_dense_T_gather(int64_t n, const int32_t* __restrict__ erp,
                                                         const int32_t* __restrict__ ee, const int32_t* __restrict__ ep,
                                                         const double* __restrict__ atval,
                                                         const double* __restrict__ T, int64_t ld,
                                                         double* __restrict__ S) {
-  for (int64_t j = blockIdx.x; j < n; j += gridDim.x) {
-    const int32_t b = erp[j], e = erp[j + 1];
-    if (b == e) continue;
-    for (int64_t k = threadIdx.x; k <= j; k += blockDim.x) {
-      double s = 0.0;
-      for (int32_t p = b; p < e; ++p) s += atval[ep[p]] * T[(int64_t)ee[p] * n + k];
-      S[j + k * ld] += s;
+  const int64_t j0 = (int64_t)blockIdx.x * TG_COLS, k = (int64_t)blockIdx.y * 256 + threadIdx.x;
+  const int64_t j1 = std::min<int64_t>(n, j0 + TG_COLS);
+  if ((int64_t)blockIdx.y * 256 >= j1) return;
+  const double* Tk = T + std::min<int64_t>(k, n - 1);
+  for (int64_t j = j0; j < j1; ++j) {
+    double s = 0.0;
+    int32_t p = erp[j];
+    const int32_t e = erp[j + 1];
+    if (p == e) continue;
+    for (; p + 8 <= e; p += 8) {
+      double t[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) t[q] = Tk[(int64_t)ee[p + q] * n];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) s += atval[ep[p + q]] * t[q];
     }
+    for (; p < e; ++p) s += atval[ep[p]] * Tk[(int64_t)ee[p] * n];
+    if (k <= j) S[j + k * ld] += s;
   }
 }
 void dense_T_gather(int64_t n, const int32_t* erp, const int32_t* ee, const int32_t* ep, const double* atval,
                     const double* T, int64_t ld, double* S, hipStream_t st) {
   if (n == 0) return;
-  hipLaunchKernelGGL(k_dense_T_gather, dim3((unsigned)std::min<int64_t>(n, 8192)), dim3(256), 0, st, n, erp, ee, ep,
-                     atval, T, ld, S);
+  hipLaunchKernelGGL(k_dense_T_gather, dim3((unsigned)ceil_div(n, TG_COLS), (unsigned)ceil_div(n, 256)), dim3(256), 0,
+                     st, n, erp, ee, ep, atval, T, ld, S);
   HC_LAUNCH_CHECK();
 }
 
+// Small groups: a wave each.
 __global__ __launch_bounds__(64) void k_group_T(GroupPlan gp, const double* __restrict__ mval,
                                                 const double* __restrict__ av) {
   const int lane = threadIdx.x;
   for (int64_t g = blockIdx.x; g < gp.ng; g += gridDim.x) {
     const int64_t nr = gp.rows_off[g + 1] - gp.rows_off[g];
     const int64_t uo = gp.u_off[g], s = gp.u_off[g + 1] - uo;
+    if (nr * s >= GROUP_WIDE) continue;
     const int64_t* gm = gp.gm + gp.m_off[g];
     double* T = gp.T + gp.t_off[g];
     for (int64_t a = 0; a < nr; ++a)
@@ -759,55 +810,151 @@ __global__ __launch_bounds__(64) void k_group_T(GroupPlan gp, const double* __re
       }
   }
 }
+// The groups of at least GROUP_WIDE entries of T: a workgroup per group and
+// GT_ROWS of its rows, whose part of M_g is staged in LDS (the index table gm
+// read once, in order) up to GT_ROWS_MAX rows per group; a thread takes a
+// column and loads its entries once for GT_ROWS rows.  A wave per group followed
+// gm -> mval for every term: 2,000 cones of 55 rows on 421 columns, 1.04 ms ->
+// 175 us (370 MB of T).
+constexpr int GT_ROWS = 8, GT_ROWS_MAX = 512;
+__global__ __launch_bounds__(256) void k_group_T_wide(GroupPlan gp, const double* __restrict__ mval,
+                                                      const double* __restrict__ av) {
+  extern __shared__ double ms[];   // row b of the group: GT_ROWS entries M[a0 .., b]
+  const int64_t g = gp.wide[blockIdx.x];
+  const int nr = (int)(gp.rows_off[g + 1] - gp.rows_off[g]);
+  const int64_t uo = gp.u_off[g], s = gp.u_off[g + 1] - uo;
+  const int64_t* gm = gp.gm + gp.m_off[g];
+  for (int a0 = blockIdx.y * GT_ROWS; a0 < nr; a0 += gridDim.y * GT_ROWS) {
+    const int na = min(GT_ROWS, nr - a0);
+    double* T = gp.T + gp.t_off[g] + (int64_t)a0 * s;
+    if (nr <= GT_ROWS_MAX) {
+      __syncthreads();   // the previous rows' readers are done
+      for (int i = threadIdx.x; i < GT_ROWS * nr; i += 256) {
+        const int q = i / nr, b = i - q * nr;
+        const int64_t mi = q < na ? gm[(int64_t)(a0 + q) * nr + b] : -1;
+        ms[b * GT_ROWS + q] = mi >= 0 ? mval[mi] : 0.0;
+      }
+      __syncthreads();
+    }
+    for (int64_t t = threadIdx.x; t < s; t += 256) {
+      double v[GT_ROWS] = {};
+      for (int64_t e = gp.c_ptr[uo + t]; e < gp.c_ptr[uo + t + 1]; ++e) {
+        const int b = gp.c_b[e];
+        const double x = av[gp.c_k[e]];
+        if (nr <= GT_ROWS_MAX) {
+#pragma unroll
+          for (int q = 0; q < GT_ROWS; ++q) v[q] += ms[b * GT_ROWS + q] * x;
+        } else {
+#pragma unroll
+          for (int q = 0; q < GT_ROWS; ++q) {
+            const int64_t mi = q < na ? gm[(int64_t)(a0 + q) * nr + b] : -1;
+            if (mi >= 0) v[q] += mval[mi] * x;
+          }
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < GT_ROWS; ++q)
+        if (q < na) T[q * s + t] = v[q];
+    }
+  }
+}
 void group_T(const GroupPlan& gp, const double* mval, const Csr& A, hipStream_t st) {
-  if (gp.ng == 0) return;
-  hipLaunchKernelGGL(k_group_T, dim3((unsigned)std::min<int64_t>(gp.ng, 65536)), dim3(64), 0, st, gp, mval, A.val);
-  HC_LAUNCH_CHECK();
+  if (gp.ng > gp.nwide) {
+    hipLaunchKernelGGL(k_group_T, dim3((unsigned)std::min<int64_t>(gp.ng, 65536)), dim3(64), 0, st, gp, mval, A.val);
+    HC_LAUNCH_CHECK();
+  }
+  if (gp.nwide > 0) {
+    const int rows = std::min(gp.wide_rows, GT_ROWS_MAX);
+    hipLaunchKernelGGL(k_group_T_wide,
+                       dim3((unsigned)gp.nwide, (unsigned)std::min<int64_t>(ceil_div(gp.wide_rows, GT_ROWS), 16)),
+                       dim3(256), (size_t)rows * GT_ROWS * sizeof(double), st, gp, mval, A.val);
+    HC_LAUNCH_CHECK();
+  }
 }
 
-__global__ __launch_bounds__(64) void k_group_gather(GroupPlan gp, int64_t n, const int32_t* __restrict__ atrp,
-                                                     const int32_t* __restrict__ atci,
+// value of one lane (wave-uniform index), as a scalar
+__device__ inline int lane_i(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
+__device__ inline int64_t lane_l(int64_t v, int l) {
+  const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)v, l), hi = __builtin_amdgcn_readlane((int)(v >> 32), l);
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+__device__ inline double lane_d(double v, int l) { return __longlong_as_double(lane_l(__double_as_longlong(v), l)); }
+// One wave per column j, its rows in order.  Each row adds a run of (index,
+// value) pairs to the column in LDS; the runs are cut into segments of 64 and
+// GG_AHEAD segments are in flight, since a wave that waits for each row's run
+// spends its time on memory latency (5 waves fit a CU): 2,000 cones of 55 rows
+// on 421 of 5,000 columns, 4.08 -> 0.78 ms (2.1 GB of T and indices; a column's
+// runs start at its own diagonal).  GATHER_CHUNK rows are 40 KB, four waves on a
+// CU; with 4,096 (five waves) a second pass over the runs began 1,000 columns
+// earlier and that workload took 0.93 ms.
+constexpr int GG_AHEAD = 8;
+__global__ __launch_bounds__(64) void k_group_gather(GroupPlan gp, int64_t n, int chunk,
+                                                     const int32_t* __restrict__ atrp,
                                                      const double* __restrict__ atv, int64_t ld,
                                                      double* __restrict__ S) {
-  __shared__ double acc[GATHER_CHUNK];
+  extern __shared__ double acc[];   // chunk rows
   const int lane = threadIdx.x;
   for (int64_t j = blockIdx.x; j < n; j += gridDim.x) {
     const int32_t p0 = atrp[j], p1 = atrp[j + 1];
-    for (int64_t c0 = j; c0 < n; c0 += GATHER_CHUNK) {
-      const int64_t c1 = std::min<int64_t>(n, c0 + GATHER_CHUNK);
-      for (int64_t i = c0 + lane; i < c1; i += 64) acc[i - c0] = 0.0;
-      // each row's T row and column list come from per-entry tables (one
-      // load level), and the next row's are loaded before this row's sum
-      int32_t s_nx = p0 < p1 ? gp.e_s[p0] : 0;
-      int64_t u_nx = p0 < p1 ? gp.e_u[p0] : 0, t_nx = p0 < p1 ? gp.e_t[p0] : 0;
-      double c_nx = p0 < p1 ? atv[p0] : 0.0;
-      for (int32_t p = p0; p < p1; ++p) {
-        const int64_t s = s_nx, uo = u_nx, to = t_nx;
-        const double coef = c_nx;
-        if (p + 1 < p1) {
-          s_nx = gp.e_s[p + 1];
-          u_nx = gp.e_u[p + 1];
-          t_nx = gp.e_t[p + 1];
-          c_nx = atv[p + 1];
-        }
-        if (s == 0) continue;
-        const double* vals = gp.T + to;
-        for (int64_t t = lane; t < s; t += 64) {
-          const int64_t i = gp.u[uo + t];
-          if (i >= c0 && i < c1) acc[i - c0] += coef * vals[t];
+    if (p0 == p1) continue;
+    for (int64_t c0 = j; c0 < n; c0 += chunk) {
+      const int len = (int)std::min<int64_t>(n - c0, chunk);
+      for (int i = lane; i < len; i += 64) acc[i] = 0.0;
+      for (int32_t pb = p0; pb < p1; pb += 64) {
+        // 64 rows' runs: a lane each, then picked by index
+        const int32_t p = std::min(pb + lane, p1 - 1);
+        const int rs = pb + lane < p1 ? gp.e_s[p] : 0;
+        const int64_t ru = gp.e_u[p], rt = gp.e_t[p];
+        const double rc = atv[p];
+        int nseg = (rs + 63) >> 6;
+        for (int off = 32; off > 0; off >>= 1) nseg += __shfl_xor(nseg, off, 64);
+        nseg = lane_i(nseg, 0);
+        int row = -1, t0 = 0, s = 0;   // the run being fetched
+        const int32_t* ui = gp.u;
+        const double* tv = gp.T;
+        double cf = 0.0;
+        int i_q[GG_AHEAD], l_q[GG_AHEAD];
+        double v_q[GG_AHEAD], c_q[GG_AHEAD];
+        auto fetch = [&](int q) {   // always two loads: the waits count them
+          while (t0 >= s && row < 63) {
+            ++row;
+            t0 = 0;
+            s = lane_i(rs, row);
+            if (s > 0) {
+              ui = gp.u + lane_l(ru, row);
+              tv = gp.T + lane_l(rt, row);
+              cf = lane_d(rc, row);
+            }
+          }
+          const int t = std::max(0, std::min(t0 + lane, s - 1));
+          i_q[q] = ui[t] - (int)c0;
+          v_q[q] = tv[t];
+          c_q[q] = cf;
+          l_q[q] = t0 + lane < s ? len : 0;
+          t0 += 64;
+        };
+#pragma unroll
+        for (int q = 0; q < GG_AHEAD; ++q) fetch(q);
+        for (int done = 0; done < nseg; done += GG_AHEAD) {
+#pragma unroll
+          for (int q = 0; q < GG_AHEAD; ++q) {
+            if ((unsigned)i_q[q] < (unsigned)l_q[q]) acc[i_q[q]] += c_q[q] * v_q[q];
+            fetch(q);
+          }
         }
       }
-      for (int64_t i = c0 + lane; i < c1; i += 64) {
-        const double v = acc[i - c0];
-        if (v != 0.0) S[i + j * ld] += v;
+      for (int i = lane; i < len; i += 64) {
+        const double v = acc[i];
+        if (v != 0.0) S[c0 + i + j * ld] += v;
       }
     }
   }
 }
 void group_gather(const GroupPlan& gp, int64_t n, const Csr& At, int64_t ld, double* S, hipStream_t st) {
   if (gp.ng == 0 || n == 0) return;
-  hipLaunchKernelGGL(k_group_gather, dim3((unsigned)std::min<int64_t>(n, 16384)), dim3(64), 0, st, gp, n, At.rowptr,
-                     At.col, At.val, ld, S);
+  const int chunk = (int)std::min<int64_t>(n, GATHER_CHUNK);
+  hipLaunchKernelGGL(k_group_gather, dim3((unsigned)std::min<int64_t>(n, 16384)), dim3(64),
+                     (size_t)chunk * sizeof(double), st, gp, n, chunk, At.rowptr, At.val, ld, S);
   HC_LAUNCH_CHECK();
 }
 
