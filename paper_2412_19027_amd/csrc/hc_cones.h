@@ -13,7 +13,7 @@ struct SegDev {
   int32_t k;          // PSD side
   int64_t base;       // first internal row
   int64_t count;      // cones
-  double* state;      // state_doubles(kind, dim, k) * count, field-major
+  double* state;      // state_doubles(kind, dim, k) * count, field-major (PSD: cone after cone)
   double* mblk;       // mblock_doubles(kind, dim) * count, entry-major
   const double* alpha;  // POW exponents (count) or null
 };
@@ -42,8 +42,8 @@ int64_t cone_mblock_work(const SegDev& g);
 //   EPI_RESID y = b - (a - v), and max |y| of its block in pmax (NaN stays NaN)
 //   EPI_NEG   y = -a - v        (recovery of Delta s from a = d_s)
 // The lane-per-cone families (zero, nonneg, SOC up to SOC_DMAX, exp, pow) run
-// in one launch for all segments and vectors, PSD segments in one each, larger
-// SOCs in one per vector (for EPI_ADD and EPI_RESID these two leave v in y and
+// in one launch for all segments and vectors, PSD segments in one per size
+// class, larger SOCs in one per vector (for EPI_ADD and EPI_RESID these two leave v in y and
 // the common launch finishes the rows).  cone_apply_parts: partials per vector
 // (EPI_RESID), at most 1,024 per segment.
 enum { EPI_PUT = 0, EPI_ADD = 1, EPI_RESID = 2, EPI_NEG = 3 };
@@ -130,6 +130,29 @@ int lsoc_max_neg_eig(const SegDev& g, const double* v, double* partial, hipStrea
 // for each (cone, column) entry e of the segment
 void lsoc_lowrank(const SegDev& g, int64_t nent, const int32_t* ent_cone, const int32_t* ent_col,
                   const int64_t* ent_dst, const Csr& At, int64_t plus_off, double* Ad, hipStream_t st);
+
+// Up to FUSED_SEGS segments in one launch: workgroups first[q] .. first[q + 1]
+// belong to g[q].
+constexpr int FUSED_SEGS = 8;
+struct SegTable {
+  SegDev g[FUSED_SEGS];
+  int32_t first[FUSED_SEGS + 1];
+  int32_t nseg;
+};
+// PSD cones (hc_psd.hip), over the PSD segments of a list; psd_step and
+// psd_max_neg_eig write at most PSD_STEP_GRID partials per segment and return
+// how many (psd_step per_cone, one segment: one value per cone, at most amax)
+constexpr int PSD_STEP_GRID = 2048;
+void psd_scale(const std::vector<SegDev>& segs, const double* s, const double* z, double* hdiag, hipStream_t st);
+void psd_ds(const std::vector<SegDev>& segs, const double* dsa, const double* dza, double sm, double* ds,
+            hipStream_t st);
+void psd_apply(const std::vector<SegDev>& segs, int mode, double delta, int epi, const ApplySys2& ss, int ns,
+               hipStream_t st);
+int64_t psd_step(const std::vector<SegDev>& segs, const double* s, const double* z, const double* ds, const double* dz,
+                 double amax, bool per_cone, double* out, hipStream_t st);
+int64_t psd_max_neg_eig(const std::vector<SegDev>& segs, const double* v, double* out, hipStream_t st);
+void psd_mblock(const SegDev& g, double delta, double* work, hipStream_t st);
+void psd_identity(const SegDev& g, double* hdiag, hipStream_t st);
 
 constexpr int CONE_BLOCK = 256;
 inline int cone_blocks(const SegDev& g) {

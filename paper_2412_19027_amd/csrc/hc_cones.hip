@@ -416,21 +416,6 @@ __global__ __launch_bounds__(CONE_BLOCK) void k_nonsym_scale(SegDev g, const dou
   }
 }
 
-// PSD kernels run one wave per cone for every side up to 32 (the paper's
-// limit), with the cone's k x k matrices in LDS (the wave kernels below).  The
-// spectral apply comes in two instantiations, KM = 12 and KM = 32, which size
-// its LDS arrays.
-constexpr int PSD_KSMALL = 12, PSD_KLARGE = 32;
-
-
-// PSD scaling and d_s correction, one wave per cone (defined with the other
-// wave kernels below)
-__global__ __launch_bounds__(64) void k_psd_scale_wave(SegDev g, const double* __restrict__ s,
-                                                       const double* __restrict__ z, double* __restrict__ hdiag);
-__global__ __launch_bounds__(64) void k_psd_ds_wave(SegDev g, const double* __restrict__ dsa,
-                                                    const double* __restrict__ dza, double sm,
-                                                    double* __restrict__ ds);
-
 void cone_scale(const SegDev& g, const double* s, const double* z, double mu, int force_dual, double* hdiag,
                 int* pd_count, hipStream_t st) {
   if (g.count == 0) return;
@@ -453,14 +438,11 @@ void cone_scale(const SegDev& g, const double* s, const double* z, double mu, in
                          pd_count);
       break;
     case HC_CONE_PSD:
-      hipLaunchKernelGGL(k_psd_scale_wave, dim3((unsigned)std::min<int64_t>(g.count, 4096)), dim3(64), 0, st, g, s, z,
-                         hdiag);
-      break;
+      psd_scale({g}, s, z, hdiag, st);
+      return;
   }
   HC_LAUNCH_CHECK();
 }
-
-constexpr int FUSED_SEGS = 8;
 
 // ===========================================================================
 // spectral application of H or (H + delta I)^-1, and the explicit inverse block
@@ -529,11 +511,6 @@ __device__ inline double epilogue(const ApplySys& s, int64_t r, double v) {
 
 // every lane-per-cone segment in one launch: block b belongs to the segment s
 // with first[s] <= b < first[s + 1]
-struct SegTable {
-  SegDev g[FUSED_SEGS];
-  int32_t first[FUSED_SEGS + 1];
-  int32_t nseg;
-};
 constexpr int SEG_ROWS = -1;     // SegDev::kind of rows whose v is in y already
 constexpr int SEG_BLOCKS = 1024; // blocks per segment of k_cone_apply_fused
 
@@ -569,81 +546,6 @@ __global__ __launch_bounds__(CONE_BLOCK) void k_cone_apply_fused(SegTable tb, in
   }
 }
 
-// Spectral application, one workgroup per cone (one lane per cone would pay
-// k^3 dependent LDS round trips for each of the four k x k products): one
-// wave up to side 12, four above.  The threads split every product by output
-// entry; Q, X and the two intermediate products live in LDS (row stride
-// KM + 1).  blockIdx.y selects the vector.
-template <int KM>
-__global__ __launch_bounds__(KM <= 12 ? 64 : 256) void k_psd_apply_wave(SegDev g, int mode, double delta, int epi, ApplySys2 ss) {
-  constexpr int LD = KM + 1;
-  __shared__ double Q[KM * LD], X[KM * LD], T[KM * LD], U[KM * LD], m[KM];
-  const int k = g.k, lane = threadIdx.x, sd = g.dim;
-  const int64_t N = g.count, kk = (int64_t)k * k;
-  constexpr int NT = KM <= 12 ? 64 : 256;   // four waves per cone above side 12
-  const ApplySys& sy = ss.s[blockIdx.y];
-  for (int64_t c = blockIdx.x; c < N; c += gridDim.x) {
-    const double* xc = sy.x + g.base + c * sd;
-    __syncthreads();   // the previous cone's readers are done
-    for (int e = lane; e < k * k; e += NT) Q[(e / k) * LD + e % k] = g.state[(2 * kk + e) * N + c];
-    for (int e = lane; e < k; e += NT) m[e] = g.state[(3 * kk + k + e) * N + c];
-    for (int p = lane; p < sd; p += NT) {   // smat: svec entry p is (i, j), i <= j, column by column
-      int j = (int)((sqrt(8.0 * p + 1.0) - 1.0) / 2.0);
-      while (j * (j + 1) / 2 > p) --j;
-      while ((j + 1) * (j + 2) / 2 <= p) ++j;
-      const int i = p - j * (j + 1) / 2;
-      const double v = xc[p] * (i == j ? 1.0 : 0.70710678118654752440);
-      X[i * LD + j] = v;
-      X[j * LD + i] = v;
-    }
-    __syncthreads();
-    for (int e = lane; e < k * k; e += NT) {   // T = X Q
-      const int i = e / k, j = e % k;
-      double acc = 0;
-      for (int p = 0; p < k; ++p) acc += X[i * LD + p] * Q[p * LD + j];
-      T[i * LD + j] = acc;
-    }
-    __syncthreads();
-    for (int e = lane; e < k * k; e += NT) {   // U = Q' T
-      const int i = e / k, j = e % k;
-      double acc = 0;
-      for (int p = 0; p < k; ++p) acc += Q[p * LD + i] * T[p * LD + j];
-      U[i * LD + j] = acc;
-    }
-    __syncthreads();
-    // average the two roundings of each eigen-coefficient, then scale
-    for (int e = lane; e < k * k; e += NT) {
-      const int i = e / k, j = e % k;
-      const double lam = m[i] * m[j];
-      T[i * LD + j] = 0.5 * (U[i * LD + j] + U[j * LD + i]) * (mode == 0 ? lam : 1.0 / (lam + delta));
-    }
-    __syncthreads();
-    for (int e = lane; e < k * k; e += NT) {   // U = T Q'
-      const int i = e / k, j = e % k;
-      double acc = 0;
-      for (int p = 0; p < k; ++p) acc += T[i * LD + p] * Q[j * LD + p];
-      U[i * LD + j] = acc;
-    }
-    __syncthreads();
-    for (int e = lane; e < k * k; e += NT) {   // X = Q U
-      const int i = e / k, j = e % k;
-      double acc = 0;
-      for (int p = 0; p < k; ++p) acc += Q[i * LD + p] * U[p * LD + j];
-      X[i * LD + j] = acc;
-    }
-    __syncthreads();
-    for (int p = lane; p < sd; p += NT) {   // svec of the upper triangle
-      int j = (int)((sqrt(8.0 * p + 1.0) - 1.0) / 2.0);
-      while (j * (j + 1) / 2 > p) --j;
-      while ((j + 1) * (j + 2) / 2 <= p) ++j;
-      const int i = p - j * (j + 1) / 2;
-      const double v = X[i * LD + j] * (i == j ? 1.0 : 1.41421356237309504880);
-      const int64_t r = g.base + c * sd + p;
-      sy.y[r] = epi == EPI_NEG ? -sy.a[r] - v : v;
-    }
-  }
-}
-
 bool lane_per_cone(const SegDev& g) {
   return g.count > 0 && g.kind != HC_CONE_PSD && !soc_large(g.kind, g.dim);
 }
@@ -667,15 +569,9 @@ void cone_apply_sys(const std::vector<SegDev>& segs, int mode, double delta, int
     if (g.count == 0) continue;
     if (soc_large(g.kind, g.dim)) {
       for (int r = 0; r < ns; ++r) lsoc_apply(g, mode, delta, sys[r].x, epi == EPI_NEG ? sys[r].a : nullptr, sys[r].y, st);
-    } else if (g.kind == HC_CONE_PSD) {
-      const dim3 grid((unsigned)std::min<int64_t>(g.count, 4096), (unsigned)ns);
-      if (g.k <= PSD_KSMALL)
-        hipLaunchKernelGGL(k_psd_apply_wave<PSD_KSMALL>, grid, dim3(64), 0, st, g, mode, delta, epi, ss);
-      else
-        hipLaunchKernelGGL(k_psd_apply_wave<PSD_KLARGE>, grid, dim3(256), 0, st, g, mode, delta, epi, ss);
-      HC_LAUNCH_CHECK();
     }
   }
+  psd_apply(segs, mode, delta, epi, ss, ns, st);
   SegTable tb{};
   int nb = 0;
   auto flush = [&]() {
@@ -727,6 +623,7 @@ __global__ __launch_bounds__(CONE_BLOCK) void k_sym_scale_fused(SegTable tb, con
 
 void cone_scale_all(const std::vector<SegDev>& segs, const double* s, const double* z, double mu, int force_dual,
                     double* hdiag, int* pd_count, hipStream_t st) {
+  psd_scale(segs, s, z, hdiag, st);
   SegTable tb{};
   int nb = 0;
   auto flush = [&]() {
@@ -740,8 +637,8 @@ void cone_scale_all(const std::vector<SegDev>& segs, const double* s, const doub
   for (const SegDev& g : segs) {
     if (g.count == 0) continue;
     const bool sym = g.kind == HC_CONE_ZERO || g.kind == HC_CONE_NONNEG || (g.kind == HC_CONE_SOC && !soc_large(g.kind, g.dim));
-    if (!sym) {   // exp/pow (primal-dual or dual scaling), PSD, large SOC: their own kernels
-      cone_scale(g, s, z, mu, force_dual, hdiag, pd_count, st);
+    if (!sym) {   // exp/pow (primal-dual or dual scaling), large SOC: their own kernels
+      if (g.kind != HC_CONE_PSD) cone_scale(g, s, z, mu, force_dual, hdiag, pd_count, st);
       continue;
     }
     if (tb.nseg == FUSED_SEGS) flush();
@@ -755,58 +652,6 @@ void cone_scale_all(const std::vector<SegDev>& segs, const double* s, const doub
 
 // explicit lower-triangle entries of M = (H + delta I)^-1, packed index
 // p = a (a + 1) / 2 + b for a >= b, stored mblk[p * count + cone]
-//
-// PSD: with f(i,j) = 1/(m_i m_j + delta) and svec index a = (ia, ja),
-//   M_ab = (c_a c_b / 2) sum_i Q[ia][i] (Q[ib][i] G_i[ja][jb] + Q[jb][i] G_i[ja][ib]),
-//   G_i[q][s] = sum_j f(i,j) Q[q][j] Q[s][j],
-// (c = 1 on the diagonal, sqrt2 off it), which is sum_e svec(E_e)_a svec(E_e)_b f_e
-// over the eigenvectors E_e = (q_i q_j' + q_j q_i')/sqrt2 of H, expanded by the
-// Kronecker structure: k^4 flops for the G_i and 2k per entry instead of k(k+1)/2
-// per entry.  G (k^3 per cone) lives in the caller's work buffer.
-__global__ __launch_bounds__(256) void k_psd_mblock_g(SegDev g, double delta, double* __restrict__ G) {
-  __shared__ double Q[PSD_KLARGE * (PSD_KLARGE + 1)], m[PSD_KLARGE];
-  const int k = g.k, LQ = PSD_KLARGE + 1;
-  const int64_t N = g.count, kk = (int64_t)k * k, c = blockIdx.x;
-  const int i = blockIdx.y;
-  for (int e = threadIdx.x; e < k * k; e += blockDim.x) Q[(e / k) * LQ + e % k] = g.state[(2 * kk + e) * N + c];
-  for (int e = threadIdx.x; e < k; e += blockDim.x) m[e] = g.state[(3 * kk + k + e) * N + c];
-  __syncthreads();
-  double* Gi = G + (c * k + i) * kk;
-  for (int e = threadIdx.x; e < k * k; e += blockDim.x) {
-    const int q = e / k, sx = e % k;
-    double acc = 0;
-    for (int j = 0; j < k; ++j) acc += Q[q * LQ + j] * Q[sx * LQ + j] / (m[i] * m[j] + delta);
-    Gi[e] = acc;
-  }
-}
-
-__device__ inline void tri_index(int e, int& i, int& j);
-
-// one thread per (cone, packed entry p = a (a + 1) / 2 + b): the grid's y
-// dimension covers a cone's entries, so even a few large cones fill the chip
-__global__ __launch_bounds__(256) void k_psd_mblock(SegDev g, const double* __restrict__ G) {
-  __shared__ double Q[PSD_KLARGE * (PSD_KLARGE + 1)];
-  const int k = g.k, LQ = PSD_KLARGE + 1, sd = g.dim;
-  const int64_t N = g.count, kk = (int64_t)k * k, c = blockIdx.x;
-  for (int e = threadIdx.x; e < k * k; e += blockDim.x) Q[(e / k) * LQ + e % k] = g.state[(2 * kk + e) * N + c];
-  __syncthreads();
-  const int np = sd * (sd + 1) / 2;
-  const int p = (int)blockIdx.y * (int)blockDim.x + (int)threadIdx.x;
-  if (p >= np) return;
-  int a, b, ja, ia, jb, ib;
-  tri_index(p, a, b);
-  tri_index(a, ja, ia);
-  tri_index(b, jb, ib);
-  const double ca = (ia == ja) ? 1.0 : 1.41421356237309504880, cb = (ib == jb) ? 1.0 : 1.41421356237309504880;
-  const double* Gc = G + c * k * kk + (int64_t)ja * k;
-  double acc = 0;
-  for (int i = 0; i < k; ++i) {
-    const double* Gi = Gc + (int64_t)i * kk;
-    acc += Q[ia * LQ + i] * (Q[ib * LQ + i] * Gi[jb] + Q[jb * LQ + i] * Gi[ib]);
-  }
-  g.mblk[(int64_t)p * N + c] = 0.5 * ca * cb * acc;
-}
-
 __device__ inline void cone_mblock_one(const SegDev& g, int64_t i, double delta) {
   const int64_t N = g.count;
   switch (g.kind) {
@@ -878,10 +723,8 @@ int64_t cone_mblock_work(const SegDev& g) {
 void cone_mblock(const SegDev& g, double delta, double* work, hipStream_t st) {
   if (g.count == 0) return;
   if (g.kind == HC_CONE_PSD) {
-    hipLaunchKernelGGL(k_psd_mblock_g, dim3((unsigned)g.count, (unsigned)g.k), dim3(256), 0, st, g, delta, work);
-    HC_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_psd_mblock, dim3((unsigned)g.count, (unsigned)ceil_div((int64_t)g.dim * (g.dim + 1) / 2, 256)),
-                       dim3(256), 0, st, g, (const double*)work);
+    psd_mblock(g, delta, work, st);
+    return;
   } else
     hipLaunchKernelGGL(k_cone_mblock, dim3((unsigned)std::max<int64_t>(1, ceil_div(g.count, CONE_BLOCK))),
                        dim3(CONE_BLOCK), 0, st, g, delta);
@@ -968,7 +811,7 @@ __device__ inline void cone_ds_one(const SegDev& g, int64_t i, const double* __r
       break;
     }
     default:
-      break;   // PSD: k_psd_ds_wave; large SOC: lsoc_ds
+      break;   // PSD: psd_ds; large SOC: lsoc_ds
   }
 }
 
@@ -990,6 +833,7 @@ __global__ __launch_bounds__(CONE_BLOCK) void k_cone_ds_fused(SegTable tb, const
 
 void cone_ds_all(const std::vector<SegDev>& segs, const double* s, const double* z, const double* dsa,
                  const double* dza, double sm, double* ds, hipStream_t st) {
+  psd_ds(segs, dsa, dza, sm, ds, st);
   SegTable tb{};
   int nb = 0;
   auto flush = [&]() {
@@ -1003,7 +847,7 @@ void cone_ds_all(const std::vector<SegDev>& segs, const double* s, const double*
   for (const SegDev& g : segs) {
     if (g.count == 0) continue;
     if (!lane_per_cone(g)) {
-      cone_ds_combined(g, s, z, dsa, dza, sm, ds, st);
+      if (g.kind != HC_CONE_PSD) cone_ds_combined(g, s, z, dsa, dza, sm, ds, st);
       continue;
     }
     if (tb.nseg == FUSED_SEGS) flush();
@@ -1021,8 +865,7 @@ void cone_ds_combined(const SegDev& g, const double* s, const double* z, const d
   if (soc_large(g.kind, g.dim))
     lsoc_ds(g, dsa, dza, sm, ds, st);
   else if (g.kind == HC_CONE_PSD)
-    hipLaunchKernelGGL(k_psd_ds_wave, dim3((unsigned)std::min<int64_t>(g.count, 4096)), dim3(64), 0, st, g, dsa, dza,
-                       sm, ds);
+    psd_ds({g}, dsa, dza, sm, ds, st);
   else
     hipLaunchKernelGGL(k_cone_ds, dim3(cone_blocks(g)), dim3(CONE_BLOCK), 0, st, g, s, z, dsa, dza, sm, ds);
   HC_LAUNCH_CHECK();
@@ -1093,397 +936,11 @@ __global__ __launch_bounds__(CONE_BLOCK) void k_step_sym_fused(SegTable tb, cons
   block_min_to(i < tb.g[q].count ? step_sym_one(tb.g[q], i, s, z, ds, dz) : INFINITY, partial);
 }
 
-// PSD: grid-stride over the cones with at most PSD_STEP_GRID blocks, one
-// partial minimum per block
-constexpr int PSD_STEP_GRID = 2048;
-
-// ---------------------------------------------------------------------------
-// One wave per cone for the Jacobi-based PSD kernels (every side).  The k
-// indices (padded to an even count kk with one that never rotates) are paired
-// round-robin (circle method: index kk - 1 fixed, the others turning), so the
-// kk/2 pairs of a round are disjoint and their rotations are applied at once;
-// a sweep is kk - 1 rounds.  Matrices sit in LDS, row stride PW_LD.
-// ---------------------------------------------------------------------------
-constexpr int PW_LD = PSD_KLARGE + 1;
-constexpr int PW_MAT = PSD_KLARGE * PW_LD;
-
-__device__ inline void rr_pair(int kk, int r, int i, int& p, int& q) {
-  if (i == 0) {
-    p = kk - 1;
-    q = r;
-  } else {
-    p = (r + i) % (kk - 1);
-    q = (r - i + (kk - 1)) % (kk - 1);
-  }
-  if (p > q) {
-    const int t = p;
-    p = q;
-    q = t;
-  }
-}
-
-// (i, j) of entry e of the packed triangle i >= j (row by row)
-__device__ inline void tri_index(int e, int& i, int& j) {
-  i = (int)((sqrt(8.0 * e + 1.0) - 1.0) / 2.0);
-  while (i * (i + 1) / 2 > e) --i;
-  while ((i + 1) * (i + 2) / 2 <= e) ++i;
-  j = e - i * (i + 1) / 2;
-}
-
-__device__ inline double wave_sum(double v) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-__device__ inline double wave_min(double v) {
-  for (int off = 32; off > 0; off >>= 1) v = fmin(v, __shfl_xor(v, off, 64));
-  return v;
-}
-
-// X = smat(v) (k x k, symmetric)
-__device__ inline void wave_smat(const double* v, int k, double* X, int lane) {
-  const int sd = k * (k + 1) / 2;
-  for (int p = lane; p < sd; p += 64) {
-    int j, i;
-    tri_index(p, j, i);   // svec: column j, rows i <= j
-    const double x = v[p] * (i == j ? 1.0 : 0.70710678118654752440);
-    X[i * PW_LD + j] = x;
-    X[j * PW_LD + i] = x;
-  }
-}
-
-// lower Cholesky in place (upper part zeroed); false (on every lane) when a
-// pivot is not positive
-__device__ bool wave_chol(double* A, int k, int lane) {
-  for (int j = 0; j < k; ++j) {
-    __syncthreads();
-    const double d = A[j * PW_LD + j];
-    if (!(d > 0.0)) return false;
-    const double r = sqrt(d);
-    __syncthreads();
-    if (lane == 0) A[j * PW_LD + j] = r;
-    for (int i = j + 1 + lane; i < k; i += 64) A[i * PW_LD + j] /= r;
-    __syncthreads();
-    const int t = k - j - 1;
-    for (int e = lane; e < t * (t + 1) / 2; e += 64) {
-      int i, l;
-      tri_index(e, i, l);
-      i += j + 1;
-      l += j + 1;
-      A[i * PW_LD + l] -= A[i * PW_LD + j] * A[l * PW_LD + j];
-    }
-  }
-  __syncthreads();
-  for (int e = lane; e < k * k; e += 64)
-    if (e / k < e % k) A[(e / k) * PW_LD + e % k] = 0.0;
-  __syncthreads();
-  return true;
-}
-
-// smallest eigenvalue of the symmetric A (destroyed): parallel cyclic Jacobi.
-// An off-diagonal entry at most 1e-18 |A|_F moves no eigenvalue by more than
-// rounding does, so it is not rotated; the sweeps end on a sweep without
-// rotations (quadratic convergence: a handful), or after 60.
-__device__ double wave_min_eig(double* A, int k, int lane, double* rc, double* rs, int* rp, int* rq, int* flag) {
-  double tot = 0;
-  for (int e = lane; e < k * k; e += 64) tot += sq(A[(e / k) * PW_LD + e % k]);
-  const double small = 1e-18 * sqrt(wave_sum(tot));
-  const int kk = (k + 1) & ~1, np = kk / 2;
-  for (int sweep = 0; sweep < 60; ++sweep) {
-    __syncthreads();
-    if (lane == 0) *flag = 0;
-    for (int r = 0; r < kk - 1; ++r) {
-      __syncthreads();
-      if (lane < np) {
-        int p, q;
-        rr_pair(kk, r, lane, p, q);
-        double c = 1.0, sn = 0.0;
-        if (q < k) {
-          const double apq = A[p * PW_LD + q];
-          if (fabs(apq) > small) {
-            const double theta = (A[q * PW_LD + q] - A[p * PW_LD + p]) / (2.0 * apq);
-            const double t = copysign(1.0, theta) / (fabs(theta) + sqrt(1.0 + theta * theta));
-            c = 1.0 / sqrt(1.0 + t * t);
-            sn = c * t;
-            *flag = 1;
-          }
-        }
-        rp[lane] = p;
-        rq[lane] = q;
-        rc[lane] = c;
-        rs[lane] = sn;
-      }
-      __syncthreads();
-      for (int e = lane; e < k * np; e += 64) {   // A <- A J: columns p, q of every pair
-        const int row = e / np, pi = e % np, p = rp[pi], q = rq[pi];
-        if (q >= k || rs[pi] == 0.0) continue;
-        const double arp = A[row * PW_LD + p], arq = A[row * PW_LD + q];
-        A[row * PW_LD + p] = rc[pi] * arp - rs[pi] * arq;
-        A[row * PW_LD + q] = rs[pi] * arp + rc[pi] * arq;
-      }
-      __syncthreads();
-      for (int e = lane; e < k * np; e += 64) {   // A <- J' A: rows p, q
-        const int col = e / np, pi = e % np, p = rp[pi], q = rq[pi];
-        if (q >= k || rs[pi] == 0.0) continue;
-        const double apc = A[p * PW_LD + col], aqc = A[q * PW_LD + col];
-        A[p * PW_LD + col] = rc[pi] * apc - rs[pi] * aqc;
-        A[q * PW_LD + col] = rs[pi] * apc + rc[pi] * aqc;
-      }
-    }
-    __syncthreads();
-    if (!*flag) break;
-  }
-  double m = INFINITY;
-  for (int i = lane; i < k; i += 64) m = fmin(m, A[i * PW_LD + i]);
-  return wave_min(m);
-}
-
-// one-sided Jacobi (Hestenes) on the columns of B (k x k): on return the
-// columns are orthogonal and W accumulates B_in W = B_out.  Four lanes per
-// pair, each summing and rotating rows sub, sub + 4, ...; a pair is skipped
-// when |b_p'b_q| <= 1e-16 |b_p||b_q| (as the exp/pow Jacobi does).
-__device__ void wave_jacobi_cols(double* B, int k, double* W, int lane, int* flag) {
-  for (int e = lane; e < k * k; e += 64) W[(e / k) * PW_LD + e % k] = (e / k == e % k) ? 1.0 : 0.0;
-  const int kk = (k + 1) & ~1, np = kk / 2, grp = lane >> 2, sub = lane & 3;
-  for (int sweep = 0; sweep < 60; ++sweep) {
-    __syncthreads();
-    if (lane == 0) *flag = 0;
-    for (int r = 0; r < kk - 1; ++r) {
-      __syncthreads();
-      if (grp >= np) continue;
-      int p, q;
-      rr_pair(kk, r, grp, p, q);
-      if (q >= k) continue;
-      double a = 0, b = 0, gg = 0;
-      for (int row = sub; row < k; row += 4) {
-        const double bp = B[row * PW_LD + p], bq = B[row * PW_LD + q];
-        a += bp * bp;
-        b += bq * bq;
-        gg += bp * bq;
-      }
-      for (int off = 1; off < 4; off <<= 1) {
-        a += __shfl_xor(a, off, 64);
-        b += __shfl_xor(b, off, 64);
-        gg += __shfl_xor(gg, off, 64);
-      }
-      if (gg == 0.0 || fabs(gg) <= 1e-15 * sqrt(a * b)) continue;   // orthogonal to a few ulps
-      const double zeta = (b - a) / (2.0 * gg);
-      const double t = copysign(1.0, zeta) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-      const double cs = 1.0 / sqrt(1.0 + t * t), sn = cs * t;
-      for (int row = sub; row < k; row += 4) {
-        const double bp = B[row * PW_LD + p], bq = B[row * PW_LD + q];
-        B[row * PW_LD + p] = cs * bp - sn * bq;
-        B[row * PW_LD + q] = sn * bp + cs * bq;
-        const double wp = W[row * PW_LD + p], wq = W[row * PW_LD + q];
-        W[row * PW_LD + p] = cs * wp - sn * wq;
-        W[row * PW_LD + q] = sn * wp + cs * wq;
-      }
-      if (sub == 0) *flag = 1;
-    }
-    __syncthreads();
-    if (!*flag) break;
-  }
-  __syncthreads();
-}
-
-// C = op(X) op(Y) over the wave (entry per lane); tx / ty transpose X / Y
-__device__ inline void wave_mm(const double* X, bool tx, const double* Y, bool ty, int k, double* C, int lane) {
-  for (int e = lane; e < k * k; e += 64) {
-    const int i = e / k, j = e % k;
-    double acc = 0;
-    for (int p = 0; p < k; ++p)
-      acc += (tx ? X[p * PW_LD + i] : X[i * PW_LD + p]) * (ty ? Y[j * PW_LD + p] : Y[p * PW_LD + j]);
-    C[i * PW_LD + j] = acc;
-  }
-  __syncthreads();
-}
-
-// PSD scaling, one wave per cone: Cholesky factors L_s, L_z; the SVD of
-// L_z' L_s = U diag(lam) V' gives R = L_s V lam^-1/2 and R^-1 = lam^-1/2 U' L_z';
-// a second one-sided Jacobi on R' gives M = R R' = Q diag(m) Q'.  State
-// fields: R (k*k row-major) | R^-1 | Q | lambda (k) | m (k)
-__global__ __launch_bounds__(64) void k_psd_scale_wave(SegDev g, const double* __restrict__ s,
-                                                       const double* __restrict__ z, double* __restrict__ hdiag) {
-  __shared__ double Ls[PW_MAT], Lz[PW_MAT], B[PW_MAT], W[PW_MAT], R[PW_MAT], Ri[PW_MAT], lam[PSD_KLARGE],
-      m[PSD_KLARGE];
-  __shared__ int flag;
-  const int lane = threadIdx.x, k = g.k, sd = g.dim;
-  const int64_t N = g.count, kk = (int64_t)k * k;
-  for (int64_t c = blockIdx.x; c < N; c += gridDim.x) {
-    __syncthreads();
-    wave_smat(s + g.base + c * sd, k, Ls, lane);
-    wave_smat(z + g.base + c * sd, k, Lz, lane);
-    wave_chol(Ls, k, lane);
-    wave_chol(Lz, k, lane);
-    wave_mm(Lz, true, Ls, false, k, B, lane);   // B = Lz' Ls
-    wave_jacobi_cols(B, k, W, lane, &flag);     // B W = U diag(lam), V = W
-    if (lane < k) {
-      double acc = 0;
-      for (int r = 0; r < k; ++r) acc += B[r * PW_LD + lane] * B[r * PW_LD + lane];
-      lam[lane] = sqrt(acc);
-    }
-    __syncthreads();
-    // R = Ls V lam^-1/2 ; Rinv = lam^-1/2 U' Lz' with U = B diag(1/lam)
-    for (int e = lane; e < k * k; e += 64) {
-      const int i = e / k, j = e % k;
-      double acc = 0, acc2 = 0;
-      for (int p = 0; p < k; ++p) {
-        acc += Ls[i * PW_LD + p] * W[p * PW_LD + j];
-        acc2 += (B[p * PW_LD + i] / lam[i]) * Lz[j * PW_LD + p];
-      }
-      R[i * PW_LD + j] = acc / sqrt(lam[j]);
-      Ri[i * PW_LD + j] = acc2 / sqrt(lam[i]);
-    }
-    __syncthreads();
-    // M = R R' = Q diag(m) Q': one-sided Jacobi on the columns of R' (in Ls) gives Q (in W)
-    for (int e = lane; e < k * k; e += 64) Ls[(e / k) * PW_LD + e % k] = R[(e % k) * PW_LD + e / k];
-    __syncthreads();
-    wave_jacobi_cols(Ls, k, W, lane, &flag);
-    if (lane < k) {
-      double acc = 0;
-      for (int r = 0; r < k; ++r) acc += Ls[r * PW_LD + lane] * Ls[r * PW_LD + lane];
-      m[lane] = acc;
-    }
-    for (int e = lane; e < k * k; e += 64) {
-      const int i = e / k, j = e % k;
-      g.state[(int64_t)e * N + c] = R[i * PW_LD + j];
-      g.state[(kk + e) * N + c] = Ri[i * PW_LD + j];
-      g.state[(2 * kk + e) * N + c] = W[i * PW_LD + j];
-    }
-    __syncthreads();
-    if (lane < k) {
-      g.state[(3 * kk + lane) * N + c] = lam[lane];
-      g.state[(3 * kk + k + lane) * N + c] = m[lane];
-    }
-    wave_mm(R, false, R, true, k, B, lane);     // Mm = R R'
-    for (int p = lane; p < sd; p += 64) {       // diag of H in svec coordinates
-      int b, a;
-      tri_index(p, b, a);
-      const double v = (a == b) ? sq(B[a * PW_LD + a])
-                                : (B[a * PW_LD + a] * B[b * PW_LD + b] + sq(B[a * PW_LD + b]));
-      hdiag[g.base + c * sd + p] = v;
-    }
-  }
-}
-
-// combined-step d_s of a PSD cone (as k_psd_ds), one wave per cone:
-//   A = R^-1 dS R^-T, B = R' dZ R, V = (A B + B A)/2 + diag(lam^2) - sm I,
-//   X_ij = 2 V_ij / (lam_i + lam_j), ds = svec(R X R')
-__global__ __launch_bounds__(64) void k_psd_ds_wave(SegDev g, const double* __restrict__ dsa,
-                                                    const double* __restrict__ dza, double sm,
-                                                    double* __restrict__ ds) {
-  __shared__ double R[PW_MAT], Ri[PW_MAT], dS[PW_MAT], dZ[PW_MAT], T1[PW_MAT], Aa[PW_MAT], Bb[PW_MAT],
-      lam[PSD_KLARGE];
-  const int lane = threadIdx.x, k = g.k, sd = g.dim;
-  const int64_t N = g.count, kk = (int64_t)k * k;
-  for (int64_t c = blockIdx.x; c < N; c += gridDim.x) {
-    __syncthreads();
-    for (int e = lane; e < k * k; e += 64) {
-      R[(e / k) * PW_LD + e % k] = g.state[(int64_t)e * N + c];
-      Ri[(e / k) * PW_LD + e % k] = g.state[(kk + e) * N + c];
-    }
-    if (lane < k) lam[lane] = g.state[(3 * kk + lane) * N + c];
-    wave_smat(dsa + g.base + c * sd, k, dS, lane);
-    wave_smat(dza + g.base + c * sd, k, dZ, lane);
-    __syncthreads();
-    wave_mm(Ri, false, dS, false, k, T1, lane);   // Ri dS
-    wave_mm(T1, false, Ri, true, k, Aa, lane);    // (Ri dS) Ri'
-    wave_mm(R, true, dZ, false, k, T1, lane);     // R' dZ
-    wave_mm(T1, false, R, false, k, Bb, lane);    // (R' dZ) R
-    // V on the upper triangle, mirrored, so X is exactly symmetric before the
-    // large 1/(lam_i + lam_j) factors
-    for (int e = lane; e < k * k; e += 64) {
-      const int r = e / k, j = e % k;
-      if (j < r) continue;
-      double acc = 0;
-      for (int p = 0; p < k; ++p)
-        acc += Aa[r * PW_LD + p] * Bb[p * PW_LD + j] + Bb[r * PW_LD + p] * Aa[p * PW_LD + j];
-      double v = 0.5 * acc;
-      if (r == j) v += lam[r] * lam[r] - sm;
-      const double x = 2.0 * v / (lam[r] + lam[j]);
-      dS[r * PW_LD + j] = x;   // dS and dZ are free now
-      dS[j * PW_LD + r] = x;
-    }
-    __syncthreads();
-    wave_mm(R, false, dS, false, k, T1, lane);    // R X
-    wave_mm(T1, false, R, true, k, dZ, lane);     // (R X) R'
-    for (int p = lane; p < sd; p += 64) {
-      int j, i;
-      tri_index(p, j, i);
-      ds[g.base + c * sd + p] = dZ[i * PW_LD + j] * (i == j ? 1.0 : 1.41421356237309504880);
-    }
-  }
-}
-
-// largest alpha with x + alpha dx PSD (INFINITY if unbounded): Cholesky
-// L L' = x, then the smallest eigenvalue of L^-1 dx L^-T
-__device__ double wave_step_one(const double* x, const double* dx, int k, int lane, double* L, double* D, double* T,
-                                double* rc, double* rs, int* rp, int* rq, int* flag) {
-  __syncthreads();
-  wave_smat(x, k, L, lane);
-  wave_smat(dx, k, D, lane);
-  if (!wave_chol(L, k, lane)) return 0.0;
-  // Y = L^-1 D (lane j owns column j), then Z = L^-1 Y', T = (Z + Z')/2
-  if (lane < k)
-    for (int i = 0; i < k; ++i) {
-      double v = D[i * PW_LD + lane];
-      for (int p = 0; p < i; ++p) v -= L[i * PW_LD + p] * D[p * PW_LD + lane];
-      D[i * PW_LD + lane] = v / L[i * PW_LD + i];
-    }
-  __syncthreads();
-  if (lane < k)
-    for (int i = 0; i < k; ++i) {
-      double v = D[lane * PW_LD + i];
-      for (int p = 0; p < i; ++p) v -= L[i * PW_LD + p] * T[p * PW_LD + lane];
-      T[i * PW_LD + lane] = v / L[i * PW_LD + i];
-    }
-  __syncthreads();
-  for (int e = lane; e < k * k; e += 64) {
-    const int i = e / k, j = e % k;
-    L[i * PW_LD + j] = 0.5 * (T[i * PW_LD + j] + T[j * PW_LD + i]);
-  }
-  const double lmin = wave_min_eig(L, k, lane, rc, rs, rp, rq, flag);
-  return (lmin < 0.0) ? -1.0 / lmin : INFINITY;
-}
-
-// one wave per cone: per-workgroup minimum over its cones, or per cone
-// (capped at amax) when per_cone
-__global__ __launch_bounds__(64) void k_step_psd_wave(SegDev g, const double* __restrict__ s,
-                                                      const double* __restrict__ z, const double* __restrict__ ds,
-                                                      const double* __restrict__ dz, double amax, int per_cone,
-                                                      double* __restrict__ out) {
-  __shared__ double L[PW_MAT], D[PW_MAT], T[PW_MAT], rc[PSD_KLARGE / 2], rs[PSD_KLARGE / 2];
-  __shared__ int rp[PSD_KLARGE / 2], rq[PSD_KLARGE / 2], flag;
-  const int lane = threadIdx.x, sd = g.dim;
-  double best = INFINITY;
-  if (per_cone) {
-    for (int64_t c = blockIdx.x; c < g.count; c += gridDim.x) {
-      const int64_t o = g.base + c * sd;
-      const double a1 = wave_step_one(s + o, ds + o, g.k, lane, L, D, T, rc, rs, rp, rq, &flag);
-      const double a2 = wave_step_one(z + o, dz + o, g.k, lane, L, D, T, rc, rs, rp, rq, &flag);
-      if (lane == 0) out[c] = fmin(amax, fmin(a1, a2));
-    }
-    return;
-  }
-  // the minimum over all cones: the s and z halves of a cone are separate
-  // tasks, so twice as many waves share the chip
-  for (int64_t t = blockIdx.x; t < 2 * g.count; t += gridDim.x) {
-    const int64_t o = g.base + (t >> 1) * sd;
-    const bool zh = (t & 1) != 0;
-    best = fmin(best, wave_step_one((zh ? z : s) + o, (zh ? dz : ds) + o, g.k, lane, L, D, T, rc, rs, rp, rq, &flag));
-  }
-  if (lane == 0) out[blockIdx.x] = best;
-}
-
 int cone_step_sym(const SegDev& g, const double* s, const double* z, const double* ds, const double* dz,
                   double* partial, hipStream_t st) {
   if (g.count == 0 || g.kind == HC_CONE_ZERO || g.kind == HC_CONE_EXP || g.kind == HC_CONE_POW) return 0;
   if (soc_large(g.kind, g.dim)) return lsoc_step(g, s, z, ds, dz, INFINITY, false, partial, st);
-  if (g.kind == HC_CONE_PSD) {
-    const int nbp = (int)std::min<int64_t>(2 * g.count, PSD_STEP_GRID);
-    hipLaunchKernelGGL(k_step_psd_wave, dim3(nbp), dim3(64), 0, st, g, s, z, ds, dz, INFINITY, 0, partial);
-    HC_LAUNCH_CHECK();
-    return nbp;
-  }
+  if (g.kind == HC_CONE_PSD) return (int)psd_step({g}, s, z, ds, dz, INFINITY, false, partial, st);
   const int nb = cone_blocks(g);
   hipLaunchKernelGGL(k_step_sym, dim3(nb), dim3(CONE_BLOCK), 0, st, g, s, z, ds, dz, partial);
   HC_LAUNCH_CHECK();
@@ -1492,7 +949,7 @@ int cone_step_sym(const SegDev& g, const double* s, const double* z, const doubl
 
 int64_t cone_step_sym_all(const std::vector<SegDev>& segs, const double* s, const double* z, const double* ds,
                           const double* dz, double* partial, hipStream_t st) {
-  int64_t off = 0;
+  int64_t off = psd_step(segs, s, z, ds, dz, INFINITY, false, partial, st);
   SegTable tb{};
   int nb = 0;
   auto flush = [&]() {
@@ -1508,7 +965,7 @@ int64_t cone_step_sym_all(const std::vector<SegDev>& segs, const double* s, cons
   for (const SegDev& g : segs) {
     if (g.count == 0 || g.kind == HC_CONE_ZERO || g.kind == HC_CONE_EXP || g.kind == HC_CONE_POW) continue;
     if (!lane_per_cone(g)) {
-      off += cone_step_sym(g, s, z, ds, dz, partial + off, st);
+      if (g.kind != HC_CONE_PSD) off += cone_step_sym(g, s, z, ds, dz, partial + off, st);
       continue;
     }
     if (tb.nseg == FUSED_SEGS) flush();
@@ -1678,32 +1135,10 @@ __global__ void k_max_neg_eig(SegDev g, const double* __restrict__ v, double* __
   if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
 }
 
-// PSD: one wave per cone (Jacobi eigenvalues as in the step kernel),
-// grid-stride over the cones, one partial maximum per workgroup
-__global__ __launch_bounds__(64) void k_psd_max_neg_eig_wave(SegDev g, const double* __restrict__ v,
-                                                             double* __restrict__ partial) {
-  __shared__ double X[PW_MAT], rc[PSD_KLARGE / 2], rs[PSD_KLARGE / 2];
-  __shared__ int rp[PSD_KLARGE / 2], rq[PSD_KLARGE / 2], flag;
-  const int lane = threadIdx.x;
-  double a = -INFINITY;
-  for (int64_t c = blockIdx.x; c < g.count; c += gridDim.x) {
-    __syncthreads();
-    wave_smat(v + g.base + c * g.dim, g.k, X, lane);
-    __syncthreads();
-    a = fmax(a, -wave_min_eig(X, g.k, lane, rc, rs, rp, rq, &flag));
-  }
-  if (lane == 0) partial[blockIdx.x] = a;
-}
-
 int cone_max_neg_eig(const SegDev& g, const double* v, double* partial, hipStream_t st) {
   if (g.count == 0 || !(g.kind == HC_CONE_NONNEG || g.kind == HC_CONE_SOC || g.kind == HC_CONE_PSD)) return 0;
   if (soc_large(g.kind, g.dim)) return lsoc_max_neg_eig(g, v, partial, st);
-  if (g.kind == HC_CONE_PSD) {
-    const int nbp = (int)std::min<int64_t>(g.count, PSD_STEP_GRID);
-    hipLaunchKernelGGL(k_psd_max_neg_eig_wave, dim3(nbp), dim3(64), 0, st, g, v, partial);
-    HC_LAUNCH_CHECK();
-    return nbp;
-  }
+  if (g.kind == HC_CONE_PSD) return (int)psd_max_neg_eig({g}, v, partial, st);
   const int nb = cone_blocks(g);
   hipLaunchKernelGGL(k_max_neg_eig, dim3(nb), dim3(CONE_BLOCK), 0, st, g, v, partial);
   HC_LAUNCH_CHECK();
@@ -1761,7 +1196,7 @@ __global__ void k_test_extract(SegDev g, const double* __restrict__ s, int what,
     }
     case HC_CONE_PSD: {
       const int64_t kk = (int64_t)g.k * g.k;
-      for (int j = 0; j < g.dim; ++j) out[i * g.dim + j] = (j < g.k) ? g.state[(3 * kk + j) * N + i] : 0.0;
+      for (int j = 0; j < g.dim; ++j) out[i * g.dim + j] = (j < g.k) ? g.state[i * (3 * kk + 2 * g.k) + 3 * kk + j] : 0.0;
       break;
     }
   }
@@ -1821,9 +1256,7 @@ void cone_test_step(const SegDev& g, const double* s, const double* z, const dou
     return;
   }
   if (g.kind == HC_CONE_PSD) {
-    hipLaunchKernelGGL(k_step_psd_wave, dim3((unsigned)std::min<int64_t>(g.count, PSD_STEP_GRID)), dim3(64), 0, st, g,
-                       s, z, ds, dz, amax, 1, out);
-    HC_LAUNCH_CHECK();
+    psd_step({g}, s, z, ds, dz, amax, true, out, st);
     return;
   }
   hipLaunchKernelGGL(k_test_step, dim3(cone_blocks(g)), dim3(CONE_BLOCK), 0, st, g, s, z, ds, dz, amax, out);

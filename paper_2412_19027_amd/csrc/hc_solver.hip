@@ -2569,21 +2569,6 @@ __global__ void k_identity_state(SegDev g, double* hdiag) {
     }
     g.state[g.dim * N + i] = 1.0;
     if (g.dim > SOC_DMAX) g.state[(2 * (int64_t)g.dim + 1) * N + i] = 0.0;   // |wbar_1|
-  } else if (g.kind == HC_CONE_PSD) {
-    const int k = g.k;
-    const int64_t kk = (int64_t)k * k;
-    for (int r = 0; r < k; ++r)
-      for (int j = 0; j < k; ++j) {
-        const double v = (r == j) ? 1.0 : 0.0;
-        g.state[(r * k + j) * N + i] = v;
-        g.state[(kk + r * k + j) * N + i] = v;
-        g.state[(2 * kk + r * k + j) * N + i] = v;
-      }
-    for (int j = 0; j < k; ++j) {
-      g.state[(3 * kk + j) * N + i] = 1.0;
-      g.state[(3 * kk + k + j) * N + i] = 1.0;
-    }
-    for (int p = 0; p < g.dim; ++p) hdiag[g.base + i * g.dim + p] = 1.0;
   }
 }
 
@@ -2639,6 +2624,11 @@ void init_point(hc_solver* S) {
     return;
   }
   for (auto& g : S->sdev) {
+    if (g.count == 0) continue;
+    if (g.kind == HC_CONE_PSD) {
+      psd_identity(g, S->dhdiag, st);
+      continue;
+    }
     hipLaunchKernelGGL(k_identity_state, dim3(cone_blocks(g)), dim3(CONE_BLOCK), 0, st, g, S->dhdiag);
     HC_LAUNCH_CHECK();
   }
