@@ -311,12 +311,12 @@ void hc_server::wave_worker(int cap) {
       // slot and pool block (the FP64 layout is the mixed one without its FP32
       // buffers), with the regularisation of the mixed mode's FP64 fallback
       // factorisation; its iterations and one fallback are added to the report
-      if (launched && j->plan->mixed &&
+      if (launched && j->plan->own.mixed &&
           (inf.status == HC_STATUS_NUMERICAL_ERROR || inf.status == HC_STATUS_INSUFFICIENT_PROGRESS)) {
-        j->plan->mixed = false;
-        j->plan->st.static_reg = 1e-8;
-        j->plan->st.dyn_reg = std::ldexp(1.0, -104);
-        j->plan->st.ir_mu_frac = 0.0;
+        j->plan->own.mixed = false;
+        j->plan->own.st.static_reg = 1e-8;
+        j->plan->own.st.dyn_reg = std::ldexp(1.0, -104);
+        j->plan->own.st.ir_mu_frac = 0.0;
         j->first_iterations = inf.iterations;
         wave_upload(*j->plan, pool_base + j->offset, &hdesc[i], st);
         restarted = true;

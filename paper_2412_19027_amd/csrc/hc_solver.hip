@@ -3341,18 +3341,10 @@ bool wave_plan(const hc_solver* S, WavePlan* out, std::string* why) {
       if (i >= j) P.Pband[(size_t)j * W + (i - j)] += S->P.v[k];
     }
   }
-  P.q.resize(n);
   P.D.resize(n);
-  for (int32_t i = 0; i < n; ++i) {
-    P.q[i] = S->q[order[i]];
-    P.D[i] = S->D[order[i]];
-  }
-  P.b.resize(m);
+  for (int32_t i = 0; i < n; ++i) P.D[i] = S->D[order[i]];
   P.E.resize(m);
-  for (int32_t r = 0; r < m; ++r) {
-    P.b[r] = S->b[srow_of[r]];
-    P.E[r] = S->E[srow_of[r]];
-  }
+  for (int32_t r = 0; r < m; ++r) P.E[r] = S->E[srow_of[r]];
   // A'MA: every zero row has the same M = 1/delta, so their products are
   // summed per band entry here (in row order) into Zband; the nonneg rows' and
   // cones' products A_pi A_qj M_pq (p = q for a nonneg row) are listed per
@@ -3418,15 +3410,62 @@ bool wave_plan(const hc_solver* S, WavePlan* out, std::string* why) {
       P.tc[o] = tt.c;
     }
   }
-  P.cscale = S->cscale;
-  P.bnorm = S->bnorm_user;
-  P.qnorm = S->qnorm_user;
-  P.maxPdiag = S->maxPdiag;
-  P.nu = S->nu;
-  P.st = S->st;
-  P.mixed = S->mixed;
+  P.srow = std::move(srow_of);
+  P.own = wave_own(S, P);
   return true;
 }
+
+WaveOwn wave_own(const hc_solver* S, const WavePlan& P) {
+  WaveOwn o;
+  o.q.resize(P.n);
+  for (int32_t i = 0; i < P.n; ++i) o.q[i] = S->q[P.colperm[i]];
+  o.b.resize(P.m);
+  for (int32_t r = 0; r < P.m; ++r) o.b[r] = S->b[P.srow[r]];
+  o.cscale = S->cscale;
+  o.bnorm = S->bnorm_user;
+  o.qnorm = S->qnorm_user;
+  o.maxPdiag = S->maxPdiag;
+  o.nu = S->nu;
+  o.st = S->st;
+  o.mixed = S->mixed;
+  return o;
+}
+
+template <typename T> static bool same_bits(const std::vector<T>& a, const std::vector<T>& b) {
+  return a.size() == b.size() && (a.empty() || std::memcmp(a.data(), b.data(), a.size() * sizeof(T)) == 0);
+}
+static bool same_csr(const HostCsr& a, const HostCsr& b) {
+  return a.nrows == b.nrows && a.ncols == b.ncols && same_bits(a.rp, b.rp) && same_bits(a.ci, b.ci) && same_bits(a.v, b.v);
+}
+bool wave_same(const hc_solver* a, const hc_solver* b) {
+  if (a == b) return true;
+  if (a->n != b->n || a->m != b->m || a->has_nonsym != b->has_nonsym || a->K1 + a->K2 != b->K1 + b->K2 ||
+      !same_bits(a->drows, b->drows) || a->segs.size() != b->segs.size())
+    return false;
+  for (size_t i = 0; i < a->segs.size(); ++i) {
+    const Segment &x = a->segs[i], &y = b->segs[i];
+    if (x.kind != y.kind || x.dim != y.dim || x.base != y.base || x.count != y.count) return false;
+  }
+  return same_bits(a->perm, b->perm) && same_bits(a->D, b->D) && same_bits(a->E, b->E) && same_csr(a->A, b->A) &&
+         same_csr(a->P, b->P);
+}
+uint64_t wave_hash(const hc_solver* S) {   // sizes and samples of the matrices' values
+  uint64_t h = 1469598103934665603ull;
+  auto mix = [&](uint64_t v) { h = (h ^ v) * 1099511628211ull, h ^= h >> 29; };
+  mix((uint64_t)S->n);
+  mix((uint64_t)S->m);
+  for (const HostCsr* c : {&S->A, &S->P}) {
+    mix(c->v.size());
+    const size_t step = c->v.size() / 256 + 1;
+    for (size_t i = 0; i < c->v.size(); i += step) {
+      uint64_t u;
+      std::memcpy(&u, &c->v[i], sizeof(u));
+      mix(u);
+    }
+  }
+  return h;
+}
+bool wave_mixed(const hc_solver* S) { return S->mixed; }
 
 }  // namespace hc
 

@@ -240,7 +240,7 @@ int reduce_launch(int64_t n, const RedOps& ops, double* partial, hipStream_t st)
 // time) whatever it does; at the large ones each reads its matrix once, as
 // k_spmv does.  With the cone applications of both systems in one launch and
 // the norms read back by k_collect, a small LP (n 300) went from 12.6 to
-// 4.7 ms, an MPC problem of 100 stages from 26 to 15.5 ms per solve.
+// 4.7 ms, an MPC problem of 100 stages from 31 to 15.5 ms per solve.
 // ---------------------------------------------------------------------------
 RowJob::RowJob(int kind_, const Csr& A, const double* x_, double* y_)
     : kind(kind_), nrows(A.nrows), lanes(A.lanes), long_nnz(A.long_nnz), nlong(A.nlong), rp(A.rowptr), ci(A.col),

@@ -27,6 +27,15 @@ constexpr int WAVE_WB = 64;          // LDS window rows (circular)
 constexpr int WAVE_PB = 8;           // rows fetched ahead per block of steps
 constexpr int WAVE_WMAX = WAVE_WB - WAVE_PB;
 
+// what the problems that share a plan have of their own
+struct WaveOwn {
+  std::vector<double> q, b;              // in the plan's order
+  double cscale = 1, bnorm = 0, qnorm = 0, maxPdiag = 0;
+  int64_t nu = 0;
+  hc_settings st{};
+  bool mixed = false;
+};
+
 // host image of one problem for the engine (columns in band order, rows:
 // zero, then nonnegative, then the second-order cones one after another)
 struct WavePlan {
@@ -36,7 +45,7 @@ struct WavePlan {
   std::vector<int32_t> soc_moff;         // offset of each cone's d x d M block
   int32_t mtot = 0;                      // M entries: one per zero/nonneg row + sum d^2
   std::vector<int32_t> Arp, Aci, Atrp, Atci, Prp, Pci;
-  std::vector<double> Av, Atv, Pv, q, b, D, E;
+  std::vector<double> Av, Atv, Pv, D, E;
   std::vector<double> Pband;             // P in band storage (n x (w + 1), column-major)
   std::vector<double> Zband;             // sum over zero rows of A_r'A_r (their M is 1/delta), same storage
   std::vector<int32_t> te, trp, tm;      // A'MA terms of the nonneg rows and cones: the band entries
@@ -44,15 +53,20 @@ struct WavePlan {
                                          // each a coefficient A_a A_b times M[tm]
   std::vector<int32_t> colperm;          // band column -> user column
   std::vector<int32_t> rowperm;          // engine row -> user row
-  double cscale = 1, bnorm = 0, qnorm = 0, maxPdiag = 0;
-  int64_t nu = 0;
-  hc_settings st{};
-  bool mixed = false;
+  std::vector<int32_t> srow;             // engine row -> row of the handle
+  WaveOwn own;
   size_t blob_bytes() const;             // device bytes of one slot (data + work)
 };
 
 // eligibility and plan from a set-up handle; false with the reason otherwise
 bool wave_plan(const hc_solver* S, WavePlan* out, std::string* why);
+// the two handles' plans differ in `own` alone: equal cones, scaled matrices
+// and scalings (wave_hash: equal for such handles)
+bool wave_same(const hc_solver* a, const hc_solver* b);
+uint64_t wave_hash(const hc_solver* S);
+// S's own part of a plan made from a handle with the same matrices
+WaveOwn wave_own(const hc_solver* S, const WavePlan& P);
+bool wave_mixed(const hc_solver* S);
 // the message hc_last_error(NULL) returns on this thread
 void set_last_error(const std::string& msg);
 
