@@ -11,14 +11,15 @@
 // Layout: S is column-major with leading dimension ld, lower triangle used.
 // Algorithm: blocked right-looking Cholesky with 64-wide diagonal blocks.
 //   step:   one launch per 64 columns: L21 = A21 * Linv' in place, one
-//           workgroup per 64 rows, the update of the next 64 columns, and
-//           the next diagonal block's factor with its inverse (Linv, 64x64
+//           workgroup per 64 rows, the update of the panel's later columns,
+//           and the next diagonal block's factor with its inverse (Linv, 64x64
 //           per block)
 //   update: trailing C -= L21 L21' on MFMA (v_mfma_f64_16x16x4f64 or
 //           v_mfma_f32_16x16x4f32), 64x64 tiles, lower tiles only.  It is
 //           delayed to every panel of 256 or Aux::nb columns, so the trailing
 //           matrix is read and written once per panel.
-// Triangular solves use the stored Linv blocks: one launch per 256 rows.
+// Triangular solves: one launch per pass, from the inverses of 128 x 128
+// diagonal blocks (FP64), or launches of 256 rows (FP32).
 #include "hc_dense.h"
 
 #include <algorithm>
@@ -320,170 +321,161 @@ __global__ __launch_bounds__(256, 3) void k_chol_diag(double* __restrict__ A, in
 // c is up to date, its diagonal block factored and that factor's inverse in
 // Linv; a workgroup takes 64 of the rows [c + 64, R), each wave 16 of them:
 //   L[i, c] = A[i, c] Linv'                                     (all rows)
-// and, when another block column follows in the panel (next), brings that
-// column up to date against the columns [kb, c + 64) of the panel:
-//   A[i, c'] -= sum_k L[i, k] L[c', k]',  c' = c + 64,
+// and brings the block columns c' in [c + 64, cend) left of its rows up to date:
+//   A[i, c'] -= L[i, c] L[c', c]',
 // whereupon workgroup 0, whose rows are the next diagonal block, factors it.
 // So the chain per 64 columns is one launch instead of three (factor, TRSM,
 // update), and the factorisation of the next diagonal block runs beside the
 // other rows' work.  L[c', c] is needed by every workgroup and recomputed by
-// each (one 64^3 product); since all of them read A[c', c], workgroup 0 leaves
-// its tile in the free Linv slot of block c'/64 + 1 (defer_out) and the next
-// step puts it in its place (defer_in).
+// each (a 64^3 product); since all of them read A[c', c], the workgroups of
+// those rows leave their tile in a slot (defer) and the next step's workgroups
+// from rowgs on put it in its place (rows below rdef of the row blocks from c).
 //
 // Products run on MFMA as X' = Linv A' and U' = X_c' X', whose output
 // registers (rows k, one matrix row i per lane) are the next product's operand
 // registers, and whose stores to A are 16 consecutive rows per column.
-// Bound: the chain of one workgroup (launch, loads past the L2, one or two
-// 64^3 products, 64 pivots); 34 KB of LDS and at most 168 VGPRs let it run
-// beside three trailing-update workgroups.  64 columns at 1,856 rows: 24 us,
-// 34 with 192 earlier columns, against 53 us in three launches.
+// Bound: the chain of workgroup 0 (launch, loads past the L2, two 64^3
+// products, 64 pivots); 34 KB of LDS and at most 168 VGPRs let it run beside
+// three trailing-update workgroups.  The four steps of a panel at 1,856 rows:
+// 34, 27, 24, 24 us (in the first two the other rows' workgroups, 7 us a tile,
+// outlast the chain), against 53 us each in three launches and 26 to 34 with
+// the panel's earlier columns applied only when a block column is next, which
+// puts up to 192 of them, and the tile of the previous step, in the chain.
 // ---------------------------------------------------------------------------
 constexpr int XST = CST;       // k row stride of X_c' in LDS
-constexpr int KST = BS + 16;   // k row stride of a chunk of L[c', k]
-static_assert(BS * XST <= CHOL_LDS && 2 * 16 * KST <= CHOL_LDS, "both fit the block's LDS");
+constexpr int SLOTS = 2 * (IB / BS + 1);   // deferred tiles: a step's, and the previous one's on their way
+static_assert(BS * XST <= CHOL_LDS, "X_c' fits the block's LDS");
 
-__global__ __launch_bounds__(256, 3) void k_panel_step(double* __restrict__ A, int64_t ld, int64_t n, int64_t kb, int64_t c,
-                                                    int64_t R, double* __restrict__ LinvAll, int next, int defer_in,
-                                                    int defer_out, double tol, double fix,
-                                                    unsigned long long* __restrict__ hits) {
+__global__ __launch_bounds__(256, 3) void k_panel_step(double* __restrict__ A, int64_t ld, int64_t n, int64_t c,
+                                                    int64_t cend, int64_t R, double* __restrict__ LinvAll,
+                                                    double* __restrict__ slots, int rowgs, int defer, int64_t rdef,
+                                                    double tol, double fix, unsigned long long* __restrict__ hits) {
   typedef Mfma<double> M;
-  __shared__ __align__(16) double lds[CHOL_LDS];   // chunks of L[c', k], X_c', then the next diagonal block
+  __shared__ __align__(16) double lds[CHOL_LDS];   // X_c', then the next diagonal block
   __builtin_amdgcn_s_setprio(3);   // the factorisation's critical path
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 15;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool first = blockIdx.x == 0;
   const double* Linv = LinvAll + (c / BS) * BS * BS;
-  double* slot = LinvAll + (c / BS + (defer_in ? 1 : 2)) * BS * BS;
-  if (first && defer_in) {
-    // L[c, c - 64] left here by the previous step
+  const int64_t c1 = c + BS;                                  // next block column
+  const int64_t r0 = c1 + (int64_t)blockIdx.x * BS;
+  // tile of L[r .., k ..] between the launch that makes it and the next
+  auto slot_of = [&](int64_t r, int64_t k) {
+    return slots + ((r / BS) % (SLOTS / 2) + ((k / BS) & 1) * (SLOTS / 2)) * BS * BS;
+  };
+  if ((int)blockIdx.x >= rowgs) {
+    const int64_t r = c + (int64_t)(blockIdx.x - rowgs) * BS;
+    const double* slot = slot_of(r, c - BS);
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       const int k = w + 4 * e;
-      A[(c + lane) + (c - BS + k) * ld] = slot[lane + k * BS];
+      if (r + lane < rdef) A[(r + lane) + (c - BS + k) * ld] = slot[lane + k * BS];
     }
+    return;
   }
-  const int64_t r0 = c + BS + (int64_t)blockIdx.x * BS;
   if (r0 >= R) return;
   const int64_t row = r0 + 16 * w + li;                       // this lane's row
-  const double* pa = A + std::min<int64_t>(row, R - 1);            // rows past R repeat the last one
-  const int64_t c1 = c + BS;                                  // next block column
-  const bool own_next = next && !first;                       // X_c' computed apart from this tile's X
-  const int nbt = first ? w + 1 : 4;                          // the diagonal tile needs its lower blocks only
-  v4d u[4];
-#pragma unroll
-  for (int b = 0; b < 4; ++b) u[b] = v4d{0, 0, 0, 0};
-  if (next && kb < c) {
-    // U' = L[c', k] L[i, k]' over the panel's earlier columns, 16 of them at a
-    // time: this lane's row in registers, the 64 rows of c' shared in LDS
-    // (each wave brings four columns); two chunks on their way ahead of the
-    // products (they come from other compute units' writes, past the L2)
-    const double* pn = A + std::min<int64_t>(c1 + lane, n - 1) + 4 * w * ld;
-    double av[2][4], bv[2][4];
-    auto load = [&](int s, int64_t k) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        av[s][q] = pa[(k + M::row(lane, q)) * ld];
-        bv[s][q] = pn[(k + q) * ld];
-      }
-    };
-    auto chunk = [&](int s, int64_t k) {   // chunk k from register set s through LDS buffer s, then its successor's loads
-      double* kl = lds + s * 16 * KST;
-      double a0[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        kl[(4 * w + q) * KST + lane] = bv[s][q];
-        a0[q] = av[s][q];
-      }
-      load(s, std::min<int64_t>(k + 32, c - 16));
-      __syncthreads();   // one barrier per chunk: buffer s was read two chunks ago
-#pragma unroll
-      for (int b = 0; b < 4; ++b)
-        if (b < nbt)
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            u[b] = M::op(kl[M::row(lane, q) * KST + 16 * b + li], a0[q], u[b]);
-    };
-    load(0, kb);
-    load(1, kb + 16);
-    for (int64_t k = kb; k < c; k += 32) {   // c - kb is a multiple of 64
-      chunk(0, k);
-      chunk(1, k + 16);
-    }
-    __syncthreads();   // X_c' overwrites the chunks
-  }
-  // x = Linv A' of the 16 rows at pr: x[t][q] = X[i][16 t + row(lane, q)]
-  v4d x[4];
-  auto trsm = [&](const double* pr) {
+  // column j + lane / 16 of a row: uniform base of column j, 32-bit lane offset
+  // (64-bit addresses per lane take twice the registers there are)
+  const uint32_t lgo = (uint32_t)((lane >> 4) * ld);
+  const uint32_t own = (uint32_t)std::min<int64_t>(row, R - 1) + lgo;   // rows past R repeat the last one
+  // Linv A' of the 16 rows at offset o, 16 of its rows at a time: f(t, x) with
+  // x[q] = X[i][16 t + row(lane, q)]
+  auto trsm = [&](uint32_t o, auto&& f) {
     double a[4][4];   // A[i][m], m = 16 u + row(lane, q)
 #pragma unroll
     for (int u = 0; u < 4; ++u)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) a[u][q] = pr[(c + 16 * u + M::row(lane, q)) * ld];
+      for (int q = 0; q < 4; ++q) a[u][q] = (A + (c + 16 * u + 4 * q) * ld)[o];
+    const double* inv = Linv;
+    asm volatile("" : "+s"(inv));   // its 40 operands are not kept from one product to the next
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      x[t] = v4d{0, 0, 0, 0};
+      v4d y = v4d{0, 0, 0, 0};
 #pragma unroll
       for (int u = 0; u <= t; ++u)   // Linv is lower triangular
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-          x[t] = M::op(Linv[(16 * t + li) + (16 * u + M::row(lane, q)) * BS], a[u][q], x[t]);
+          y = M::op(inv[(16 * t + li) + (16 * u + M::row(lane, q)) * BS], a[u][q], y);
+      f(t, y);
     }
   };
-  if (own_next) trsm(A + std::min<int64_t>(c1 + 16 * w + li, n - 1));
-  else trsm(pa);
-  if (next) {
+  // columns cb + j, j = 16 b + row(lane, q), of this lane's row
+  auto load = [&](int64_t cb, double (&cv)[4][4]) {
+    const int nb = (int)std::min<int64_t>(BS, n - cb);
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int b = 0; b < 4; ++b)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) lds[(16 * t + M::row(lane, q)) * XST + 16 * w + li] = x[t][q];
-  }
-  if (own_next) trsm(pa);
+      for (int q = 0; q < 4; ++q) {
+        const int j = std::min(16 * b + 4 * q, nb - 1);   // past nb: any column
+        cv[b][q] = (A + (cb + j) * ld)[nb < BS && j + (lane >> 4) >= nb ? own - lgo : own];
+      }
+  };
+  v4d x[4];
+  trsm(own, [&](int t, v4d y) { x[t] = y; });
   // L[i][c + k], k = 16 t + row(lane, q)
+  const bool slot_out = defer && r0 < cend;
+  double* slot = slot_of(r0, c);
 #pragma unroll
   for (int t = 0; t < 4; ++t)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int k = 16 * t + M::row(lane, q);
-      if (first && defer_out) LinvAll[(c / BS + 2) * BS * BS + (16 * w + li) + k * BS] = x[t][q];
-      else if (row < R) A[row + (c + k) * ld] = x[t][q];
+      if (slot_out) slot[(16 * w + li) + k * BS] = x[t][q];
+      else if (row < R) (A + (c + 16 * t + 4 * q) * ld)[own] = x[t][q];
     }
-  if (!next) return;
-  // columns c1 + j, j = 16 b + row(lane, q), of this lane's row
-  double cv[4][4];
-  const int nb = (int)std::min<int64_t>(BS, n - c1);
+#pragma unroll 1
+  for (int64_t cb = c1; cb < cend && cb <= r0; cb += BS) {
+    const int nb = (int)std::min<int64_t>(BS, n - cb);
+    const int nbt = first ? w + 1 : 4;   // the next diagonal tile needs its lower blocks only
+    if (cb > c1) __syncthreads();   // the previous X_c' has been read
+    auto put = [&](int t, v4d y) {
 #pragma unroll
-  for (int b = 0; b < 4; ++b)
+      for (int q = 0; q < 4; ++q) lds[(16 * t + M::row(lane, q)) * XST + 16 * w + li] = y[q];
+    };
+    if (cb == r0) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) cv[b][q] = pa[(c1 + std::min(16 * b + M::row(lane, q), nb - 1)) * ld];
-  __syncthreads();   // X_c' is in LDS
+      for (int t = 0; t < 4; ++t) put(t, x[t]);
+    } else {
+      trsm((uint32_t)std::min<int64_t>(cb + 16 * w + li, n - 1) + lgo, put);
+    }
+    double cv[4][4];
+    load(cb, cv);
+    __syncthreads();   // X_c' is in LDS
+    v4d u[4];
 #pragma unroll
-  for (int t = 0; t < 4; ++t)
+    for (int b = 0; b < 4; ++b) u[b] = v4d{0, 0, 0, 0};
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
-      if (b < nbt)
+    for (int t = 0; t < 4; ++t)
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          u[b] = M::op(lds[(16 * t + M::row(lane, q)) * XST + 16 * b + li], x[t][q], u[b]);
-  if (!first) {
-    if (row < R)
+      for (int b = 0; b < 4; ++b)
+        if (b < nbt)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            u[b] = M::op(lds[(16 * t + M::row(lane, q)) * XST + 16 * b + li], x[t][q], u[b]);
+    if (!first) {
 #pragma unroll
       for (int b = 0; b < 4; ++b)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) A[row + (c1 + 16 * b + M::row(lane, q)) * ld] = cv[b][q] - u[b][q];
-    return;
-  }
-  __syncthreads();   // every wave has read X_c'
-#pragma unroll
-  for (int b = 0; b < 4; ++b)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int k = 16 * b + M::row(lane, q), i = 16 * w + li;
-      lds[k * CST + i] = chol_pad(cv[b][q] - u[b][q], i, k, nb);
+        for (int q = 0; q < 4; ++q) {
+          const int j = 16 * b + M::row(lane, q);
+          if (row < R && j < nb) (A + (cb + 16 * b + 4 * q) * ld)[own] = cv[b][q] - u[b][q];
+        }
+      continue;
     }
+    __syncthreads();   // every wave has read X_c'
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int k = 16 * b + M::row(lane, q), i = 16 * w + li;
+        lds[k * CST + i] = chol_pad(cv[b][q] - u[b][q], i, k, nb);
+      }
+  }
+  if (!first || c1 >= cend) return;
   __syncthreads();
   chol_block(lane, w, lds, tol, fix, hits);
-  chol_store(lane, w, nb, lds, A, ld, c1, LinvAll + (c1 / BS) * BS * BS);
+  chol_store(lane, w, (int)std::min<int64_t>(BS, n - c1), lds, A, ld, c1, LinvAll + (c1 / BS) * BS * BS);
 }
 
 // ---------------------------------------------------------------------------
@@ -970,21 +962,26 @@ static void factor_panel(double* S, int64_t n, int64_t ld, double* Linv, double 
   hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(256), 0, st, S, ld, K0, n, Linv + (K0 / BS) * BS * BS, tol, fix,
                      hits);
   HC_LAUNCH_CHECK();
-  bool deferred = false;   // a tile of L waits in a Linv slot (k_panel_step)
+  double* slots = Linv + ceil_div(n, BS) * BS * BS;
+  int64_t cdef = 0, rdef = 0;   // tiles of L that wait in their slots (k_panel_step): row blocks before cdef, rows before rdef
   for (int64_t I0 = K0; I0 < Kend; I0 += IB) {
     const int64_t Iend = std::min<int64_t>(Kend, I0 + IB);
+    const int64_t upto = Iend < Kend ? Iend + BS : Kend;   // the block column after the panel is brought up to date too
     for (int64_t c = I0; c < Iend; c += BS) {
       const int64_t c1 = std::min<int64_t>(n, c + BS);
       const bool next = c1 < Kend;
       int64_t R = rows_below(last, n, c1 - 1);
       if (next) R = std::max(R, std::min<int64_t>(n, c1 + BS));   // the next diagonal block, also when it is not reached
-      if (R <= c1 && !deferred) continue;
+      if (R <= c1 && cdef == 0) continue;
       const int64_t wgs = std::max<int64_t>(1, ceil_div(R - c1, BS));
+      const int64_t cend = next ? std::min(std::min(upto, n), R) : c1;
       const bool defer = next && wgs > 1;
-      hipLaunchKernelGGL(k_panel_step, dim3((unsigned)wgs), dim3(256), 0, st, S, ld, n, I0, c, R, Linv,
-                         next ? 1 : 0, deferred ? 1 : 0, defer ? 1 : 0, tol, fix, hits);
+      const int64_t tiles = cdef > c ? ceil_div(std::min(cdef, rdef) - c, BS) : 0;
+      hipLaunchKernelGGL(k_panel_step, dim3((unsigned)(wgs + tiles)), dim3(256), 0, st, S, ld, n, c, cend, R, Linv,
+                         slots, (int)wgs, defer ? 1 : 0, rdef, tol, fix, hits);
       HC_LAUNCH_CHECK();
-      deferred = defer;
+      cdef = defer ? cend : 0;
+      rdef = defer ? R : 0;
     }
     if (Iend < Kend) {
       const int64_t c2 = Iend + BS, R = rows_below(last, n, Iend - 1);   // Iend's own block column is up to date
@@ -1724,7 +1721,8 @@ template void gemm_nt<double>(double*, int64_t, const double*, int64_t, const do
                               int64_t, double, bool, int64_t, int64_t, hipStream_t, GemmRole);
 template void gemm_nt<float>(float*, int64_t, const float*, int64_t, const float*, int64_t, int64_t, int64_t,
                              int64_t, float, bool, int64_t, int64_t, hipStream_t, GemmRole);
-int64_t linv_elems(int64_t n) { return ceil_div(n, BS) * BS * BS; }
+// the diagonal blocks' inverses, then the FP64 panels' tiles on their way
+int64_t linv_elems(int64_t n) { return (ceil_div(n, BS) + SLOTS) * BS * BS; }
 
 // factor flops of a dense n x n Cholesky
 double cholesky_flops(int64_t n) { return (double)n * n * n / 3.0; }
