@@ -67,16 +67,19 @@ void add_P_delta_map(const Csr& P, int64_t n, double delta, const ColMap& cm, hi
 // W_b = S_Tb L_b^-T, and S_TT -= W_b W_b' (lower part: into cm.lslot for an
 // ordered sum when set, else with FP64 atomics).
 void leaf_factor(const ColMap& cm, double tol, double fix, unsigned long long* hits, hipStream_t st);
-// Forward half of the leaf solve: y_b = L_b^-1 u_b written to y at the leaf
-// columns, then uT[t] -= sum over the leaves coupled to t of (W_b y_b)[t]
-// (uT: compact tail vector, already gathered), one writer per t in a fixed
+// One or two right-hand sides of the leaf solves.
+struct LeafVecs {
+  const double* u[2];   // right-hand side, all columns
+  double* x[2];         // y_b = L_b^-1 u_b, then the solution, all columns
+  double* uT[2];        // compact tail vectors
+  const double* xT[2];
+};
+// Forward half: y_b into x at the leaf columns, uT[t] = u[tcols[t]] minus the
+// sum over the leaves coupled to t of (W_b y_b)[t], one writer per t in a fixed
 // order.
-void leaf_forward(const ColMap& cm, const double* u, double* y, double* uT, hipStream_t st);
-// Backward half: x_b = L_b^-T (y_b - W_b' xT), reading y_b from x at the
-// leaf columns and overwriting it.
-void leaf_backward(const ColMap& cm, const double* xT, double* x, hipStream_t st);
-// uT[t] = u[tcols[t]] and x[tcols[t]] = xT[t]
-void gather_tail(const ColMap& cm, const double* u, double* uT, hipStream_t st);
-void scatter_tail(const ColMap& cm, const double* xT, double* x, hipStream_t st);
+void leaf_forward(const ColMap& cm, const LeafVecs& w, int nr, hipStream_t st);
+// Backward half: x_b = L_b^-T (y_b - W_b' xT), reading y_b from x at the leaf
+// columns and overwriting it, and x[tcols[t]] = xT[t].
+void leaf_backward(const ColMap& cm, const LeafVecs& w, int nr, hipStream_t st);
 
 }  // namespace hc

@@ -173,186 +173,248 @@ void leaf_factor(const ColMap& cm, double tol, double fix, unsigned long long* h
   HC_LAUNCH_CHECK();
 }
 
-__device__ inline void load_leaf_L(const ColMap& cm, int b, int l, int lane, double (*Lb)[LEAF_MAX + 1]) {
-  const double* lv = cm.lval + cm.lval_off[b];
-  for (int e = lane; e < l * l; e += 64) Lb[e % l][e / l] = lv[e];
-}
-
-// Leaf solves.  Leaves of at most LEAF_SMALL columns run one lane each
+// Leaf solves, for one or two right-hand sides side by side (NR), which share
+// the reads of L and W.  Leaves of at most LEAF_SMALL columns run one lane each
 // (their L and coupling rows read straight from memory), larger ones one wave
-// each through LDS; the tail's share of the forward solve is a gather per tail
-// index over the leaves coupled to it (no atomics, a fixed order).
-__global__ __launch_bounds__(256) void k_leaf_fwd_small(ColMap cm, const double* __restrict__ u,
-                                                        double* __restrict__ y) {
-  const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (k >= cm.nsmall) return;
+// each: lane i keeps entry i, the current entry is divided by the pivot and
+// broadcast by readlane, the others lose their multiple of it.  (With the
+// substitution in one lane a leaf of 32 columns took 16 us a pass; a launch per
+// kind, right-hand side and copy of the tail made ten of a solve's three.)
+__device__ inline double lane_value(double v, int l) {
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, l),
+                 hi = (uint32_t)__builtin_amdgcn_readlane((int)(b >> 32), l);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+constexpr int LEAF_AHEAD = 8;   // columns of L loaded together
+
+template <int NR>
+__device__ inline void leaf_fwd_small(const ColMap& cm, int64_t k, const LeafVecs& w) {
   const int b = cm.small[k];
   const int l = cm.lsize[b];
   const double* lv = cm.lval + cm.lval_off[b];   // L_b column-major: L[i][j] = lv[i + j l]
   const int32_t* cols = cm.lcols + cm.lcol_off[b];
-  double yb[LEAF_SMALL];
+  double yb[NR][LEAF_SMALL];
 #pragma unroll
   for (int j = 0; j < LEAF_SMALL; ++j) {
     if (j < l) {
-      double v = u[cols[j]];
+      double lr[LEAF_SMALL];
 #pragma unroll
-      for (int q = 0; q < j; ++q) v -= lv[j + q * l] * yb[q];
-      yb[j] = v / lv[j + j * l];
-      y[cols[j]] = yb[j];
+      for (int q = 0; q <= j; ++q) lr[q] = lv[j + q * l];
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        double v = w.u[r][cols[j]];
+#pragma unroll
+        for (int q = 0; q < j; ++q) v -= lr[q] * yb[r][q];
+        yb[r][j] = v / lr[j];
+        w.x[r][cols[j]] = yb[r][j];
+      }
     }
   }
 }
-
-__global__ __launch_bounds__(64) void k_leaf_fwd(ColMap cm, const double* __restrict__ u, double* __restrict__ y) {
-  __shared__ double Lb[LEAF_MAX][LEAF_MAX + 1];
-  __shared__ double yb[LEAF_MAX];
-  const int b = cm.large[blockIdx.x], lane = threadIdx.x;
-  const int l = cm.lsize[b];
-  const int32_t* cols = cm.lcols + cm.lcol_off[b];
-  load_leaf_L(cm, b, l, lane, Lb);
-  if (lane < l) yb[lane] = u[cols[lane]];
-  __syncthreads();
-  if (lane == 0)
-    for (int j = 0; j < l; ++j) {
-      double v = yb[j];
-      for (int k = 0; k < j; ++k) v -= Lb[j][k] * yb[k];
-      yb[j] = v / Lb[j][j];
+template <int NR>
+__device__ inline void leaf_fwd_wave(const ColMap& cm, int b, int lane, const LeafVecs& w) {
+  const int l = cm.lsize[b], i = min(lane, l - 1);
+  const double* lv = cm.lval + cm.lval_off[b] + i;
+  const int col = cm.lcols[cm.lcol_off[b] + i];
+  double v[NR];
+#pragma unroll
+  for (int r = 0; r < NR; ++r) v[r] = w.u[r][col];
+  for (int k0 = 0; k0 < l; k0 += LEAF_AHEAD) {
+    double lr[LEAF_AHEAD];
+#pragma unroll
+    for (int q = 0; q < LEAF_AHEAD; ++q) lr[q] = lv[(int64_t)min(k0 + q, l - 1) * l];
+#pragma unroll
+    for (int q = 0; q < LEAF_AHEAD; ++q) {
+      const int k = k0 + q;
+      if (k >= l) break;
+      const double d = lane_value(lr[q], k);
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const double y = lane_value(v[r], k) / d;
+        v[r] = lane == k ? y : lane > k ? v[r] - lr[q] * y : v[r];
+      }
     }
-  __syncthreads();
-  if (lane < l) y[cols[lane]] = yb[lane];
+  }
+  if (lane < l)
+#pragma unroll
+    for (int r = 0; r < NR; ++r) w.x[r][col] = v[r];
+}
+// workgroups: small leaves (256 each), then large ones (four each)
+template <int NR>
+__global__ __launch_bounds__(256) void k_leaf_fwd(ColMap cm, LeafVecs w) {
+  const int64_t ns = (cm.nsmall + 255) / 256;
+  if ((int64_t)blockIdx.x < ns) {
+    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (k < cm.nsmall) leaf_fwd_small<NR>(cm, k, w);
+    return;
+  }
+  const int64_t k = ((int64_t)blockIdx.x - ns) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (k < cm.nlarge) leaf_fwd_wave<NR>(cm, cm.large[k], threadIdx.x & 63, w);
 }
 
-// uT[t] -= sum over the couplings (b, a) of t of sum_j W_b[a][j] y_b[j]; one
-// wave per tail index, lanes over its couplings, then a shuffle tree
-// one workgroup per tail index, of cm.tail_threads threads: its W entries
-// (flattened at set-up into (cval index, leaf column) pairs, so each costs
-// two independent gathers) split over the threads; per-wave shuffle sums meet
-// in LDS in a fixed order
+// uT[t] = u[tcols[t]] - sum over the couplings (b, a) of t of sum_j W_b[a][j]
+// y_b[j]: one workgroup per tail index, of cm.tail_threads threads, its W
+// entries (flattened at set-up into (cval index, leaf column) pairs, so each
+// costs two independent gathers) split over the threads; per-wave shuffle sums
+// meet in LDS in a fixed order
 constexpr int TAIL_THREADS_MAX = 1024;
-__global__ __launch_bounds__(TAIL_THREADS_MAX) void k_leaf_tail(ColMap cm, const double* __restrict__ y,
-                                                                double* __restrict__ uT) {
-  __shared__ double part[TAIL_THREADS_MAX / 64];
+template <int NR>
+__global__ __launch_bounds__(TAIL_THREADS_MAX) void k_leaf_tail(ColMap cm, LeafVecs w) {
+  __shared__ double part[NR][TAIL_THREADS_MAX / 64];
   const int64_t t = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, nthr = blockDim.x;
   const int64_t e0 = cm.tc_ptr[t], e1 = cm.tc_ptr[t + 1];
-  double acc = 0.0;
-  for (int64_t e = e0 + tid; e < e1; e += nthr) acc += cm.cval[cm.te_cv[e]] * y[cm.te_y[e]];
-  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-  if (lane == 0) part[tid >> 6] = acc;
+  double acc[NR] = {};
+  for (int64_t e = e0 + tid; e < e1; e += nthr) {
+    const double c = cm.cval[cm.te_cv[e]];
+    const int32_t j = cm.te_y[e];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) acc[r] += c * w.x[r][j];
+  }
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    for (int o = 32; o > 0; o >>= 1) acc[r] += __shfl_xor(acc[r], o, 64);
+    if (lane == 0) part[r][tid >> 6] = acc[r];
+  }
   __syncthreads();
-  if (tid == 0 && e1 > e0) {
+  if (tid < NR) {
+    const double u = w.u[tid][cm.tcols[t]];
     double s = 0.0;
-    for (int w = 0; w < nthr / 64; ++w) s += part[w];
-    uT[t] -= s;
+    for (int k = 0; k < nthr / 64; ++k) s += part[tid][k];
+    w.uT[tid][t] = e1 > e0 ? u - s : u;
   }
 }
 
-__global__ __launch_bounds__(256) void k_leaf_bwd_small(ColMap cm, const double* __restrict__ xT,
-                                                        double* __restrict__ x) {
-  const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (k >= cm.nsmall) return;
+template <int NR>
+__device__ inline void leaf_bwd_small(const ColMap& cm, int64_t k, const LeafVecs& w) {
   const int b = cm.small[k];
   const int l = cm.lsize[b], cnt = cm.ccnt[b];
   const double* lv = cm.lval + cm.lval_off[b];
   const int32_t* cols = cm.lcols + cm.lcol_off[b];
   const int32_t* cl = cm.clist + cm.clist_off[b];
   const double* cv = cm.cval + cm.cval_off[b];
-  double vb[LEAF_SMALL];
+  double vb[NR][LEAF_SMALL];
 #pragma unroll
   for (int j = 0; j < LEAF_SMALL; ++j) {
     if (j < l) {
-      double v = x[cols[j]];
-      for (int a = 0; a < cnt; ++a) v -= cv[a + (int64_t)j * cnt] * xT[cl[a]];
-      vb[j] = v;
+#pragma unroll
+      for (int r = 0; r < NR; ++r) vb[r][j] = w.x[r][cols[j]];
+      for (int a = 0; a < cnt; ++a) {
+        const double c = cv[a + (int64_t)j * cnt];
+        const int32_t t = cl[a];
+#pragma unroll
+        for (int r = 0; r < NR; ++r) vb[r][j] -= c * w.xT[r][t];
+      }
     }
   }
 #pragma unroll
   for (int j = LEAF_SMALL - 1; j >= 0; --j) {
     if (j < l) {
-      double v = vb[j];
+      double lr[LEAF_SMALL];
 #pragma unroll
-      for (int q = j + 1; q < LEAF_SMALL; ++q)
-        if (q < l) v -= lv[q + j * l] * vb[q];
-      vb[j] = v / lv[j + j * l];
-      x[cols[j]] = vb[j];
+      for (int q = j; q < LEAF_SMALL; ++q) lr[q] = q < l ? lv[q + j * l] : 0.0;
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        double v = vb[r][j];
+#pragma unroll
+        for (int q = j + 1; q < LEAF_SMALL; ++q)
+          if (q < l) v -= lr[q] * vb[r][q];
+        vb[r][j] = v / lr[j];
+        w.x[r][cols[j]] = vb[r][j];
+      }
     }
   }
 }
-
-__global__ __launch_bounds__(64) void k_leaf_bwd(ColMap cm, const double* __restrict__ xT, double* __restrict__ x) {
-  __shared__ double Lb[LEAF_MAX][LEAF_MAX + 1];
-  __shared__ double vb[LEAF_MAX];
-  const int b = cm.large[blockIdx.x], lane = threadIdx.x;
-  const int l = cm.lsize[b], cnt = cm.ccnt[b];
-  const int32_t* cols = cm.lcols + cm.lcol_off[b];
-  const int32_t* cl = cm.clist + cm.clist_off[b];
-  const double* cv = cm.cval + cm.cval_off[b];
-  load_leaf_L(cm, b, l, lane, Lb);
-  if (lane < l) {
-    double v = x[cols[lane]];
-    for (int a = 0; a < cnt; ++a) v -= cv[a + (int64_t)lane * cnt] * xT[cl[a]];
-    vb[lane] = v;
+template <int NR>
+__device__ inline void leaf_bwd_wave(const ColMap& cm, int b, int lane, const LeafVecs& w) {
+  const int l = cm.lsize[b], cnt = cm.ccnt[b], i = min(lane, l - 1);
+  const double* lv = cm.lval + cm.lval_off[b] + (int64_t)i * l;   // column i of L
+  const int col = cm.lcols[cm.lcol_off[b] + i];
+  const double* cv = cm.cval + cm.cval_off[b] + (int64_t)i * cnt;
+  double v[NR], xt[NR];   // lane a: the tail entry of coupling a
+  const int32_t t = cnt > 0 ? cm.clist[cm.clist_off[b] + min(lane, cnt - 1)] : 0;
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    v[r] = w.x[r][col];
+    xt[r] = cnt > 0 ? w.xT[r][t] : 0.0;
   }
-  __syncthreads();
-  if (lane == 0)
-    for (int j = l - 1; j >= 0; --j) {
-      double v = vb[j];
-      for (int k = j + 1; k < l; ++k) v -= Lb[k][j] * vb[k];
-      vb[j] = v / Lb[j][j];
+  for (int a0 = 0; a0 < cnt; a0 += LEAF_AHEAD) {
+    double c[LEAF_AHEAD];
+#pragma unroll
+    for (int q = 0; q < LEAF_AHEAD; ++q) c[q] = cv[min(a0 + q, cnt - 1)];
+#pragma unroll
+    for (int q = 0; q < LEAF_AHEAD; ++q) {
+      if (a0 + q >= cnt) break;
+#pragma unroll
+      for (int r = 0; r < NR; ++r) v[r] -= c[q] * lane_value(xt[r], a0 + q);
     }
-  __syncthreads();
-  if (lane < l) x[cols[lane]] = vb[lane];
+  }
+  for (int k0 = l - 1; k0 >= 0; k0 -= LEAF_AHEAD) {
+    double lr[LEAF_AHEAD];
+#pragma unroll
+    for (int q = 0; q < LEAF_AHEAD; ++q) lr[q] = lv[max(k0 - q, 0)];
+#pragma unroll
+    for (int q = 0; q < LEAF_AHEAD; ++q) {
+      const int k = k0 - q;
+      if (k < 0) break;
+      const double d = lane_value(lr[q], k);
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const double y = lane_value(v[r], k) / d;
+        v[r] = lane == k ? y : lane < k ? v[r] - lr[q] * y : v[r];
+      }
+    }
+  }
+  if (lane < l)
+#pragma unroll
+    for (int r = 0; r < NR; ++r) w.x[r][col] = v[r];
+}
+// workgroups: small leaves, large leaves (as k_leaf_fwd), then the tail's
+// entries of x
+template <int NR>
+__global__ __launch_bounds__(256) void k_leaf_bwd(ColMap cm, LeafVecs w) {
+  const int64_t ns = (cm.nsmall + 255) / 256, nl = (cm.nlarge + 3) / 4;
+  if ((int64_t)blockIdx.x < ns) {
+    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (k < cm.nsmall) leaf_bwd_small<NR>(cm, k, w);
+  } else if ((int64_t)blockIdx.x < ns + nl) {
+    const int64_t k = ((int64_t)blockIdx.x - ns) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (k < cm.nlarge) leaf_bwd_wave<NR>(cm, cm.large[k], threadIdx.x & 63, w);
+  } else {
+    const int64_t t = ((int64_t)blockIdx.x - ns - nl) * 256 + threadIdx.x;
+    if (t < cm.nt)
+#pragma unroll
+      for (int r = 0; r < NR; ++r) w.x[r][cm.tcols[t]] = w.xT[r][t];
+  }
 }
 
-void leaf_forward(const ColMap& cm, const double* u, double* y, double* uT, hipStream_t st) {
-  if (cm.nleaf == 0) return;
-  if (cm.nsmall) {
-    hipLaunchKernelGGL(k_leaf_fwd_small, dim3((unsigned)ceil_div(cm.nsmall, 256)), dim3(256), 0, st, cm, u, y);
-    HC_LAUNCH_CHECK();
-  }
-  if (cm.nlarge) {
-    hipLaunchKernelGGL(k_leaf_fwd, dim3((unsigned)cm.nlarge), dim3(64), 0, st, cm, u, y);
+template <int NR> static void leaf_forward_n(const ColMap& cm, const LeafVecs& w, hipStream_t st) {
+  const int64_t wgs = ceil_div(cm.nsmall, 256) + ceil_div(cm.nlarge, 4);
+  if (wgs > 0) {
+    hipLaunchKernelGGL(k_leaf_fwd<NR>, dim3((unsigned)wgs), dim3(256), 0, st, cm, w);
     HC_LAUNCH_CHECK();
   }
   if (cm.nt) {
     const int thr = cm.tail_threads == 1024 || cm.tail_threads == 256 ? cm.tail_threads : 64;
-    hipLaunchKernelGGL(k_leaf_tail, dim3((unsigned)cm.nt), dim3(thr), 0, st, cm, (const double*)y, uT);
+    hipLaunchKernelGGL(k_leaf_tail<NR>, dim3((unsigned)cm.nt), dim3(thr), 0, st, cm, w);
     HC_LAUNCH_CHECK();
   }
 }
-
-void leaf_backward(const ColMap& cm, const double* xT, double* x, hipStream_t st) {
-  if (cm.nleaf == 0) return;
-  if (cm.nsmall) {
-    hipLaunchKernelGGL(k_leaf_bwd_small, dim3((unsigned)ceil_div(cm.nsmall, 256)), dim3(256), 0, st, cm, xT, x);
-    HC_LAUNCH_CHECK();
-  }
-  if (cm.nlarge) {
-    hipLaunchKernelGGL(k_leaf_bwd, dim3((unsigned)cm.nlarge), dim3(64), 0, st, cm, xT, x);
-    HC_LAUNCH_CHECK();
-  }
+void leaf_forward(const ColMap& cm, const LeafVecs& w, int nr, hipStream_t st) {
+  if (nr == 1) leaf_forward_n<1>(cm, w, st);
+  else leaf_forward_n<2>(cm, w, st);
 }
 
-__global__ void k_gather_tail(int64_t nt, const int32_t* __restrict__ tcols, const double* __restrict__ u,
-                              double* __restrict__ uT) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < nt) uT[t] = u[tcols[t]];
-}
-__global__ void k_scatter_tail(int64_t nt, const int32_t* __restrict__ tcols, const double* __restrict__ xT,
-                               double* __restrict__ x) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < nt) x[tcols[t]] = xT[t];
-}
-
-void gather_tail(const ColMap& cm, const double* u, double* uT, hipStream_t st) {
-  if (cm.nt == 0) return;
-  hipLaunchKernelGGL(k_gather_tail, dim3((unsigned)ceil_div(cm.nt, 256)), dim3(256), 0, st, cm.nt, cm.tcols, u, uT);
+template <int NR> static void leaf_backward_n(const ColMap& cm, const LeafVecs& w, hipStream_t st) {
+  const int64_t wgs = ceil_div(cm.nsmall, 256) + ceil_div(cm.nlarge, 4) + ceil_div(cm.nt, 256);
+  if (wgs == 0) return;
+  hipLaunchKernelGGL(k_leaf_bwd<NR>, dim3((unsigned)wgs), dim3(256), 0, st, cm, w);
   HC_LAUNCH_CHECK();
 }
-void scatter_tail(const ColMap& cm, const double* xT, double* x, hipStream_t st) {
-  if (cm.nt == 0) return;
-  hipLaunchKernelGGL(k_scatter_tail, dim3((unsigned)ceil_div(cm.nt, 256)), dim3(256), 0, st, cm.nt, cm.tcols, xT, x);
-  HC_LAUNCH_CHECK();
+void leaf_backward(const ColMap& cm, const LeafVecs& w, int nr, hipStream_t st) {
+  if (nr == 1) leaf_backward_n<1>(cm, w, st);
+  else leaf_backward_n<2>(cm, w, st);
 }
 
 }  // namespace hc

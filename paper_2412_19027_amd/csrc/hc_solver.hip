@@ -2025,23 +2025,26 @@ void fallback_fp64(hc_solver* S) {
   S->info.fp64_fallbacks++;
 }
 
-// x_r = S^-1 u_r for k = 1 or 2 right-hand sides: leaves in FP64 (one pass
-// per right-hand side), the tail in the factor precision with both
-// right-hand sides in one pass of the dense triangular solves
+// x_r = S^-1 u_r for k = 1 or 2 right-hand sides: leaves in FP64, the tail in
+// the factor precision, both right-hand sides in one pass of each
 void schur_solve_n(hc_solver* S, int k, const double* const* u, double* const* x) {
   hipStream_t st = S->stream;
   const int64_t nt = S->nt;
   const double* ut[2] = {u[0], k > 1 ? u[1] : nullptr};
   double* xt[2] = {x[0], k > 1 ? x[1] : nullptr};
-  double* uTs[2] = {S->uT, S->uTb};
-  double* xTs[2] = {S->xT, S->xTb};
-  if (S->leaves)
+  LeafVecs w{};
+  if (S->leaves) {
+    double *uTs[2] = {S->uT, S->uTb}, *xTs[2] = {S->xT, S->xTb};
     for (int r = 0; r < k; ++r) {
-      gather_tail(S->cm, u[r], uTs[r], st);
-      leaf_forward(S->cm, u[r], x[r], uTs[r], st);   // y_b into x at the leaf columns
+      w.u[r] = u[r];
+      w.x[r] = x[r];
+      w.uT[r] = uTs[r];
+      w.xT[r] = xTs[r];
       ut[r] = uTs[r];
       xt[r] = xTs[r];
     }
+    leaf_forward(S->cm, w, k, st);   // y_b into x at the leaf columns
+  }
   if (nt == 0) {
     // all columns in leaf blocks
   } else if (S->mixed && !S->use64) {
@@ -2059,11 +2062,7 @@ void schur_solve_n(hc_solver* S, int k, const double* const* u, double* const* x
   } else {
     tri_solve(S->tri, S->dS, S->ld, ut, xt, k, st);
   }
-  if (S->leaves)
-    for (int r = 0; r < k; ++r) {
-      leaf_backward(S->cm, xTs[r], x[r], st);
-      scatter_tail(S->cm, xTs[r], x[r], st);
-    }
+  if (S->leaves) leaf_backward(S->cm, w, k, st);
 }
 void schur_solve(hc_solver* S, const double* u, double* x) { schur_solve_n(S, 1, &u, &x); }
 
