@@ -1096,8 +1096,9 @@ void dense_cholesky(T* S, int64_t n, int64_t ld, T* Linv, double tol, double fix
 // other streams' load; each wait is bounded all the same (POLL_MAX loads, and
 // one load per value once it has run out).
 // Bound: the chain of n / 128 exchanges (about 2 us each), then L's bytes.
-// A solve (both passes, one right-hand side): 500 / 1,856 / 5,056 / 20,032 rows
-// 26 / 79 / 204 / 1,113 us against 28 / 107 / 284 / 1,600 us of kernel time in
+// A solve (both passes, one right-hand side): 700 / 1,856 / 5,056 / 20,032 rows
+// 33 / 71 / 181 / 1,110 us, with two 40 / 92 / 236 / 1,287; one right-hand side
+// of 1,856 / 5,056 / 20,032 rows took 107 / 284 / 1,600 us of kernel time in
 // two launches per 256 rows and pass (and, launched one by one, as much again
 // at the small sizes); a second tile on its way ahead of the first one's
 // values changes nothing.  The 128-blocks' inverses take 22 us, the 256-blocks'
@@ -1273,23 +1274,35 @@ __global__ __launch_bounds__(512) void k_tri_fwd(const double* __restrict__ L, i
   }
 }
 
-// sums a[0..15] over the wave: lane l returns the total of a[l / 4]
-template <int H>
-__device__ __forceinline__ void halve_sums(double (&a)[16], int lane) {
-#pragma unroll
-  for (int q = 0; q < H; ++q) {
-    const bool up = lane & (4 * H);
-    const double keep = up ? a[q + H] : a[q], send = up ? a[q] : a[q + H];
-    a[q] = keep + __shfl_xor(send, 4 * H, 64);
-  }
+// sums a[0..15] over the wave: lane l returns the total of a[l / 4].  Each level
+// halves the values and the lanes they are spread over: lane-group swaps for 32
+// and 16 lanes, DPP below.  It stands in the chain twice per block and
+// right-hand side; with shuffles through LDS a backward pass with two of them
+// took 211 us at 5,056 rows, now 142.
+template <int CTRL> __device__ inline double dpp(double v) {
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)b, CTRL, 0xf, 0xf, true),
+                 hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+template <int CTRL> __device__ inline double halve(double lower, double upper, bool up) {
+  return (up ? upper : lower) + dpp<CTRL>(up ? lower : upper);
 }
 __device__ __forceinline__ double wave_sum16(double (&a)[16], int lane) {
-  halve_sums<8>(a, lane);
-  halve_sums<4>(a, lane);
-  halve_sums<2>(a, lane);
-  halve_sums<1>(a, lane);
-  const double s = a[0] + __shfl_xor(a[0], 1, 64);
-  return s + __shfl_xor(s, 2, 64);
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    swap32(a[q], a[q + 8]);
+    a[q] += a[q + 8];
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    swap16(a[q], a[q + 4]);
+    a[q] += a[q + 4];
+  }
+  const double b0 = halve<0x128>(a[0], a[2], lane & 8), b1 = halve<0x128>(a[1], a[3], lane & 8);   // row_ror 8
+  double s = halve<0x141>(b0, b1, lane & 4);   // row_half_mirror
+  s += dpp<0xB1>(s);                           // quad_perm [1, 0, 3, 2]
+  return s + dpp<0x4E>(s);                     // quad_perm [2, 3, 0, 1]
 }
 
 // x = L^-T y, last block first.  Lane l holds the rows l and l + 64 of a tile,
