@@ -227,7 +227,6 @@ struct hc_solver {
   double* dpart = nullptr;          // reduction partials
   double* hpart = nullptr;          // pinned host copy
   double* hmap = nullptr;           // device address of hpart (null: not mapped, values come by copy)
-  unsigned long long rb_seq = 0;    // last value collect() wrote to hpart's flag
   double nb_const = 0;              // max(|q|, |b|), the constant system's right-hand side (scaled)
   bool own_stage = false;           // hpart/hmask allocated here (no caller staging)
   unsigned long long *dmask = nullptr, *hmask = nullptr;
@@ -1742,12 +1741,9 @@ Csr upload_csr(Buf& buf, const HostCsr& h, hipStream_t st) {
 // ===========================================================================
 // device-side building blocks of one iteration
 // ===========================================================================
-// hpart: combined values in [0, 32), the flag after them
-constexpr int RB_FLAG = 32;
-
 // Combines partials on the device and brings the values to the host.  Where
-// the staging is mapped, the kernel writes them there and the host watches the
-// flag behind them (no copy, no stream synchronisation); otherwise a copy.
+// the staging is mapped, the kernel writes them there and the host watches for
+// each of them (no copy, no stream synchronisation); otherwise a copy.
 // The wait falls back to the stream's own after WATCH_US, and so reports a
 // device error.  (A copy with its synchronisation took 10 to 20 us of host
 // time; an iteration reads back about ten times.)
@@ -1756,23 +1752,27 @@ void fetch(hc_solver* S, const Collect& c, double* out) {
   hipStream_t st = S->stream;
   if (c.n == 0) return;
   if (S->hmap) {
-    volatile unsigned long long* flag = (volatile unsigned long long*)(S->hpart + RB_FLAG);
-    const unsigned long long seq = ++S->rb_seq;
-    collect(c, S->hmap, (unsigned long long*)(S->hmap + RB_FLAG), seq, st);
+    volatile unsigned long long* h = (volatile unsigned long long*)S->hpart;
+    for (int i = 0; i < c.n; ++i) h[i] = COLLECT_EMPTY;
+    std::atomic_thread_fence(std::memory_order_seq_cst);
+    collect(c, S->hmap, st);
     const auto t0 = std::chrono::steady_clock::now();
+    bool synced = false;
     int spins = 0;
-    while (*flag != seq) {
-      __builtin_ia32_pause();
-      if (++spins % 256 == 0 &&
-          std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count() > WATCH_US) {
-        HC_HIP(hipStreamSynchronize(st));
-        break;
+    for (int i = 0; i < c.n && !synced; ++i)
+      while (h[i] == COLLECT_EMPTY) {
+        __builtin_ia32_pause();
+        if (++spins % 256 == 0 &&
+            std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count() > WATCH_US) {
+          HC_HIP(hipStreamSynchronize(st));
+          synced = true;
+          break;
+        }
       }
-    }
     std::atomic_thread_fence(std::memory_order_acquire);
   } else {
     double* dev = (double*)S->dmask;   // not in use between two step trials
-    collect(c, dev, nullptr, 0, st);
+    collect(c, dev, st);
     HC_HIP(hipMemcpyAsync(S->hpart, dev, c.n * sizeof(double), hipMemcpyDeviceToHost, st));
     HC_HIP(hipStreamSynchronize(st));
   }
@@ -3055,7 +3055,6 @@ void bind(hc_solver* S, const hc_device* dev) {
     void* d = nullptr;
     if (hipHostGetDevicePointer(&d, S->hpart, 0) == hipSuccess) S->hmap = (double*)d;
     else (void)hipGetLastError();
-    S->hpart[RB_FLAG] = 0.0;   // all bits clear, as rb_seq
   }
   S->clock.events = S->own_stage;
   vfill(1, 0.0, (double*)S->dhits, st);

@@ -78,9 +78,9 @@ void resid_launch(const ResidArgs& a, double* partial, int* nbn, int* nbm, hipSt
 void dir_dots(int64_t n, int64_t m, double pc, const double* Px, const double* q, const double* x1, const double* x2,
               const double* b, const double* z1, const double* z2, double* partial, int* nbn, int* nbm,
               hipStream_t st);
-// Combines partials, op by op in a fixed order, into out[0 .. n) and then
-// writes seq to *flag (when given): with out and flag in pinned host memory
-// the host has the values without a copy.
+// Combines partials, op by op in a fixed order, into out[0 .. n), each with one
+// store and none of them COLLECT_EMPTY (a NaN): with out in mapped host memory
+// filled with it, the host sees every value arrive without a copy.
 // MAX: of magnitudes (from 0, a NaN stays a NaN); MIN, TOP: smallest, largest
 // value (NaN ignored); INT: *(int*)p
 enum { COLLECT_SUM = 0, COLLECT_MAX = 1, COLLECT_MIN = 2, COLLECT_TOP = 3, COLLECT_INT = 4 };
@@ -96,7 +96,8 @@ struct Collect {
     op[n++] = CollectOp{p, (int32_t)cnt, stride, kind};
   }
 };
-void collect(const Collect& c, double* out, unsigned long long* flag, unsigned long long seq, hipStream_t st);
+constexpr unsigned long long COLLECT_EMPTY = 0x7ff8feedfacebeefull;
+void collect(const Collect& c, double* out, hipStream_t st);
 void combine_max(int nb, const double* partial, double* out, hipStream_t st);
 void to_f32(int64_t n, const double* x, const double* scale, float* y, hipStream_t st);
 void from_f32(int64_t n, const float* x, const double* scale, double* y, hipStream_t st);
