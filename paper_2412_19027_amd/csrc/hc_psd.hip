@@ -70,6 +70,20 @@ template <int KM, typename F> __device__ inline void psd_each(int k, F&& f) {
   for (int q = 0; q < 4; ++q) f(i0 + Psd<KM>::RS * q, l, i0 + Psd<KM>::RS * q < k && l < k);
 }
 
+// e with 2^e times the largest magnitude of the workgroup's entries in [1, 2)
+// (0 for zeros, and beside an infinity), the same in every thread; w: four
+// doubles of LDS that nobody reads any more
+template <int KM> __device__ inline int psd_unit_exp(const double (&d)[4], double* w) {
+  double big = fmax(fmax(fabs(d[0]), fabs(d[1])), fmax(fabs(d[2]), fabs(d[3])));
+  for (int off = 32; off > 0; off >>= 1) big = fmax(big, __shfl_xor(big, off, 64));
+  if (Psd<KM>::NT > 64) {
+    if ((threadIdx.x & 63) == 0) w[threadIdx.x >> 6] = big;
+    __syncthreads();
+    big = fmax(fmax(w[0], w[1]), fmax(w[2], w[3]));
+  }
+  return big > 0.0 && big < INFINITY ? -ilogb(big) : 0;
+}
+
 // C = op(X) op(Y), tx / ty transpose X / Y (C is neither; one 16 x 16 tile per
 // wave).  Lane l holds A[l % 16][l / 16] and B[l / 16][l % 16] of a step and
 // rows l / 16 + 4 r of column l % 16 of the result.
@@ -93,12 +107,19 @@ __device__ inline void psd_mm(const double* X, bool tx, const double* Y, bool ty
 // hold in d: Householder reduction to tridiagonal form, then multisection: 64
 // shifts a round, each lane testing one by the signs of the leading minors of
 // T - x (three-term recurrence, rescaled).  Nine rounds leave 2^-54 of the
-// initial interval, which lies in [-b, b] for b the largest row sum of T.
+// initial interval, which lies in [-b, b] for b the largest row sum of T.  The
+// matrix is first scaled by a power of two to entries below 2, so that neither
+// squares nor the reflection's reciprocal leave the range of a double: a column
+// whose squares add up to less than 1e-280 (entries under 1e-140 of the largest
+// one, which move no eigenvalue) counts as reduced.
 // k reductions of two barriers each; two-sided Jacobi took about seven sweeps
 // of k - 1 rounds with three barriers and twice the matrix through LDS.
 template <int KM> __device__ __forceinline__ double psd_min_eig(double (&d)[4], int k, PsdShared<KM>& sh) {
   const int l = threadIdx.x % KM, lane = threadIdx.x & 63;
   __syncthreads();   // the exchange buffers' previous readers are done
+  const int unit = psd_unit_exp<KM>(d, sh.td);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) d[q] = ldexp(d[q], unit);
   for (int j = 0; j < k - 2; ++j) {
     double *x = sh.ca[j & 1], *pv = sh.cb[j & 1];
     int q = 0;
@@ -110,7 +131,7 @@ template <int KM> __device__ __forceinline__ double psd_min_eig(double (&d)[4], 
     const double xl = l > j && l < k ? x[l] : 0.0, x1 = x[j + 1];
     const double s2 = group_sum<KM>(l > j + 1 ? xl * xl : 0.0);
     if (threadIdx.x == 0) sh.td[j] = x[j];
-    if (s2 == 0.0) {   // nothing to reflect (every thread has the same s2)
+    if (s2 < 1e-280) {   // nothing to reflect (every thread has the same s2)
       if (threadIdx.x == 0) sh.te[j] = x1;
       continue;
     }
@@ -157,7 +178,7 @@ template <int KM> __device__ __forceinline__ double psd_min_eig(double (&d)[4], 
     b = fmax(b, __shfl_xor(b, off, 64));
     dmin = fmin(dmin, __shfl_xor(dmin, off, 64));
   }
-  if (bad || b == 0.0 || k == 1) return dmin;
+  if (bad || b == 0.0 || k == 1) return ldexp(dmin, -unit);
   const int ex = ilogb(b) + 1;   // scaled by a power of two into (-1, 1)
   __syncthreads();
   if (threadIdx.x < KM && (int)threadIdx.x < k) {
@@ -188,7 +209,7 @@ template <int KM> __device__ __forceinline__ double psd_min_eig(double (&d)[4], 
     lo = nlo;
     hi = nhi;
   }
-  return ldexp(0.5 * (lo + hi), ex);
+  return ldexp(0.5 * (lo + hi), ex - unit);
 }
 
 // largest alpha with x + alpha dx PSD (INFINITY if unbounded): Cholesky
