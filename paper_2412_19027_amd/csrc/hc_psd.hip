@@ -71,17 +71,25 @@ template <int KM, typename F> __device__ inline void psd_each(int k, F&& f) {
 }
 
 // e with 2^e times the largest magnitude of the workgroup's entries in [1, 2)
-// (0 for zeros, and beside an infinity), the same in every thread; w: four
-// doubles of LDS that nobody reads any more
+// (less for subnormal ones; 0 beside an infinity or a NaN), the same in every
+// thread, from the entries' upper words; w: LDS that nobody reads any more
 template <int KM> __device__ inline int psd_unit_exp(const double (&d)[4], double* w) {
-  double big = fmax(fmax(fabs(d[0]), fabs(d[1])), fmax(fabs(d[2]), fabs(d[3])));
-  for (int off = 32; off > 0; off >>= 1) big = fmax(big, __shfl_xor(big, off, 64));
+  int h = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) h = max(h, __double2hiint(d[q]) & 0x7fffffff);
+  h = max(h, __builtin_amdgcn_mov_dpp(h, 0xB1, 0xf, 0xf, true));    // as group_sum
+  h = max(h, __builtin_amdgcn_mov_dpp(h, 0x4E, 0xf, 0xf, true));
+  h = max(h, __builtin_amdgcn_mov_dpp(h, 0x141, 0xf, 0xf, true));
+  h = max(h, __builtin_amdgcn_mov_dpp(h, 0x140, 0xf, 0xf, true));
+  h = max(max(__builtin_amdgcn_readlane(h, 0), __builtin_amdgcn_readlane(h, 16)),
+          max(__builtin_amdgcn_readlane(h, 32), __builtin_amdgcn_readlane(h, 48)));
   if (Psd<KM>::NT > 64) {
-    if ((threadIdx.x & 63) == 0) w[threadIdx.x >> 6] = big;
+    int* hw = reinterpret_cast<int*>(w);
+    if ((threadIdx.x & 63) == 0) hw[threadIdx.x >> 6] = h;
     __syncthreads();
-    big = fmax(fmax(w[0], w[1]), fmax(w[2], w[3]));
+    h = max(max(hw[0], hw[1]), max(hw[2], hw[3]));
   }
-  return big > 0.0 && big < INFINITY ? -ilogb(big) : 0;
+  return h < 0x7ff00000 ? 1023 - max(h >> 20, 1) : 0;
 }
 
 // C = op(X) op(Y), tx / ty transpose X / Y (C is neither; one 16 x 16 tile per
@@ -326,11 +334,24 @@ __device__ inline void rr_pair(int kk, int r, int i, int& p, int& q) {
 }
 
 // one-sided Jacobi (Hestenes) on the columns of B (k x k): on return the
-// columns are orthogonal and W accumulates B_in W = B_out.  G lanes per pair,
-// two rows each; a pair is skipped when |b_p'b_q| <= 1e-15 |b_p||b_q|.
-template <int KM> __device__ __forceinline__ void psd_jacobi_cols(double* B, int k, double* W, int* flag) {
+// columns are orthogonal and W accumulates 2^e B_in W = B_out, e the returned
+// power that takes B's largest entry into [1, 2) (squares of products of
+// columns stay in range).  G lanes per pair, two rows each; a pair is skipped
+// when |b_p'b_q| <= 1e-15 |b_p||b_q|.
+template <int KM>
+__device__ __forceinline__ int psd_jacobi_cols(double* B, int k, double* W, int* flag, PsdShared<KM>& sh) {
   constexpr int LD = Psd<KM>::LD, G = Psd<KM>::G;
-  psd_each<KM>(k, [&](int i, int l, bool in) { W[i * LD + l] = in && i == l ? 1.0 : 0.0; });
+  double d[4];
+  int n = 0;
+  __syncthreads();   // B is complete
+  psd_each<KM>(k, [&](int i, int l, bool in) { d[n++] = in ? B[i * LD + l] : 0.0; });
+  const int e = psd_unit_exp<KM>(d, sh.td);
+  n = 0;
+  psd_each<KM>(k, [&](int i, int l, bool in) {
+    if (in) B[i * LD + l] = ldexp(d[n], e);
+    W[i * LD + l] = in && i == l ? 1.0 : 0.0;
+    ++n;
+  });
   const int kk = (k + 1) & ~1, np = kk / 2, grp = threadIdx.x / G, sub = threadIdx.x % G;
   for (int sweep = 0; sweep < 60; ++sweep) {
     bool any = false;
@@ -379,6 +400,7 @@ template <int KM> __device__ __forceinline__ void psd_jacobi_cols(double* B, int
     if (!*flag) break;
   }
   __syncthreads();
+  return e;
 }
 
 // squared norms of B's columns
@@ -447,8 +469,8 @@ __global__ __launch_bounds__(Psd<KM>::NT) void k_psd_scale(SegTable tb, const do
   }
   __syncthreads();
   psd_mm<KM>(Lz, true, Ls, false, k, B);   // B = Lz' Ls
-  psd_jacobi_cols<KM>(B, k, W, &flag);     // B W = U diag(lam), V = W
-  if (tid < k) lam[tid] = sqrt(psd_col_norm2<KM>(B, k, tid));
+  const int eb = psd_jacobi_cols<KM>(B, k, W, &flag, sh);   // B W = U diag(lam) (now 2^eb of it), V = W
+  if (tid < k) lam[tid] = ldexp(sqrt(psd_col_norm2<KM>(B, k, tid)), -eb);
   __syncthreads();
   // R = Ls V lam^-1/2 ; Rinv = lam^-1/2 U' Lz' with U = B diag(1/lam)
   psd_mm<KM>(Ls, false, W, false, k, R);
@@ -456,12 +478,12 @@ __global__ __launch_bounds__(Psd<KM>::NT) void k_psd_scale(SegTable tb, const do
   psd_each<KM>(k, [&](int i, int, bool in) {
     const double r = in ? R[i * LD + l] / sqrt(lam[l]) : 0.0;
     R[i * LD + l] = r;
-    if (in) Ri[i * LD + l] = Ri[i * LD + l] / lam[i] / sqrt(lam[i]);
+    if (in) Ri[i * LD + l] = ldexp(Ri[i * LD + l], -eb) / lam[i] / sqrt(lam[i]);
     // M = R R' = Q diag(m) Q': one-sided Jacobi on the columns of R' (in Ls) gives Q (in W)
     Ls[l * LD + i] = r;
   });
-  psd_jacobi_cols<KM>(Ls, k, W, &flag);
-  if (tid < k) m[tid] = psd_col_norm2<KM>(Ls, k, tid);
+  const int em = psd_jacobi_cols<KM>(Ls, k, W, &flag, sh);
+  if (tid < k) m[tid] = ldexp(psd_col_norm2<KM>(Ls, k, tid), -2 * em);
   __syncthreads();
   double* st = g.state + c * (3 * k * k + 2 * k);
   psd_each<KM>(k, [&](int i, int, bool in) {

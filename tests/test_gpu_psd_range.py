@@ -37,3 +37,15 @@ def test_step_of_a_scaled_direction(k, e):
     s, dx = C.svec(spd(3, k, rng)), rng.standard_normal((3, k * (k + 1) // 2))
     got = HC.test_cone_step(HC.PSD, k, T(s), T(s), T(np.ldexp(dx, e)), T(0 * dx), np.inf)
     assert relerr(got * 2.0 ** (e // 2) * 2.0 ** (e // 2), C.psd_step(s, dx, k)) < 1e-12
+
+
+@pytest.mark.parametrize("k", [2, 15, 16, 17, 32])
+@pytest.mark.parametrize("e", [-300, 300])
+def test_scaling_of_scaled_points(k, e):
+    rng = np.random.default_rng(k)
+    s, z = C.svec(spd(3, k, rng)), C.svec(spd(3, k, rng))
+    H, lam, _ = HC.test_cone_scale(HC.PSD, k, T(np.ldexp(s, e)), T(np.ldexp(z, e)), 1.0)
+    ref = C.psd_scale(s, z, k)
+    assert relerr(H, ref["H"]) < 1e-12
+    lam = np.ldexp(np.sort(lam.cpu().numpy()[:, :k], 1), -e)
+    assert np.abs(lam - np.sort(ref["lam"], 1)).max() < 1e-12 * ref["lam"].max()
