@@ -28,7 +28,7 @@ struct Aux {
 };
 // In-place lower Cholesky of the n x n column-major S (leading dim ld).
 // Linv receives the inverses of the 64 x 64 diagonal factor blocks
-// (linv_elems(n) entries).  Pivots <= tol are replaced by fix and counted.
+// (linv_elems(n) or linv32_elems(n) entries).  Pivots <= tol are replaced by fix and counted.
 // The trailing updates overlap the next panel's factorisation on aux's side
 // stream unless aux->serial; all work is complete with respect to `st` on
 // return.
@@ -79,6 +79,7 @@ enum GemmRole { GEMM_PLAIN, GEMM_AHEAD, GEMM_BEHIND };
 template <typename T>
 void gemm_nt(T* C, int64_t ldc, const T* A, int64_t lda, const T* B, int64_t ldb, int64_t M, int64_t N, int64_t K,
              T alpha, bool lower, int64_t gr, int64_t gc, hipStream_t st, GemmRole role = GEMM_PLAIN);
-int64_t linv_elems(int64_t n);
+int64_t linv_elems(int64_t n);     // FP64: the inverses, then the panels' tiles on their way (none for n = 0)
+int64_t linv32_elems(int64_t n);   // FP32: the inverses alone
 double cholesky_flops(int64_t n);
 }  // namespace hc

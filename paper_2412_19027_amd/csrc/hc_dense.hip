@@ -1393,7 +1393,7 @@ __global__ __launch_bounds__(512) void k_tri_bwd(const double* __restrict__ L, i
 }
 
 int64_t tri_inv_elems(int64_t n) { return ceil_div(n, TB) * TB * TB; }
-int64_t tri_exchange_elems(int64_t n) { return 4 * n + 1; }
+int64_t tri_exchange_elems(int64_t n) { return n > 0 ? 4 * n + 1 : 0; }
 
 void tri_envelope(int64_t n, const int64_t* last, std::vector<int32_t>& lo, std::vector<int32_t>& hi) {
   const int64_t nb = ceil_div(n, TB);
@@ -1734,8 +1734,8 @@ template void gemm_nt<double>(double*, int64_t, const double*, int64_t, const do
                               int64_t, double, bool, int64_t, int64_t, hipStream_t, GemmRole);
 template void gemm_nt<float>(float*, int64_t, const float*, int64_t, const float*, int64_t, int64_t, int64_t,
                              int64_t, float, bool, int64_t, int64_t, hipStream_t, GemmRole);
-// the diagonal blocks' inverses, then the FP64 panels' tiles on their way
-int64_t linv_elems(int64_t n) { return (ceil_div(n, BS) + SLOTS) * BS * BS; }
+int64_t linv_elems(int64_t n) { return n > 0 ? (ceil_div(n, BS) + SLOTS) * BS * BS : 0; }
+int64_t linv32_elems(int64_t n) { return ceil_div(n, BS) * BS * BS; }
 
 // factor flops of a dense n x n Cholesky
 double cholesky_flops(int64_t n) { return (double)n * n * n / 3.0; }

@@ -173,7 +173,7 @@ struct hc_solver {
   // two-level split of the Schur complement (leaf blocks + dense tail)
   int64_t nt = 0;                  // tail columns
   std::vector<int64_t> tail_last;  // envelope of the tail (see dense_cholesky), padded to ld
-  std::vector<int32_t> tri_lo, tri_hi;   // and by the triangular solves' blocks (tri_envelope)
+  std::vector<int32_t> tri_env;    // and by the triangular solves' blocks (tri_envelope: lo, then hi)
   bool leaves = false;             // any leaf block
   std::vector<int32_t> col_leaf, col_loc, tail_cols, leaf_size, leaf_cols, leaf_ccnt, leaf_clist;
   std::vector<int64_t> leaf_lval_off, leaf_lcol_off, leaf_clist_off, leaf_cval_off;
@@ -1135,7 +1135,9 @@ void setup_host(hc_solver* S, const hc_problem* p) {
   build_lowrank(S, nd);
   S->ld = ((S->nt + 63) / 64) * 64;
   for (int64_t t = S->nt; t < S->ld; ++t) S->tail_last.push_back(t + 1);   // identity padding
-  tri_envelope(S->nt, S->tail_last.data(), S->tri_lo, S->tri_hi);
+  std::vector<int32_t> tri_hi;
+  tri_envelope(S->nt, S->tail_last.data(), S->tri_env, tri_hi);
+  S->tri_env.insert(S->tri_env.end(), tri_hi.begin(), tri_hi.end());
   if (S->st.static_reg <= 0) S->st.static_reg = S->mixed ? 3.4526698300124393e-04 : 1e-8;
   if (S->st.dyn_reg < 0) S->st.dyn_reg = S->mixed ? std::ldexp(1.0, -46) : std::ldexp(1.0, -104);
   if (S->st.ir_mu_frac < 0) S->st.ir_mu_frac = S->mixed ? 1e-3 : 0.0;
@@ -2876,11 +2878,11 @@ void alloc_all(hc_solver* S, Buf& buf, hipStream_t st) {
   S->tri.n = nt;
   S->tri.inv = buf.take<double>(tri_inv_elems(nt));
   S->tri.ex = buf.take<double>(tri_exchange_elems(nt));
-  S->tri.lo = upload(buf, S->tri_lo, st);
-  S->tri.hi = upload(buf, S->tri_hi, st);
+  S->tri.lo = upload(buf, S->tri_env, st);
+  S->tri.hi = S->tri.lo + S->tri_env.size() / 2;
   if (S->mixed) {
     S->dS32 = buf.take<float>((size_t)S->ld * ntp);
-    S->dLinv32 = buf.take<float>(linv_elems(ntp));
+    S->dLinv32 = buf.take<float>(linv32_elems(ntp));
     S->dX256f = buf.take<float>(inv256_elems(ntp));
     S->dXT256f = buf.take<float>(inv256_elems(ntp));
     S->sb32 = buf.take<float>(2 * nt);   // two right-hand sides (kkt_solve_pair)

@@ -322,7 +322,7 @@ int32_t hc_test_dense_chol_solve_env(int32_t precision, int64_t n, int64_t ld, d
     try {
       if (precision == HC_PRECISION_MIXED) {
         float* A32 = (float*)al((size_t)ld * n * 4);
-        float* L32 = (float*)al(linv_elems(n) * 4);
+        float* L32 = (float*)al(linv32_elems(n) * 4);
         float* b32 = (float*)al((size_t)n * nrhs * 4);
         float* y32 = (float*)al((size_t)n * nrhs * 4);
         float* x32 = (float*)al((size_t)n * nrhs * 4);
