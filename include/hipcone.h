@@ -298,8 +298,10 @@ int32_t hc_test_kkt_solve(hc_solver* s, double mu, int32_t force_dual, const dou
  * after the same scaling and factorisation: one regularised solve
  *   [P + delta I,  A'; A,  -(H + delta I)] [xr; zr] = [r1; r2]
  * (z eliminated through M = (H + delta I)^-1, then S xr = r1 + A' M r2), and
- * the unregularised product [kx; kz] = [P xr + A' zr; A xr - H zr].  Host
- * arrays in the internal row order: r1, xr, kx (n); r2, zr, kz (m). */
+ * the unregularised product [kx; kz] = [P xr + A' zr; A xr - H zr].  Both by
+ * the launches of one refinement step from zero (info.ir_solves counts it),
+ * the product as [r1; r2] minus the residual that step leaves.  Host arrays in
+ * the internal row order: r1, xr, kx (n); r2, zr, kz (m). */
 int32_t hc_test_kkt_ops(hc_solver* s, double mu, int32_t force_dual, const double* r1,
                         const double* r2, double* xr, double* zr, double* kx, double* kz);
 

@@ -84,16 +84,14 @@ struct Csr {          // device CSR, int32 indices
   int32_t* rowptr = nullptr;
   int32_t* col = nullptr;
   double* val = nullptr;
-  int32_t lanes = 1;  // lanes per row used by spmv
-  // rows longer than long_nnz entries (a few long rows among short ones) are
-  // left to a second kernel with one wave per row
+  int32_t lanes = 1;  // lanes per row of a product
+  // rows longer than long_nnz entries (a few long rows among short ones) take a
+  // workgroup each
   int32_t long_nnz = 0x7fffffff;
   int32_t nlong = 0;
   int32_t* longrows = nullptr;
 };
 
-// y = alpha * A x + beta * y
-void spmv(const Csr& A, const double* x, double* y, double alpha, double beta, hipStream_t st);
 // y[rows_i] += alpha * (Ad x)_i for the dense rows Ad (nd x n row-major;
 // column j is variable cols[j], or j when cols is null)
 void dense_rows_gemv(int nd, int64_t n, const double* Ad, const int32_t* rows, const int32_t* cols, const double* x,
@@ -106,15 +104,6 @@ int64_t dense_rows_t_parts(int nd);
 
 // generic fused vector kernels
 void vaxpby(int64_t n, double a, const double* x, double b, double* y, hipStream_t st);   // y = a x + b y
-void vcopy(int64_t n, const double* x, double* y, hipStream_t st);
 void vfill(int64_t n, double v, double* y, hipStream_t st);
-
-// reductions: each returns per-block partials that the host combines in order
-struct Reducer {
-  double* dev = nullptr;    // partials, device
-  double* host = nullptr;   // pinned host copy
-  int nblocks = 0;
-  int nvals = 0;
-};
 
 }  // namespace hc

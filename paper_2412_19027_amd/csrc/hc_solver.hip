@@ -235,7 +235,7 @@ struct hc_solver {
   double tau = 1, kappa = 1;
   double *Px, *Ax, *Atz, *rdv, *rpv;   // rdv = Px + A'z + q tau ; rpv = -Ax - s + b tau
   double *x2, *z2, *x1, *z1, *dx, *dz, *dsv, *dsrhs, *dxa, *dza, *dsa;
-  double *r1, *r2, *irx, *irz, *irxn, *irzn, *irbx, *irbz, *irrx, *irrz, *kx, *kz, *t1, *t2, *u1, *w1;
+  double *r1, *r2, *irx, *irz, *irxn, *irzn, *irbx, *irbz, *irrx, *irrz, *kx, *kz, *t1, *u1, *w1;
   double* sb;                       // diagonal of the tail (mixed mode)
   // the second system's refinement vectors (kkt_solve_pair) and the constant
   // system's first block
@@ -1815,17 +1815,6 @@ struct Red {
   }
 };
 
-void A_mul(hc_solver* S, const double* x, double* y, double alpha, double beta) {
-  spmv(S->dA, x, y, alpha, beta, S->stream);
-  // with leaf blocks the dense rows are stored on the tail columns only
-  dense_rows_gemv((int)S->drows.size(), S->leaves ? S->nt : S->n, S->dAd, S->ddrows,
-                  S->leaves ? S->cm.tcols : nullptr, x, y, alpha, S->stream);
-}
-void At_mul(hc_solver* S, const double* z, double* y, double alpha, double beta) {
-  spmv(S->dAt, z, y, alpha, beta, S->stream);
-  dense_rows_gemv_t((int)S->drows.size(), S->leaves ? S->nt : S->n, S->dAd, S->ddrows,
-                    S->leaves ? S->cm.tcols : nullptr, z, y, alpha, S->dDrT, S->stream);
-}
 // Cone-layer probes (settings.profile): an event pair on the handle's stream
 // around each group of cone launches, and the algorithmic HBM bytes of every
 // launch from its segment's size: what the step must read and write at least
@@ -1867,19 +1856,6 @@ struct ConeProbe {
     if (S->st.profile && S->cprof) (void)hipEventRecord(S->cprof->next(), S->stream);
   }
 };
-
-void P_mul(hc_solver* S, const double* x, double* y, double alpha, double beta) {
-  if (S->dP.nnz == 0) {
-    if (beta == 0.0) vfill(S->n, 0.0, y, S->stream);
-    else if (beta != 1.0) vaxpby(S->n, 0.0, x, beta, y, S->stream);
-    return;
-  }
-  spmv(S->dP, x, y, alpha, beta, S->stream);
-}
-void H_apply(hc_solver* S, int mode, const double* x, double* y) {
-  ConeProbe probe(S, CO_APPLY);
-  cone_apply_all(S->sdev, mode, S->delta, x, nullptr, y, S->stream);
-}
 
 // unit diagonal on the padding rows [nt, ntp) of the dense tail
 __global__ void k_pad_identity(int64_t nt, int64_t ntp, int64_t ld, double* __restrict__ S) {
@@ -2066,20 +2042,6 @@ void schur_solve_n(hc_solver* S, int k, const double* const* u, double* const* x
   }
   if (S->leaves) leaf_backward(S->cm, w, k, st);
 }
-void schur_solve(hc_solver* S, const double* u, double* x) { schur_solve_n(S, 1, &u, &x); }
-
-// K_reg [x; z] = [r1; r2]:  z = M (A x - r2),  S x = r1 + A' M r2
-void solve_reg(hc_solver* S, const double* r1, const double* r2, double* x, double* z) {
-  hipStream_t st = S->stream;
-  H_apply(S, 1, r2, S->t1);                    // t1 = M r2
-  vcopy(S->n, r1, S->u1, st);
-  At_mul(S, S->t1, S->u1, 1.0, 1.0);           // u1 = r1 + A' t1
-  schur_solve(S, S->u1, x);
-  A_mul(S, x, S->w1, 1.0, 0.0);                // w1 = A x
-  vaxpby(S->m, -1.0, r2, 1.0, S->w1, st);      // w1 -= r2
-  H_apply(S, 1, S->w1, z);
-}
-
 // y = a x + b c over n entries
 RowJob lin_job(int64_t n, double a, const double* x, double b, const double* c, double* y) {
   RowJob j;
@@ -2124,17 +2086,126 @@ IRSys ir_second(hc_solver* S, const double* r1, const double* r2, double** xo, d
                S->jkx, S->u1b, S->kz, S->jkz};
 }
 
-// Iterative refinement against the unregularised K of one system or of two in
-// lockstep: each step's Schur solves share one pass of the triangular solves
-// and its products, cone applications and sums go side by side in common
-// launches (a step is eight of them, and one read-back of the residual norms);
-// a system leaves the loop under its own stopping test.
-int64_t refine(hc_solver* S, IRSys* sy, int ns) {
+// One refinement step of one or two systems (act[0 .. k)): the regularised
+// system's solution for the residual (rx, rz) on top of the iterate, into the
+// buffers next() names, the residual r - K [x; z] it leaves with the
+// unregularised K in (rxb, rzb), and that residual's norms in rn.  The Schur
+// solves share one pass of the triangular solves; products, cone applications
+// and sums go side by side in common launches (eight of them, and one read-back
+// of the norms).
+void refine_step(hc_solver* S, IRSys* const* act, int k, double* rn) {
   hipStream_t st = S->stream;
   const int64_t n = S->n, m = S->m;
   const int nd = (int)S->drows.size();
   const int64_t ncol = S->leaves ? S->nt : n;                       // columns the dense rows are stored on
   const int32_t* dcols = S->leaves ? S->cm.tcols : nullptr;
+  ApplySys as[2];
+  const double* us[2];
+  double* xs[2];
+  // Schur right-hand side u = r1 + A' M r2 of the residual
+  for (int r = 0; r < k; ++r) as[r] = ApplySys{act[r]->rz, act[r]->t, nullptr, nullptr, nullptr};
+  {
+    ConeProbe probe(S, CO_APPLY, 0, nullptr, k);
+    cone_apply_sys(S->sdev, 1, S->delta, EPI_PUT, as, k, st);
+  }
+  RowJobs ju;
+  for (int r = 0; r < k; ++r) {
+    IRSys& y = *act[r];
+    RowJob j(ROW_MUL, S->dAt, y.t, y.u);
+    j.c = y.rx;
+    j.beta = 1.0;
+    ju.add(j);
+    us[r] = y.u;
+    xs[r] = y.cur < 0 ? y.xb[y.next()] : y.kx;
+  }
+  row_jobs(ju, st);
+  for (int r = 0; r < k && nd; ++r)
+    dense_rows_gemv_t(nd, ncol, S->dAd, S->ddrows, dcols, act[r]->t, act[r]->u, 1.0, S->dDrT, st);
+  schur_solve_n(S, k, us, xs);
+  // correction's z = M (A x - r2), on top of the iterate
+  RowJobs jw;
+  for (int r = 0; r < k; ++r) {
+    IRSys& y = *act[r];
+    RowJob j(ROW_MUL, S->dA, xs[r], y.w);
+    if (!nd) {
+      j.c = y.rz;
+      j.beta = -1.0;
+    }
+    jw.add(j);
+    if (y.cur >= 0) jw.add(lin_job(n, 1.0, y.xb[y.cur], 1.0, y.kx, y.xb[y.next()]));
+  }
+  row_jobs(jw, st);
+  if (nd) {   // the dense rows' part, then - r2
+    RowJobs js;
+    for (int r = 0; r < k; ++r) {
+      dense_rows_gemv(nd, ncol, S->dAd, S->ddrows, dcols, xs[r], act[r]->w, 1.0, st);
+      js.add(lin_job(m, -1.0, act[r]->rz, 1.0, act[r]->w, act[r]->w));
+    }
+    row_jobs(js, st);
+  }
+  const bool first = act[0]->cur < 0;   // of both, if there are two
+  for (int r = 0; r < k; ++r) {
+    IRSys& y = *act[r];
+    as[r] = ApplySys{y.w, y.zb[y.next()], first ? nullptr : y.zb[y.cur], nullptr, nullptr};
+  }
+  {
+    ConeProbe probe(S, CO_APPLY, 0, nullptr, k);
+    cone_apply_sys(S->sdev, 1, S->delta, first ? EPI_PUT : EPI_ADD, as, k, st);
+  }
+  // residual r - K [x; z] with the unregularised K, and its norm
+  Collect c;
+  RowJobs jp, jr, jd;
+  int64_t off = 0;
+  for (int r = 0; r < k; ++r) {
+    IRSys& y = *act[r];
+    double *xn = y.xb[y.next()], *zn = y.zb[y.next()];
+    RowJob j(nd ? ROW_SUM : ROW_RESID, S->dAt, zn, y.rxb);
+    j.c = y.r1;
+    if (S->dP.nnz > 0 && RowJob::pairs(S->dAt, S->dP)) {
+      j.second(S->dP, xn);
+    } else if (S->dP.nnz > 0) {
+      jp.add(RowJob(ROW_MUL, S->dP, xn, y.kx));
+      j.addp = y.kx;
+    }
+    RowJob d = lin_job(n, -1.0, y.rxb, 1.0, y.r1, y.rxb);   // with dense rows: r1 - (P x + A' z) once they are in
+    RowJob& fin = nd ? d : j;
+    fin.pmax = S->dpart + off;
+    c.add(fin.pmax, fin.blocks(), 1, COLLECT_MAX);
+    off += fin.blocks();
+    if (nd) jd.add(d);
+    jr.add(j);
+    jr.add(RowJob(ROW_MUL, S->dA, xn, y.w));
+  }
+  row_jobs(jp, st);
+  row_jobs(jr, st);
+  for (int r = 0; r < k && nd; ++r) {
+    IRSys& y = *act[r];
+    dense_rows_gemv_t(nd, ncol, S->dAd, S->ddrows, dcols, y.zb[y.next()], y.rxb, 1.0, S->dDrT, st);
+    dense_rows_gemv(nd, ncol, S->dAd, S->ddrows, dcols, y.xb[y.next()], y.w, 1.0, st);
+  }
+  row_jobs(jd, st);
+  const int64_t zparts = cone_apply_parts(S->sdev);
+  for (int r = 0; r < k; ++r) {
+    IRSys& y = *act[r];
+    as[r] = ApplySys{y.zb[y.next()], y.rzb, y.w, y.r2, S->dpart + off};
+    c.add(S->dpart + off, zparts, 1, COLLECT_MAX);
+    off += zparts;
+  }
+  {
+    ConeProbe probe(S, CO_APPLY, 0, nullptr, k);
+    cone_apply_sys(S->sdev, 0, S->delta, EPI_RESID, as, k, st);
+  }
+  double v[4];
+  fetch(S, c, v);
+  for (int r = 0; r < k; ++r) rn[r] = std::isnan(v[r]) || std::isnan(v[k + r]) ? NAN : std::max(v[r], v[k + r]);
+  S->info.ir_solves += k;
+}
+
+// Iterative refinement against the unregularised K of one system or of two in
+// lockstep; a system leaves the loop under its own stopping test.
+int64_t refine(hc_solver* S, IRSys* sy, int ns) {
+  hipStream_t st = S->stream;
+  const int64_t n = S->n, m = S->m;
   {
     Collect c;
     int64_t off = 0;
@@ -2168,122 +2239,24 @@ int64_t refine(hc_solver* S, IRSys* sy, int ns) {
     for (int r = 0; r < ns; ++r)
       if (!sy[r].done) act[k++] = &sy[r];
     if (k == 0) break;
-    ApplySys as[2];
-    const double* us[2];
-    double* xs[2];
-    // Schur right-hand side u = r1 + A' M r2 of the residual
-    for (int r = 0; r < k; ++r) as[r] = ApplySys{act[r]->rz, act[r]->t, nullptr, nullptr, nullptr};
-    {
-      ConeProbe probe(S, CO_APPLY, 0, nullptr, k);
-      cone_apply_sys(S->sdev, 1, S->delta, EPI_PUT, as, k, st);
-    }
-    RowJobs ju;
-    for (int r = 0; r < k; ++r) {
-      IRSys& y = *act[r];
-      RowJob j(ROW_MUL, S->dAt, y.t, y.u);
-      j.c = y.rx;
-      j.beta = 1.0;
-      ju.add(j);
-      us[r] = y.u;
-      xs[r] = y.cur < 0 ? y.xb[y.next()] : y.kx;
-    }
-    row_jobs(ju, st);
-    for (int r = 0; r < k && nd; ++r)
-      dense_rows_gemv_t(nd, ncol, S->dAd, S->ddrows, dcols, act[r]->t, act[r]->u, 1.0, S->dDrT, st);
-    schur_solve_n(S, k, us, xs);
-    // correction's z = M (A x - r2), on top of the iterate
-    RowJobs jw;
-    for (int r = 0; r < k; ++r) {
-      IRSys& y = *act[r];
-      RowJob j(ROW_MUL, S->dA, xs[r], y.w);
-      if (!nd) {
-        j.c = y.rz;
-        j.beta = -1.0;
-      }
-      jw.add(j);
-      if (y.cur >= 0) jw.add(lin_job(n, 1.0, y.xb[y.cur], 1.0, y.kx, y.xb[y.next()]));
-    }
-    row_jobs(jw, st);
-    if (nd) {   // the dense rows' part, then - r2
-      RowJobs js;
-      for (int r = 0; r < k; ++r) {
-        dense_rows_gemv(nd, ncol, S->dAd, S->ddrows, dcols, xs[r], act[r]->w, 1.0, st);
-        js.add(lin_job(m, -1.0, act[r]->rz, 1.0, act[r]->w, act[r]->w));
-      }
-      row_jobs(js, st);
-    }
-    const bool first = act[0]->cur < 0;   // of both, if there are two
-    for (int r = 0; r < k; ++r) {
-      IRSys& y = *act[r];
-      as[r] = ApplySys{y.w, y.zb[y.next()], first ? nullptr : y.zb[y.cur], nullptr, nullptr};
-    }
-    {
-      ConeProbe probe(S, CO_APPLY, 0, nullptr, k);
-      cone_apply_sys(S->sdev, 1, S->delta, first ? EPI_PUT : EPI_ADD, as, k, st);
-    }
+    double rn[2];
+    refine_step(S, act, k, rn);
     solves += k;
-    // residual r - K [x; z] with the unregularised K, and its norm
-    Collect c;
-    RowJobs jp, jr, jd;
-    int64_t off = 0;
     for (int r = 0; r < k; ++r) {
       IRSys& y = *act[r];
-      double *xn = y.xb[y.next()], *zn = y.zb[y.next()];
-      RowJob j(nd ? ROW_SUM : ROW_RESID, S->dAt, zn, y.rxb);
-      j.c = y.r1;
-      if (S->dP.nnz > 0 && RowJob::pairs(S->dAt, S->dP)) {
-        j.second(S->dP, xn);
-      } else if (S->dP.nnz > 0) {
-        jp.add(RowJob(ROW_MUL, S->dP, xn, y.kx));
-        j.addp = y.kx;
-      }
-      RowJob d = lin_job(n, -1.0, y.rxb, 1.0, y.r1, y.rxb);   // with dense rows: r1 - (P x + A' z) once they are in
-      RowJob& fin = nd ? d : j;
-      fin.pmax = S->dpart + off;
-      c.add(fin.pmax, fin.blocks(), 1, COLLECT_MAX);
-      off += fin.blocks();
-      if (nd) jd.add(d);
-      jr.add(j);
-      jr.add(RowJob(ROW_MUL, S->dA, xn, y.w));
-    }
-    row_jobs(jp, st);
-    row_jobs(jr, st);
-    for (int r = 0; r < k && nd; ++r) {
-      IRSys& y = *act[r];
-      dense_rows_gemv_t(nd, ncol, S->dAd, S->ddrows, dcols, y.zb[y.next()], y.rxb, 1.0, S->dDrT, st);
-      dense_rows_gemv(nd, ncol, S->dAd, S->ddrows, dcols, y.xb[y.next()], y.w, 1.0, st);
-    }
-    row_jobs(jd, st);
-    const int64_t zparts = cone_apply_parts(S->sdev);
-    for (int r = 0; r < k; ++r) {
-      IRSys& y = *act[r];
-      as[r] = ApplySys{y.zb[y.next()], y.rzb, y.w, y.r2, S->dpart + off};
-      c.add(S->dpart + off, zparts, 1, COLLECT_MAX);
-      off += zparts;
-    }
-    {
-      ConeProbe probe(S, CO_APPLY, 0, nullptr, k);
-      cone_apply_sys(S->sdev, 0, S->delta, EPI_RESID, as, k, st);
-    }
-    double v[4];
-    fetch(S, c, v);
-    for (int r = 0; r < k; ++r) {
-      IRSys& y = *act[r];
-      const double a = v[r], b = v[k + r];
-      const double rn = std::isnan(a) || std::isnan(b) ? NAN : std::max(a, b);
       const int nx = y.next();
-      if (rn < y.best) {
-        y.best = rn;
+      if (rn[r] < y.best) {
+        y.best = rn[r];
         y.bst = nx;
       }
-      if (rn <= y.target || (it > 0 && rn > 0.5 * y.rnorm)) {
+      if (rn[r] <= y.target || (it > 0 && rn[r] > 0.5 * y.rnorm)) {
         y.done = true;
         continue;
       }
       y.cur = nx;
       y.rx = y.rxb;
       y.rz = y.rzb;
-      y.rnorm = rn;
+      y.rnorm = rn[r];
     }
   }
   for (int r = 0; r < ns; ++r) {
@@ -2302,7 +2275,6 @@ int64_t refine(hc_solver* S, IRSys* sy, int ns) {
     S->jrx = sy[1].xb[0], S->jrxn = sy[1].xb[1], S->jrbx = sy[1].xb[2];
     S->jrz = sy[1].zb[0], S->jrzn = sy[1].zb[1], S->jrbz = sy[1].zb[2];
   }
-  S->info.ir_solves += solves;
   if (S->st.verbose >= 2)
     for (int r = 0; r < ns; ++r) {
       std::printf("      kkt solve: |rhs| %.3e best residual %.3e (%s) solves %lld\n", sy[r].nb,
@@ -2989,7 +2961,6 @@ void alloc_all(hc_solver* S, Buf& buf, hipStream_t st) {
   for (double** v : vecs) *v = buf.take<double>(L);
   S->kz = buf.take<double>(L);
   S->t1 = buf.take<double>(L);
-  S->t2 = buf.take<double>(L);
   S->u1 = buf.take<double>(L);
   S->w1 = buf.take<double>(L);
   S->sb = buf.take<double>(nt);
@@ -4000,18 +3971,20 @@ int32_t hc_test_kkt_ops(hc_solver* S, double mu, int32_t force_dual, const doubl
     factor(S);
     HC_HIP(hipMemcpyAsync(S->r1, r1, n * 8, hipMemcpyHostToDevice, st));
     HC_HIP(hipMemcpyAsync(S->r2, r2, m * 8, hipMemcpyHostToDevice, st));
-    solve_reg(S, S->r1, S->r2, S->x1, S->z1);
-    // K [x1; z1] with the unregularised K, as the refinement forms it
-    P_mul(S, S->x1, S->kx, 1.0, 0.0);
-    At_mul(S, S->z1, S->kx, 1.0, 1.0);
-    A_mul(S, S->x1, S->kz, 1.0, 0.0);
-    H_apply(S, 0, S->z1, S->t2);
-    vaxpby(m, -1.0, S->t2, 1.0, S->kz, st);
-    HC_HIP(hipMemcpyAsync(xr, S->x1, n * 8, hipMemcpyDeviceToHost, st));
-    HC_HIP(hipMemcpyAsync(zr, S->z1, m * 8, hipMemcpyDeviceToHost, st));
-    HC_HIP(hipMemcpyAsync(kx, S->kx, n * 8, hipMemcpyDeviceToHost, st));
-    HC_HIP(hipMemcpyAsync(kz, S->kz, m * 8, hipMemcpyDeviceToHost, st));
+    // one step of the refinement from zero; K [x; z] from the residual it leaves
+    IRSys y = ir_first(S, S->r1, S->r2, nullptr, nullptr);
+    y.rx = y.r1;
+    y.rz = y.r2;
+    IRSys* act[1] = {&y};
+    double rn;
+    refine_step(S, act, 1, &rn);
+    HC_HIP(hipMemcpyAsync(xr, y.xb[y.next()], n * 8, hipMemcpyDeviceToHost, st));
+    HC_HIP(hipMemcpyAsync(zr, y.zb[y.next()], m * 8, hipMemcpyDeviceToHost, st));
+    HC_HIP(hipMemcpyAsync(kx, y.rxb, n * 8, hipMemcpyDeviceToHost, st));
+    HC_HIP(hipMemcpyAsync(kz, y.rzb, m * 8, hipMemcpyDeviceToHost, st));
     HC_HIP(hipStreamSynchronize(st));
+    for (int64_t i = 0; i < n; ++i) kx[i] = r1[i] - kx[i];
+    for (int64_t i = 0; i < m; ++i) kz[i] = r2[i] - kz[i];
   } catch (const Error& e) {
     g_last_error = e.msg;
     return e.code;

@@ -29,7 +29,8 @@ int reduce_launch(int64_t n, const RedOps& ops, double* partial, hipStream_t st)
 //   ROW_SUM    y = A x + p                   p: A2 x2 (second()), addp[row] or 0
 //   ROW_RESID  y = c - (A x + p)
 //   ROW_LIN    y = alpha x + beta c          (no matrix; alpha x rounded first)
-// Sums run in spmv's order.  With pmax, block b of the job (blocks() of them) leaves max |y| over its
+// A row is summed by A.lanes lanes (a long one by 1,024), lane by lane, then
+// across them in a fixed order.  With pmax, block b of the job (blocks() of them) leaves max |y| over its
 // rows in pmax[b] (a NaN stays a NaN).  c may be y.  Rows above A's long_nnz
 // take a workgroup each; A2 must have none, and no more lanes per row than A.
 enum { ROW_MUL = 0, ROW_SUM = 1, ROW_RESID = 2, ROW_LIN = 3 };

@@ -1,4 +1,4 @@
-// Vector, sparse and reduction kernels of the IPM (gfx950): SpMV for A, A'
+// Vector, sparse and reduction kernels of the IPM (gfx950): row jobs with A, A'
 // and P (residuals, eq. residuals-objectives; KKT products), fused axpys,
 // ordered block reductions, and the assembly of the KKT Schur complement.
 #include "hc_vec.h"
@@ -10,76 +10,7 @@ namespace hc {
 // max that propagates NaN (a NaN residual must never pass a test)
 __device__ inline double nmax(double a, double b) { return (a != a || b != b) ? NAN : (a > b ? a : b); }
 
-// ---------------------------------------------------------------------------
-// CSR SpMV: LPR lanes per row (1, 4, 16 or 64), chosen from the mean row length
-// ---------------------------------------------------------------------------
-template <int LPR>
-__global__ __launch_bounds__(256) void k_spmv(int32_t nrows, const int32_t* __restrict__ rp,
-                                              const int32_t* __restrict__ ci, const double* __restrict__ v,
-                                              const double* __restrict__ x, double* __restrict__ y, double alpha,
-                                              double beta, int32_t long_nnz) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t row = t / LPR;
-  const int sub = (int)(t % LPR);
-  double acc = 0.0;
-  bool mine = false;   // rows above long_nnz entries belong to k_spmv_long
-  if (row < nrows) {
-    const int32_t b = rp[row], e = rp[row + 1];
-    mine = (e - b) <= long_nnz;
-    if (mine)
-      for (int32_t p = b + sub; p < e; p += LPR) acc += v[p] * x[ci[p]];
-  }
-#pragma unroll
-  for (int off = LPR / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-  if (mine && sub == 0) y[row] = alpha * acc + (beta == 0.0 ? 0.0 : beta * y[row]);
-}
-
-// the long rows, one wave each
-// one workgroup of 1024 threads per long row (many independent loads in
-// flight for a row of tens of thousands of entries); per-wave shuffle sums
-// meet in LDS in a fixed order
-constexpr int LONG_THREADS = 1024;
-__global__ __launch_bounds__(LONG_THREADS) void k_spmv_long(int32_t nlong, const int32_t* __restrict__ rows,
-                                                            const int32_t* __restrict__ rp,
-                                                            const int32_t* __restrict__ ci,
-                                                            const double* __restrict__ v,
-                                                            const double* __restrict__ x, double* __restrict__ y,
-                                                            double alpha, double beta) {
-  __shared__ double part[LONG_THREADS / 64];
-  if ((int32_t)blockIdx.x >= nlong) return;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int32_t row = rows[blockIdx.x], b = rp[row], e = rp[row + 1];
-  double acc = 0.0;
-  for (int32_t p = b + tid; p < e; p += LONG_THREADS) acc += v[p] * x[ci[p]];
-  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-  if (lane == 0) part[tid >> 6] = acc;
-  __syncthreads();
-  if (tid == 0) {
-    double s = 0.0;
-    for (int w = 0; w < LONG_THREADS / 64; ++w) s += part[w];
-    y[row] = alpha * s + (beta == 0.0 ? 0.0 : beta * y[row]);
-  }
-}
-
-void spmv(const Csr& A, const double* x, double* y, double alpha, double beta, hipStream_t st) {
-  if (A.nrows == 0) return;
-  const int64_t threads = (int64_t)A.nrows * A.lanes;
-  const unsigned grid = (unsigned)ceil_div(threads, 256);
-  const int32_t ln = A.long_nnz;
-  switch (A.lanes) {
-    case 1: hipLaunchKernelGGL(k_spmv<1>, dim3(grid), dim3(256), 0, st, A.nrows, A.rowptr, A.col, A.val, x, y, alpha, beta, ln); break;
-    case 4: hipLaunchKernelGGL(k_spmv<4>, dim3(grid), dim3(256), 0, st, A.nrows, A.rowptr, A.col, A.val, x, y, alpha, beta, ln); break;
-    case 16: hipLaunchKernelGGL(k_spmv<16>, dim3(grid), dim3(256), 0, st, A.nrows, A.rowptr, A.col, A.val, x, y, alpha, beta, ln); break;
-    default: hipLaunchKernelGGL(k_spmv<64>, dim3(grid), dim3(256), 0, st, A.nrows, A.rowptr, A.col, A.val, x, y, alpha, beta, ln); break;
-  }
-  HC_LAUNCH_CHECK();
-  if (A.nlong > 0) {
-    hipLaunchKernelGGL(k_spmv_long, dim3((unsigned)A.nlong), dim3(LONG_THREADS), 0, st, A.nlong, A.longrows,
-                       A.rowptr, A.col, A.val, x, y, alpha, beta);
-    HC_LAUNCH_CHECK();
-  }
-}
-
+// lanes per row of a sparse product, from the mean row length
 int choose_lanes(double mean_nnz) {
   if (mean_nnz <= 6.0) return 1;
   if (mean_nnz <= 24.0) return 4;
@@ -182,10 +113,6 @@ void vlin3(int64_t n, double a, const double* x, double b, const double* y, doub
   hipLaunchKernelGGL(k_lin3, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, st, n, a, x, b, y, c, w, z);
   HC_LAUNCH_CHECK();
 }
-void vcopy(int64_t n, const double* x, double* y, hipStream_t st) {
-  if (n == 0 || x == y) return;
-  HC_HIP(hipMemcpyAsync(y, x, n * sizeof(double), hipMemcpyDeviceToDevice, st));
-}
 __global__ void k_fill(int64_t n, double v, double* __restrict__ y) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) y[i] = v;
@@ -196,7 +123,7 @@ void vfill(int64_t n, double v, double* y, hipStream_t st) {
   HC_LAUNCH_CHECK();
 }
 // ---------------------------------------------------------------------------
-// reductions: per-block partials, combined on the host in block order
+// reductions: per-block partials, combined in block order by k_collect
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_reduce(int64_t n, RedOps ops, double* __restrict__ partial) {
   __shared__ double red[256];
@@ -237,8 +164,7 @@ int reduce_launch(int64_t n, const RedOps& ops, double* partial, hipStream_t st)
 // Row jobs: the sparse products, sums and residuals of a refinement step (of
 // both of its systems), side by side in one launch.  At the sizes where a
 // solve is a chain of short kernels each costs its launch (about 4 us of host
-// time) whatever it does; at the large ones each reads its matrix once, as
-// k_spmv does.  With the cone applications of both systems in one launch and
+// time) whatever it does; at the large ones each reads its matrix once.  With the cone applications of both systems in one launch and
 // the norms read back by k_collect, a small LP (n 50) went from 12.6 to
 // 4.7 ms, an MPC problem of 100 stages from 31 to 15.5 ms per solve.
 // ---------------------------------------------------------------------------
@@ -329,7 +255,7 @@ __global__ __launch_bounds__(256) void k_row_jobs(RowJobs J) {
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     for (int l = blk - nblk; l < j.nlong; l += nl) {
       const int32_t row = j.longrows[l];
-      double acc[4] = {}, p = 0.0;   // four of k_spmv_long's 1,024 lanes each
+      double acc[4] = {}, p = 0.0;   // the row is summed by 1,024 lanes, four to a thread
       const int32_t b = j.rp[row], e = j.rp[row + 1];
       for (int32_t k = b + threadIdx.x; k < e; k += 1024)
 #pragma unroll
