@@ -167,7 +167,7 @@ typedef struct {
   double solve_ms;         /* the iterations                                       */
   double factor_ms;        /* summed over iterations (device events)               */
   double solve_kkt_ms;
-  double cone_ms;
+  double cone_ms;          /* the cone scalings                                   */
   int64_t ir_solves;       /* triangular-solve passes including refinement         */
   int64_t pivot_guard_hits;
   int64_t dual_switches;   /* iterations redone with the dual exp/pow scaling      */

@@ -66,9 +66,10 @@ struct Buf {   // bump allocator over one device block; `dry` only counts bytes
 
 }  // namespace
 
-// Device time of one factorisation: an event pair on the stream it runs on, or
-// (the allocation-free call creates no events) host time with a wait.
-struct FactorClock {
+// Device time of a phase that ends without a read-back: an event pair on the
+// stream it runs on, or (the allocation-free call creates no events) host time
+// with a wait.
+struct PhaseClock {
   hipEvent_t a = nullptr, b = nullptr;
   bool events = true;
   double t0 = 0, ms = 0;
@@ -101,7 +102,7 @@ struct FactorClock {
     HC_HIP(hipEventElapsedTime(&t, a, b));
     return t;
   }
-  ~FactorClock() {
+  ~PhaseClock() {
     if (a) (void)hipEventDestroy(a);
     if (b) (void)hipEventDestroy(b);
   }
@@ -247,7 +248,8 @@ struct hc_solver {
   int status = 0;
   double delta = 0;
   bool px_zero = false;             // Px holds the zeros of a problem without P
-  FactorClock clock;                // the factorisation's time (info.factor_ms)
+  PhaseClock clock;                 // the factorisation's time (info.factor_ms)
+  PhaseClock cone_clock;            // the scalings' (info.cone_ms) where they read nothing back
   double xPx_cache = 0;             // x'Px of the current iterate (from residuals)
   std::unique_ptr<Prof> prof;
   std::unique_ptr<Prof> cprof;      // events around the cone-layer launches (settings.profile)
@@ -2645,12 +2647,14 @@ int iterate(hc_solver* S, const Resid& R) {
   for (int attempt = 0; attempt < 2; ++attempt) {
     double t0 = now_ms();
     int pd = 0;
+    const bool timed = S->mixed && !S->has_nonsym;   // scale_all waits for nothing
+    if (timed) S->cone_clock.start(st);
     const double hmax = scale_all(S, mu, force_dual, &pd);
-    double t1 = now_ms();
+    if (timed) S->cone_clock.stop(st);
+    const double t1 = now_ms();
     S->clock.start(st);
     factor(S, false, hmax);
     S->clock.stop(st);
-    S->info.cone_ms += t1 - t0;
     // constant system K [x2; z2] = [-q; b] and the affine one (r1, r2 from the
     // residuals), refined together
     if (attempt > 0) {   // the combined system's right-hand side took r1 and r2
@@ -2663,6 +2667,8 @@ int iterate(hc_solver* S, const Resid& R) {
                    ir_second(S, S->r1, S->r2, &S->x1, &S->z1, R.nb));
     const double fms = S->clock.read_ms();   // (done: the refinement has read its norms back)
     S->info.factor_ms += fms;
+    const double cms = timed ? S->cone_clock.read_ms() : t1 - t0;
+    S->info.cone_ms += cms;
     const Dir da = direction(S, nullptr, nullptr, gt, S->kappa * S->tau, S->s, S->dxa, S->dza, S->dsa);
     alpha_a = step_length(S, Step{S->dsa, S->dza, da.dtau, da.dkappa}, false);
     sigma = (1.0 - alpha_a) * (1.0 - alpha_a) * (1.0 - alpha_a);
@@ -2681,7 +2687,7 @@ int iterate(hc_solver* S, const Resid& R) {
     }
     dc = direction(S, S->r1, S->r2, f * gt, dk, S->dsrhs, S->dx, S->dz, S->dsv);
     alpha_c = step_length(S, Step{S->dsv, S->dz, dc.dtau, dc.dkappa}, true);
-    S->info.solve_kkt_ms += std::max(0.0, now_ms() - t1 - fms);
+    S->info.solve_kkt_ms += std::max(0.0, now_ms() - t0 - cms - fms);
     if (alpha_c < 0.1 && pd > 0 && !force_dual) {
       force_dual = true;
       S->info.dual_switches++;
@@ -3029,7 +3035,7 @@ void bind(hc_solver* S, const hc_device* dev) {
     if (hipHostGetDevicePointer(&d, S->hpart, 0) == hipSuccess) S->hmap = (double*)d;
     else (void)hipGetLastError();
   }
-  S->clock.events = S->own_stage;
+  S->clock.events = S->cone_clock.events = S->own_stage;
   vfill(1, 0.0, (double*)S->dhits, st);
   if (S->K1 + S->K2 > 0) {   // zero padding rows of the dense-row operand, zero rank-2 rows
     vfill((S->K1 + S->K2) * S->nt, 0.0, S->dBd, st);
