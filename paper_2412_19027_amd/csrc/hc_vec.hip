@@ -229,7 +229,13 @@ __device__ inline double block_nmax(double v, double* red) {
   return nmax(nmax(red[0], red[1]), nmax(red[2], red[3]));
 }
 
-__global__ __launch_bounds__(256) void k_row_jobs(RowJobs J) {
+// Rounds of 1,024 entries of a long row in flight.  A long row is one workgroup's
+// latency: with its four entries a round under a condition each (the compiler
+// then waits for every load) the KKT solves of eight iterations with 20 columns
+// of 200,000 entries took 27.3 ms, with one round loaded together 11.1, two 8.1,
+// four 7.9; two leave the eight waves per SIMD that the short rows had.
+constexpr int LONG_AHEAD = 2;
+__global__ __launch_bounds__(256, 8) void k_row_jobs(RowJobs J) {
   __shared__ double red[16];
   int q = 0;
   while (q + 1 < J.n && (int)blockIdx.x >= J.first[q + 1]) ++q;
@@ -257,7 +263,20 @@ __global__ __launch_bounds__(256) void k_row_jobs(RowJobs J) {
       const int32_t row = j.longrows[l];
       double acc[4] = {}, p = 0.0;   // the row is summed by 1,024 lanes, four to a thread
       const int32_t b = j.rp[row], e = j.rp[row + 1];
-      for (int32_t k = b + threadIdx.x; k < e; k += 1024)
+      int32_t k = b + threadIdx.x;
+      for (; e - k > 1024 * (LONG_AHEAD - 1) + 768; k += 1024 * LONG_AHEAD) {
+        int32_t col[4 * LONG_AHEAD];
+        double v[4 * LONG_AHEAD], x[4 * LONG_AHEAD];
+#pragma unroll
+        for (int q = 0; q < 4 * LONG_AHEAD; ++q) col[q] = j.ci[k + 256 * q];
+#pragma unroll
+        for (int q = 0; q < 4 * LONG_AHEAD; ++q) v[q] = j.v[k + 256 * q];
+#pragma unroll
+        for (int q = 0; q < 4 * LONG_AHEAD; ++q) x[q] = j.x[col[q]];
+#pragma unroll
+        for (int q = 0; q < 4 * LONG_AHEAD; ++q) acc[q % 4] += v[q] * x[q];
+      }
+      for (; k < e; k += 1024)
 #pragma unroll
         for (int h = 0; h < 4; ++h)
           if (k + 256 * h < e) acc[h] += j.v[k + 256 * h] * j.x[j.ci[k + 256 * h]];
