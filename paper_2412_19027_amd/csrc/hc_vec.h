@@ -141,7 +141,7 @@ void dense_T_gather(int64_t n, const int32_t* erp, const int32_t* ee, const int3
 // among them) take workgroups, the others a wave.
 // group_gather: column j of S (rows i >= j) gains sum over the rows r of
 // column j of A, in order, of A[r][j] T_r[i]; one wave per column, the column
-// in LDS chunks of at most GATHER_CHUNK rows.
+// in equal LDS chunks of at most GATHER_CHUNK rows.
 constexpr int GATHER_CHUNK = 5120;
 constexpr int64_t GROUP_WIDE = 1024;
 struct GroupPlan {

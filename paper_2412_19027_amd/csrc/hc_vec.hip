@@ -827,11 +827,17 @@ __device__ inline double lane_d(double v, int l) { return __longlong_as_double(l
 // One wave per column j, its rows in order.  Each row adds a run of (index,
 // value) pairs to the column in LDS; the runs are cut into segments of 64 and
 // GG_AHEAD segments are in flight, since a wave that waits for each row's run
-// spends its time on memory latency (5 waves fit a CU): 2,000 cones of 55 rows
-// on 421 of 5,000 columns, 4.08 -> 0.78 ms (2.1 GB of T and indices; a column's
-// runs start at its own diagonal).  GATHER_CHUNK rows are 40 KB, four waves on a
-// CU; with 4,096 (five waves) a second pass over the runs began 1,000 columns
-// earlier and that workload took 0.93 ms.
+// spends its time on memory latency: 2,000 cones of 55 rows on 421 of 5,000
+// columns, 4.08 -> 0.78 ms (2.1 GB of T and indices; a column's runs start at its
+// own diagonal).  Chunks trade passes over a column's runs against LDS, that is
+// waves on a CU: GATHER_CHUNK rows are 40 KB, four waves, and every further chunk
+// reads the runs again, so a column has as few chunks as that allows and they
+// have equal lengths.  800 cones of 55 rows on 4,600 / 5,200 / 5,700 / 6,400 /
+// 7,200 / 8,000 / 10,000 columns: 351 / 325 / 344 / 423 / 520 / 570 / 823 us; with
+// chunks of 5,120 rows and a rest 350 / 391 / 447 / 518 / 579 / 649 / 823, of 4,096
+// 378 / 449 / 493 / 557 / 615 / 674 / 883.  SOCs of three rows, 11,000 to 16,000 of
+// them on 5,620 / 6,920 / 8,120 columns: 136 / 243 / 416 us, 186 / 268 / 403 and
+// 199 / 282 / 412.
 constexpr int GG_AHEAD = 8;
 __global__ __launch_bounds__(64) void k_group_gather(GroupPlan gp, int64_t n, int chunk,
                                                      const int32_t* __restrict__ atrp,
@@ -897,7 +903,7 @@ __global__ __launch_bounds__(64) void k_group_gather(GroupPlan gp, int64_t n, in
 }
 void group_gather(const GroupPlan& gp, int64_t n, const Csr& At, int64_t ld, double* S, hipStream_t st) {
   if (gp.ng == 0 || n == 0) return;
-  const int chunk = (int)std::min<int64_t>(n, GATHER_CHUNK);
+  const int chunk = (int)ceil_div(n, ceil_div(n, GATHER_CHUNK));
   hipLaunchKernelGGL(k_group_gather, dim3((unsigned)std::min<int64_t>(n, 16384)), dim3(64),
                      (size_t)chunk * sizeof(double), st, gp, n, chunk, At.rowptr, At.val, ld, S);
   HC_LAUNCH_CHECK();
