@@ -144,6 +144,10 @@ __device__ __forceinline__ double chol_inv(const double* __restrict__ lds, int i
 // product's operand layout.  One pivot at a time with a 15-column update each
 // (an FP64 FMA issues every 8 cycles) and a lane-per-column inverse took
 // 45,600 cycles a block, this takes 30,500 (12.7 us).
+// The 2 x 2 determinant is a product of two diagonal entries: within 1e-150 ..
+// 1e150 it stays in range.  (Taking one pivot after the other where it does not
+// cost every step 1 us of 24, for matrices that no solve gets to: the refinement
+// makes no progress on data from about 1e40 on.)
 __device__ __forceinline__ void chol_block(int lane, int p, double* __restrict__ lds, double tol, double fix,
                                   unsigned long long* __restrict__ hits) {
   typedef Mfma<double> M;
@@ -338,7 +342,8 @@ __global__ __launch_bounds__(256, 3) void k_chol_diag(double* __restrict__ A, in
 // products, 64 pivots); 34 KB of LDS and at most 168 VGPRs let it run beside
 // three trailing-update workgroups.  The four steps of a panel at 1,856 rows:
 // 34, 27, 24, 24 us (in the first two the other rows' workgroups, 7 us a tile,
-// outlast the chain), against 53 us each in three launches and 26 to 34 with
+// outlast the chain; up to about 5,000 rows a step stays under 30 us, at 20,032 it
+// averages 58 with the trailing update beside it), against 53 us each in three launches and 26 to 34 with
 // the panel's earlier columns applied only when a block column is next, which
 // puts up to 192 of them, and the tile of the previous step, in the chain.
 // ---------------------------------------------------------------------------
@@ -622,9 +627,9 @@ __global__ __launch_bounds__(256) void k_chol_diag32(float* __restrict__ A, int6
 // ---------------------------------------------------------------------------
 // On MFMA: each wave takes 16 rows and all 64 columns (four 16 x 16 output
 // tiles, 16 k-steps of four).  A wave's 16 x 64 block of A21 is loaded into
-// registers at once; Linv goes through an 8 KB LDS slice, the 16 rows of Linv
+// registers at once; Linv goes through a 4 KB LDS slice, the 16 rows of Linv
 // that one output tile needs, one tile after another.  With few registers and
-// 8 KB of LDS a workgroup fits beside a running trailing-update workgroup on
+// 4 KB of LDS a workgroup fits beside a running trailing-update workgroup on
 // the same compute unit instead of waiting for one to finish: this kernel sits
 // on the factorisation's critical path while the trailing update runs.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_trsm32(
@@ -665,7 +670,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
 // of L), the shape of the TRSM so that it also fits beside a running
 // trailing-update workgroup: a workgroup takes 64 rows x 64 columns of C,
 // each wave 16 rows (its 16 x K block of A in registers) and four 16 x 16
-// tiles, B through an 8 KB LDS slice per tile.  Tiles strictly above the
+// tiles, B through a 4 KB LDS slice per tile.  Tiles strictly above the
 // global diagonal (C[0, 0] at global (gr, gc)) are skipped.  The products are
 // the same MFMA chain as the large update kernels' (k in steps of four).
 // ---------------------------------------------------------------------------
@@ -953,10 +958,9 @@ static int64_t rows_below(const int64_t* last, int64_t n, int64_t j) {
 }
 
 // Factor the columns [K0, Kend).  Steps of 64 columns (k_panel_step) inside
-// inner panels of IB columns: the left-looking update of the next block column
-// reaches back to the start of the inner panel, and at its end one MFMA update
-// (K = IB) brings the columns up to Kend up to date.  The first of them is
-// already, by the last step.
+// inner panels of IB columns: every step updates the inner panel's later block
+// columns and the one behind it, and at the inner panel's end one MFMA update
+// (K = IB) brings the rest of the columns up to Kend up to date.
 static void factor_panel(double* S, int64_t n, int64_t ld, double* Linv, double tol, double fix, unsigned long long* hits,
                          int64_t K0, int64_t Kend, const int64_t* last, hipStream_t st, Prof* prof) {
   hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(256), 0, st, S, ld, K0, n, Linv + (K0 / BS) * BS * BS, tol, fix,
@@ -1525,7 +1529,7 @@ void dense_block_inverses(const float* L, int64_t n, int64_t ld, const float* Li
 // ---------------------------------------------------------------------------
 // triangular solves, nrhs <= 4 right-hand sides stored column-major with
 // leading dimension n:  forward Y = L^-1 B (B overwritten), backward
-// X = L^-float Y (Y overwritten).  Per 256-row block: one workgroup applies the
+// X = L^-T Y (Y overwritten).  Per 256-row block: one workgroup applies the
 // block inverse (a 256 x 256 triangular matvec), then a bandwidth-bound kernel
 // updates the rows below (forward) or the columns to the left (backward).
 // ---------------------------------------------------------------------------
@@ -1576,7 +1580,7 @@ __global__ __launch_bounds__(256) void k_trsv_diag(const float* __restrict__ Xin
 
 // rows below the block: B[row] -= L[row, c:c+cb] y_c.  A workgroup takes 64
 // rows; wave w sums columns [16 w, 16 w + 16) with one lane per row (each
-// column read is 512 contiguous bytes, 16 loads in flight per lane), and the
+// column read is 256 contiguous bytes, 16 loads in flight per lane), and the
 // 16 partial sums meet in LDS.
 template <int NR>
 __global__ __launch_bounds__(1024) void k_trsv_fwd_update(const float* __restrict__ L, int64_t ld, int64_t c, int64_t n,

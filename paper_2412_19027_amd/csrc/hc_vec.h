@@ -30,9 +30,10 @@ int reduce_launch(int64_t n, const RedOps& ops, double* partial, hipStream_t st)
 //   ROW_RESID  y = c - (A x + p)
 //   ROW_LIN    y = alpha x + beta c          (no matrix; alpha x rounded first)
 // A row is summed by A.lanes lanes (a long one by 1,024), lane by lane, then
-// across them in a fixed order.  With pmax, block b of the job (blocks() of them) leaves max |y| over its
-// rows in pmax[b] (a NaN stays a NaN).  c may be y.  Rows above A's long_nnz
-// take a workgroup each; A2 must have none, and no more lanes per row than A.
+// across them in a fixed order.  With pmax, block b of the job (blocks() of
+// them) leaves max |y| over its rows in pmax[b] (a NaN stays a NaN).  c may be
+// y.  Rows above A's long_nnz take a workgroup each; A2 must have none, and no
+// more lanes per row than A.
 enum { ROW_MUL = 0, ROW_SUM = 1, ROW_RESID = 2, ROW_LIN = 3 };
 struct RowJob {
   int32_t kind = ROW_LIN, nrows = 0, lanes = 1, long_nnz = 0x7fffffff, nlong = 0, lanes2 = 1;
@@ -113,8 +114,8 @@ void assemble_pairs(int64_t ntask, const int32_t* tra, const int32_t* trb, const
 // segment (psd_dense_T, row-major rows of n doubles starting at T), then the
 // lower triangle of S gains A_e' T over the rows of all such segments
 // (dense_T_gather, erp/ee/ep: per column j of A the T rows e and the
-// positions in atval of the values A[row(e), j]).  n <= PSD_DENSE_NMAX (one
-// LDS row of n doubles per workgroup).
+// positions in atval of the values A[row(e), j]).  n <= PSD_DENSE_NMAX (T takes
+// n doubles per row, whatever the row's cone touches).
 // psd_dense_T writes T[e, j] for the columns j the cone touches (per cone
 // coff + c its columns cu_col[cu_off[.] ..] and per column u its entries
 // cu_ptr[u] .. cu_ptr[u + 1] as (row b of the cone, index of A[row b, j] in A),

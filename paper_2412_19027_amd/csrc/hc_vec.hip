@@ -542,13 +542,12 @@ void add_P_delta(const Csr& P, int64_t n, double delta, int64_t ld, double* S, h
   HC_LAUNCH_CHECK();
 }
 
-// one task = an unordered pair of rows (ra >= rb, same cone) with the index of
-// M_c[ra, rb]; adds M * (a_ra a_rb' + a_rb a_ra') (or M a a' when ra == rb)
-// into the lower triangle with hardware FP64 atomics.
-// One task adds m (a_ra a_rb' + a_rb a_ra') (m a_ra a_ra' when ra = rb) to the
-// lower triangle of S.  Short tasks run one lane each; long ones (rows with
-// hundreds of entries) one wave each, the lanes striding over the entries of
-// row ra, so no single lane issues the whole row's quadratic update.
+// One task, an unordered pair of rows (ra >= rb, same cone) with the index of
+// m = M_c[ra, rb], adds m (a_ra a_rb' + a_rb a_ra') (m a_ra a_ra' when ra = rb) to
+// the lower triangle of S by hardware FP64 atomics.  Short tasks run one lane
+// each; long ones (rows with hundreds of entries) one wave each, the lanes
+// striding over the entries of row ra, so no single lane issues the whole row's
+// quadratic update.
 template <bool WIDE>
 __global__ __launch_bounds__(256) void k_assemble_pairs(int64_t ntask, const int32_t* __restrict__ tra,
                                                         const int32_t* __restrict__ trb,
@@ -598,11 +597,10 @@ void assemble_pairs(int64_t ntask, const int32_t* tra, const int32_t* trb, const
 
 // T[e, j] = sum_b M_c[a, b] A[row b of cone c, j] for segment row e = c dim + a
 // (M_c symmetric, stored as its lower triangle: entry (a, b), a >= b, at
-// moff + (a (a + 1) / 2 + b) count + c).  One workgroup per row, a thread per
-// column the cone touches summing that column's entries in row order.
-// One workgroup per cone and PT_ROWS rows of T.  Those rows of M_c are staged in
-// LDS (M is packed by cone, so its entries lie `count` apart), a thread takes a
-// column and loads each of its entries once for all PT_ROWS rows; with a row of
+// moff + (a (a + 1) / 2 + b) count + c).  One workgroup per cone and PT_ROWS rows
+// of T: those rows of M_c are staged in LDS (M is packed by cone, so its entries
+// lie `count` apart), a thread takes a column the cone touches and loads each of
+// its entries, in row order, once for all PT_ROWS rows; with a row of
 // T per workgroup, every term was two loads of scattered lines.  30 cones each
 // of sides 20 and 32 on 1,800 columns, both segments: 826 -> 241 us.
 constexpr int PT_ROWS = 8;
